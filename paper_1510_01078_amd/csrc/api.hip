@@ -27,6 +27,8 @@ using patsz::next_smooth_even;
 // exact-division multiplier for x < 2^16, d < 2^16 (0 encodes d == 1)
 inline uint32_t div_magic(int d) { return d == 1 ? 0u : uint32_t((uint64_t(1) << 32) / uint64_t(d) + 1); }
 
+void two_pass_plan(int n, patk::Fft2Raw& f);
+
 bool radix_plan(int n, patk::FftRaw& f) {
   f.n = n;
   f.npass = 0;
@@ -49,7 +51,35 @@ bool radix_plan(int n, patk::FftRaw& f) {
     p *= radix[i];
   }
   f.npass = np;
+  two_pass_plan(n, f.two);
   return true;
+}
+
+// Radices of the two-pass register transform: the largest r1 <= r2 of the
+// radices the kernels hold (every even 2,3,5-smooth length up to 640 has a
+// pair; longer ones need radices whose registers cost occupancy, and keep the
+// passes in LDS). 288 and 320 points take r2 = 16 with r1 = 18 and 20: the
+// first pass then loads whole 128-byte lines and fills its waves (x and y
+// passes of a 192^3 image 84.8 and 49.3 us, 93.3 and 54.2 us as 16 * 18; the
+// same order lost 10 to 20 % at 384 = 24 * 16 and 480 = 30 * 16, whose first
+// pass holds more registers, and at 192 = 16 * 12).
+void two_pass_plan(int n, patk::Fft2Raw& f) {
+  f = patk::Fft2Raw{0, 0, 0, 0, 0, 0, nullptr};
+  if (n > 640) return;
+  if (n % 16 == 0 && n / 16 > 16 && n / 16 <= 20) {
+    f.r1 = n / 16;  // 18 or 20: no other of these is 2,3,5-smooth
+    f.r2 = 16;
+    return;
+  }
+  for (int r1 : {20, 18, 16, 15, 12, 10, 9, 8, 6, 5, 4, 3, 2}) {
+    if (n % r1 != 0 || n / r1 < r1) continue;
+    for (int r2 : {2, 3, 4, 5, 6, 8, 9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 30, 32})
+      if (r1 * r2 == n) {
+        f.r1 = r1;
+        f.r2 = r2;
+        return;
+      }
+  }
 }
 
 struct HostBlob {
@@ -76,6 +106,19 @@ size_t add_twiddles(HostBlob& b, int n) {
     t[2 * i] = T(std::cos(a));
     t[2 * i + 1] = T(std::sin(a));
   }
+  return b.add(t.data(), t.size() * sizeof(T));
+}
+
+// tw[k*r2 + i] = exp(-2 pi i ik/n) of the two-pass transform
+template <typename T>
+size_t add_twiddles2(HostBlob& b, int n, const patk::Fft2Raw& f) {
+  std::vector<T> t(2 * size_t(f.r1) * f.r2);
+  for (int k = 0; k < f.r1; ++k)
+    for (int i = 0; i < f.r2; ++i) {
+      const double a = -2.0 * M_PI * double(i * k % n) / double(n);
+      t[2 * (size_t(k) * f.r2 + i)] = T(std::cos(a));
+      t[2 * (size_t(k) * f.r2 + i) + 1] = T(std::sin(a));
+    }
   return b.add(t.data(), t.size() * sizeof(T));
 }
 
@@ -377,7 +420,7 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   // the y-FFT transforms only these (x mode, bin) pairs.
   std::vector<int> jr(2 * size_t(d.nx));
   {
-    const int ybins = patk::fft_batch<T>(dp.n_y, patk::kFftThreads, patk::kFftCap);
+    const int ybins = patk::fft_bins<T>(dp.f_ny, patk::kFftThreads, patk::kFftCap);
     const int wt = dp.w_t;
     auto base = [&](double sv) {
       long b = (long)std::floor(sv) - wt / 2 + 1 - dp.b_lo;
@@ -402,7 +445,7 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   // major: its grid holds these only (no work-groups that would return at once)
   std::vector<int> yl;
   {
-    const int ybins = patk::fft_batch<T>(dp.n_y, patk::kFftThreads, patk::kFftCap);
+    const int ybins = patk::fft_bins<T>(dp.f_ny, patk::kFftThreads, patk::kFftCap);
     for (int jj = 0; jj < d.nx; ++jj)
       for (int b = jr[2 * jj]; b <= jr[2 * jj + 1]; b += ybins) yl.push_back(jj << 16 | (b / ybins));
   }
@@ -434,7 +477,8 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   const size_t o_tw_Ny = add_twiddles<T>(blob, d.ny);
   const size_t o_tw_Nz = add_twiddles<T>(blob, d.nz);
   patk::FftRaw* ffts[6] = {&dp.f_nt, &dp.f_nx, &dp.f_ny, &dp.f_Nx, &dp.f_Ny, &dp.f_Nz};
-  size_t o_pass[6];
+  size_t o_pass[6], o_tw2[6];
+  for (int i = 0; i < 6; ++i) o_tw2[i] = add_twiddles2<T>(blob, ffts[i]->n, ffts[i]->two);
   for (int i = 0; i < 6; ++i) o_pass[i] = blob.add(ffts[i]->pass, sizeof(patk::FftPassRaw) * ffts[i]->npass);
 
   P->dev_bytes = align_up(blob.bytes.size());
@@ -471,7 +515,10 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   dp.f_Nx.tw = at(o_tw_Nx);
   dp.f_Ny.tw = at(o_tw_Ny);
   dp.f_Nz.tw = at(o_tw_Nz);
-  for (int i = 0; i < 6; ++i) ffts[i]->dpass = at(o_pass[i]);
+  for (int i = 0; i < 6; ++i) {
+    ffts[i]->dpass = at(o_pass[i]);
+    ffts[i]->two.tw = at(o_tw2[i]);
+  }
 
   // Spread and x-FFT can run in rounds of chunk_bins bins through one smaller
   // grid buffer (a multiple of the spread's 16-bin groups). One round is the

@@ -10,6 +10,8 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "kernels_common.hpp"
@@ -34,7 +36,9 @@ struct BatchGroup {
   std::vector<int> members;   // problem indices, ascending grid size
   void* tables = nullptr;     // argument tables and prefix sums
   size_t table_bytes = 0;
-  patk::BatchStage st[kStages];
+  // launches of each stage: one, or for the FFT stages one per class of
+  // two-pass transform among the problems' lengths (fft_reg.hpp)
+  std::vector<patk::BatchStage> st[kStages];
 };
 
 struct pat_batch {
@@ -99,9 +103,15 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
   std::vector<patk::GatherBA> a4(P);
   std::vector<patk::CfftBA> a5(P);
   std::vector<patk::C2rBA> a6(P);
-  std::vector<int> pre[kStages];
-  for (auto& v : pre) v.assign(P + 1, 0);
-  size_t lds[kStages] = {};
+  // per stage and problem: work items, LDS bytes, work-group size and variant
+  std::vector<int> pre[kStages], threads[kStages], variant[kStages];
+  std::vector<size_t> lds[kStages];
+  for (int i = 0; i < kStages; ++i) {
+    pre[i].assign(P, 0);
+    threads[i].assign(P, 256);
+    variant[i].assign(P, 0);
+    lds[i].assign(P, 0);
+  }
   const int kFft = patk::kFftMaxV * cfg.threads;
   size_t off = 0;
   for (int p = 0; p < P; ++p) {
@@ -116,28 +126,34 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     if (d.n_t > patk::kFftMaxV * 512) return PAT_ERR_UNSUPPORTED;
     // stage 0: temporal FFT, one block per sensor pair
     a0[p] = patk::TemporalBA{d.hw, d.deap, patk::as_view(d.f_nt), d.M, d.Nt, d.n0, d.b_lo, d.nb, C};
-    pre[0][p + 1] = (d.M + 1) / 2;
-    lds[0] = std::max(lds[0], size_t(patk::temporal_lds_slots(d.n_t)) * c);
+    pre[0][p] = (d.M + 1) / 2;
+    lds[0][p] = size_t(patk::temporal_lds_slots(d.n_t)) * c;
     // stage 1: spread, all bins in one round
     const int nchunks = (d.nb + 15) / 16;
     a1[p] = patk::SpreadBA{C, d.slot_off, d.slot_sens, d.slot_w, d.slot_k, d.nb, d.n_x, d.n_y, d.tiles_x, nchunks, A};
-    pre[1][p + 1] = d.tiles_x * d.patches_y * ((nchunks + patk::kSpreadGroups - 1) / patk::kSpreadGroups);
+    pre[1][p] = d.tiles_x * d.patches_y * ((nchunks + patk::kSpreadGroups - 1) / patk::kSpreadGroups);
     // stage 2: FFT along x
-    const int rows = patk::fft_batch<T>(d.n_x, cfg.threads, cfg.cap);
-    if (rows * d.n_x > kFft || rows * d.Nx > kFft) return PAT_ERR_UNSUPPORTED;
+    const int rows = patk::fft_seqs<T>(d.f_nx, cfg.threads, cfg.cap);
+    const patk::Fft2Raw fx = d.f_nx.two.r1 ? patk::fft2_shape<T>(d.f_nx, rows) : d.f_nx.two;
+    if (!fx.r1 && (rows * d.n_x > kFft || rows * d.Nx > kFft)) return PAT_ERR_UNSUPPORTED;
     const int gx2 = (d.n_y + rows - 1) / rows;
-    a2[p] = patk::FftXBA{A, patk::as_view(d.f_nx), d.n_y, d.Nx, rows, gx2, Bw, d.jrange ? d.brange : nullptr};
-    pre[2][p + 1] = gx2 * d.nb;
-    lds[2] = std::max(lds[2], (size_t(rows) * patk::lseq(d.n_x) + d.n_x) * c);
+    a2[p] = patk::FftXBA{A, patk::as_view(d.f_nx), fx, d.n_y, d.Nx, rows, gx2, Bw, d.jrange ? d.brange : nullptr};
+    pre[2][p] = gx2 * d.nb;
+    lds[2][p] = (fx.r1 ? patk::fft2_slots(fx) : size_t(rows) * patk::lseq(d.n_x) + d.n_x) * c;
+    variant[2][p] = fx.r1 ? patk::reg_class(fx) : 0;
+    threads[2][p] = fx.r1 ? patk::fft2_threads(fx) : cfg.threads;
     // stage 3: FFT along y with deconvolution
-    const int bins = patk::fft_batch<T>(d.n_y, cfg.threads, cfg.cap);
-    if (bins * d.n_y > kFft || bins * d.Ny > kFft) return PAT_ERR_UNSUPPORTED;
+    const int bins = patk::fft_bins<T>(d.f_ny, cfg.threads, cfg.cap);
+    const patk::Fft2Raw fy = d.f_ny.two.r1 ? patk::fft2_shape<T>(d.f_ny, bins) : d.f_ny.two;
+    if (!fy.r1 && (bins * d.n_y > kFft || bins * d.Ny > kFft)) return PAT_ERR_UNSUPPORTED;
     const int gx3 = (d.nb + bins - 1) / bins;
     const bool listed = d.ylist && d.ylist_n > 0 && d.jrange;
-    a3[p] = patk::FftYBA{Bw, d.dcx, d.dcy, patk::as_view(d.f_ny), d.nb, d.Nx, d.Ny, bins, gx3, A, d.jrange,
+    a3[p] = patk::FftYBA{Bw, d.dcx, d.dcy, patk::as_view(d.f_ny), fy, d.nb, d.Nx, d.Ny, bins, gx3, A, d.jrange,
                          listed ? d.ylist : nullptr};
-    pre[3][p + 1] = listed ? d.ylist_n : gx3 * d.Nx;
-    lds[3] = std::max(lds[3], (size_t(bins) * patk::lseq(d.n_y) + d.n_y) * c);
+    pre[3][p] = listed ? d.ylist_n : gx3 * d.Nx;
+    lds[3][p] = (fy.r1 ? patk::fft2_slots(fy) : size_t(bins) * patk::lseq(d.n_y) + d.n_y) * c;
+    variant[3][p] = fy.r1 ? patk::reg_class(fy) : 0;
+    threads[3][p] = fy.r1 ? patk::fft2_threads(fy) : cfg.threads;
     // stage 4: temporal interpolation and weight (image-ready spectrum) fused
     // with the inverse transform along x
     const int lcx = patk::fft_batch<T>(d.Nx, icfg.threads, patk::kGatherCap);
@@ -148,39 +164,58 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     a4[p] = patk::GatherBA{A, d.hcoef, d.nb, d.b_lo, d.Nx, d.Ny, d.Nz, d.w_t, d.hdeg, wt_ct, 0,
                            d.s_per_k, d.kxu, d.kyu, d.kzu, d.two_c, d.n0_over_nt, d.inv_vol, Bw,
                            patk::as_view(d.f_Nx), lcx, gx5};
-    pre[4][p + 1] = gx5 * d.Ny;
-    lds[4] = std::max(lds[4], (size_t(lcx) * patk::lseq(d.Nx) + d.Nx) * c);
+    pre[4][p] = gx5 * d.Ny;
+    lds[4][p] = (size_t(lcx) * patk::lseq(d.Nx) + d.Nx) * c;
     // stage 5: inverse transform along y (in place on the spectrum)
     const int lcy = patk::fft_batch<T>(d.Ny, icfg.threads, icfg.cap);
     const int gx6 = (Lh + lcy - 1) / lcy;
     a5[p] = patk::CfftBA{Bw, patk::as_view(d.f_Ny), d.Ny, Lh, lcy, gx6};
-    pre[5][p + 1] = gx6 * d.Nx;
-    lds[5] = std::max(lds[5], (size_t(lcy) * patk::lseq(d.Ny) + d.Ny) * c);
+    pre[5][p] = gx6 * d.Nx;
+    lds[5][p] = (size_t(lcy) * patk::lseq(d.Ny) + d.Ny) * c;
     // stage 6: complex-to-real along z into the caller's image
     const int rz = patk::fft_batch<T>(d.Nz, icfg.threads, icfg.cap);
     const long long nrows = (long long)d.Nx * d.Ny;
     a6[p] = patk::C2rBA{Bw, patk::as_view(d.f_Nz), nrows, rz};
-    pre[6][p + 1] = int((nrows + rz - 1) / rz);
+    pre[6][p] = int((nrows + rz - 1) / rz);
     if ((rz + 1) / 2 * (d.Nz / 2 + 1) > patk::kC2rStage * icfg.threads) return PAT_ERR_UNSUPPORTED;
-    lds[6] = std::max(lds[6], size_t(patk::c2r_lds_slots(rz, d.Nz)) * c);
+    lds[6][p] = size_t(patk::c2r_lds_slots(rz, d.Nz)) * c;
   }
-  for (auto& v : pre) {
-    for (int p = 0; p < P; ++p) {
-      const long long next = (long long)v[p] + v[p + 1];
-      if (next > 0x7fffffffLL) return PAT_ERR_UNSUPPORTED;
-      v[p + 1] = int(next);
-    }
-  }
+  // each stage's launches: the problems of one variant, their arguments and
+  // the running sums of their work items
   Blob blob;
-  size_t oa[kStages], op[kStages];
-  oa[0] = blob.add(a0.data(), a0.size() * sizeof(a0[0]));
-  oa[1] = blob.add(a1.data(), a1.size() * sizeof(a1[0]));
-  oa[2] = blob.add(a2.data(), a2.size() * sizeof(a2[0]));
-  oa[3] = blob.add(a3.data(), a3.size() * sizeof(a3[0]));
-  oa[4] = blob.add(a4.data(), a4.size() * sizeof(a4[0]));
-  oa[5] = blob.add(a5.data(), a5.size() * sizeof(a5[0]));
-  oa[6] = blob.add(a6.data(), a6.size() * sizeof(a6[0]));
-  for (int i = 0; i < kStages; ++i) op[i] = blob.add(pre[i].data(), pre[i].size() * sizeof(int));
+  const bool kahan = B->plans[0]->dp.kahan;
+  std::vector<std::pair<size_t, size_t>> at[kStages];
+  auto add_stage = [&](int i, const auto& args) {
+    std::vector<int> kinds(variant[i]);
+    std::sort(kinds.begin(), kinds.end());
+    kinds.erase(std::unique(kinds.begin(), kinds.end()), kinds.end());
+    for (int kind : kinds) {
+      std::vector<typename std::decay_t<decltype(args)>::value_type> part;
+      std::vector<int> prefix(1, 0);
+      patk::BatchStage st;
+      for (int p = 0; p < P; ++p) {
+        if (variant[i][p] != kind) continue;
+        const long long next = (long long)prefix.back() + pre[i][p];
+        if (next > 0x7fffffffLL) return false;
+        part.push_back(args[p]);
+        prefix.push_back(int(next));
+        st.lds = std::max(st.lds, lds[i][p]);
+        st.threads = std::max(part.size() == 1 ? 0 : st.threads, threads[i][p]);
+      }
+      st.nprob = int(part.size());
+      st.total = prefix.back();
+      st.grid = kPersistentBlocks;
+      st.kahan = kahan;
+      st.variant = kind;
+      const size_t oa = blob.add(part.data(), part.size() * sizeof(part[0]));
+      at[i].emplace_back(oa, blob.add(prefix.data(), prefix.size() * sizeof(int)));
+      G.st[i].push_back(st);
+    }
+    return true;
+  };
+  if (!add_stage(0, a0) || !add_stage(1, a1) || !add_stage(2, a2) || !add_stage(3, a3) || !add_stage(4, a4) ||
+      !add_stage(5, a5) || !add_stage(6, a6))
+    return PAT_ERR_UNSUPPORTED;
   G.table_bytes = align_up(blob.bytes.size());
   G.tables = dev_alloc(B->alloc_desc, G.table_bytes);
   if (!G.tables) return PAT_ERR_ALLOC;
@@ -190,16 +225,11 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     return PAT_ERR_HIP;
   }
   unsigned char* tb = static_cast<unsigned char*>(G.tables);
-  const bool kahan = B->plans[0]->dp.kahan;
-  for (int i = 0; i < kStages; ++i) {
-    G.st[i].args = tb + oa[i];
-    G.st[i].prefix = reinterpret_cast<const int*>(tb + op[i]);
-    G.st[i].nprob = P;
-    G.st[i].total = pre[i][P];
-    G.st[i].lds = lds[i];
-    G.st[i].grid = kPersistentBlocks;
-    G.st[i].kahan = kahan;
-  }
+  for (int i = 0; i < kStages; ++i)
+    for (size_t v = 0; v < G.st[i].size(); ++v) {
+      G.st[i][v].args = tb + at[i][v].first;
+      G.st[i][v].prefix = reinterpret_cast<const int*>(tb + at[i][v].second);
+    }
   return PAT_OK;
 }
 
@@ -253,14 +283,16 @@ pat_status run_batch(pat_batch* B, const void* const* g, void* const* f, hipStre
       io.in[i] = g[G.members[i]];
       io.out[i] = f[G.members[i]];
     }
-    hipError_t e;
-    if ((e = patk::launch_temporal_batch<T>(G.st[0], io, s)) != hipSuccess) return to_status(e);
-    if ((e = patk::launch_spread_batch<T>(G.st[1], io, s)) != hipSuccess) return to_status(e);
-    if ((e = patk::launch_fft_x_batch<T>(G.st[2], io, s)) != hipSuccess) return to_status(e);
-    if ((e = patk::launch_fft_y_batch<T>(G.st[3], io, s)) != hipSuccess) return to_status(e);
-    if ((e = patk::launch_gather_batch<T>(G.st[4], io, s)) != hipSuccess) return to_status(e);
-    if ((e = patk::launch_cfft_y_inv_batch<T>(G.st[5], io, s)) != hipSuccess) return to_status(e);
-    if ((e = patk::launch_c2r_z_batch<T>(G.st[6], io, s)) != hipSuccess) return to_status(e);
+    using Launch = hipError_t (*)(const patk::BatchStage&, const patk::BatchIO&, hipStream_t);
+    const Launch launch[kStages] = {patk::launch_temporal_batch<T>, patk::launch_spread_batch<T>,
+                                    patk::launch_fft_x_batch<T>, patk::launch_fft_y_batch<T>,
+                                    patk::launch_gather_batch<T>, patk::launch_cfft_y_inv_batch<T>,
+                                    patk::launch_c2r_z_batch<T>};
+    for (int i = 0; i < kStages; ++i)
+      for (const patk::BatchStage& st : G.st[i]) {
+        const hipError_t e = launch[i](st, io, s);
+        if (e != hipSuccess) return to_status(e);
+      }
   }
   return PAT_OK;
 }
@@ -318,7 +350,8 @@ pat_status pat_batch_get_plan(const pat_batch* B, int32_t index, const pat_plan*
 pat_status pat_batch_set_grid(pat_batch* B, int32_t blocks) {
   if (!B || blocks < 0) return PAT_ERR_INVALID_ARGUMENT;
   for (auto& g : B->groups)
-    for (auto& s : g.st) s.grid = blocks;
+    for (auto& stage : g.st)
+      for (auto& s : stage) s.grid = blocks;
   return PAT_OK;
 }
 

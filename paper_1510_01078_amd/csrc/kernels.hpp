@@ -22,9 +22,20 @@ struct FftPassRaw {
   uint32_t m_nbf = 0, m_p = 0;
 };
 
+// Two-pass register transform (fft_reg.hpp) of a length n = r1*r2; r1 = 0:
+// the length has none. P, Q and ls (LDS strides, log2 of the sequences per
+// work-group) depend on the kernel and are set where it is launched.
+struct Fft2Raw {
+  int r1, r2;
+  int P, Q, ls;
+  int pad;
+  const void* tw;  // device, tw[k*r2 + i] = exp(-2 pi i ik/n), k < r1, i < r2
+};
+
 struct FftRaw {
   int n = 0;
   int npass = 0;
+  Fft2Raw two{0, 0, 0, 0, 0, 0, nullptr};
   FftPassRaw pass[12];           // host copy
   const void* dpass = nullptr;   // device copy of pass[0..npass)
   const void* tw = nullptr;      // device, n complex entries exp(-2 pi i t/n)
@@ -175,10 +186,10 @@ struct SpreadBA {
   int nb, n_x, n_y, tiles_x, nchunks; void* U;
 };
 struct FftXBA {
-  const void* U; FftView fd; int n_y, Nx, rows, gx; void* V; const int* brange;
+  const void* U; FftView fd; Fft2Raw f2; int n_y, Nx, rows, gx; void* V; const int* brange;
 };
 struct FftYBA {
-  const void* V; const void* dcx; const void* dcy; FftView fd; int nb, Nx, Ny, bins, gx; void* Gh;
+  const void* V; const void* dcx; const void* dcy; FftView fd; Fft2Raw f2; int nb, Nx, Ny, bins, gx; void* Gh;
   const int* jrange;  // per x-mode band range (bin groups outside it are skipped)
   const int* ylist;   // the work items inside the ranges (jj << 16 | bin group), or nullptr: gx * Nx items
 };
@@ -207,6 +218,8 @@ struct BatchStage {
   size_t lds = 0;
   int grid = 0;
   bool kahan = false;  // spread with compensated summation
+  int variant = 0;     // FFT stages: class of the problems' two-pass transforms (0: longer lengths)
+  int threads = 256;   // FFT stages: work-group size
 };
 
 // tap counts the batched gather instantiates at compile time (each problem

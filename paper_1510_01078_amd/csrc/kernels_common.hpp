@@ -9,6 +9,7 @@
 #include <utility>
 
 #include "fft_device.hpp"
+#include "fft_reg.hpp"
 #include "kernels.hpp"
 
 namespace patk {
@@ -27,6 +28,46 @@ static inline int fft_batch(int n, int nthr, int cap) {
   if (b > cap) b = cap;
   return b < 1 ? 1 : b;
 }
+
+// Sequences per work-group of an FFT stage: a power of two for lengths with a
+// two-pass register transform (one butterfly per thread, so at most
+// nthr / the larger radix of them), else fft_batch.
+template <typename T>
+static inline int fft_seqs(const FftRaw& f, int nthr, int cap) {
+  if (!f.two.r1) return fft_batch<T>(f.n, nthr, cap);
+  int s = 1;
+  while (2 * s <= cap && 2 * s * reg_larger(f.two) <= nthr) s *= 2;
+  return s;
+}
+
+// Bins per work-group of the y passes (the band ranges are whole groups of
+// them): also within what the transposed pass holds with its passes in LDS.
+template <typename T>
+static inline int fft_bins(const FftRaw& f, int nthr, int cap) {
+  const int most = fft_batch<T>(f.n, nthr, cap);
+  int s = fft_seqs<T>(f, nthr, cap);
+  while (s > most) s /= 2;
+  return s;
+}
+
+// Launch shape of a two-pass transform of S = fft_seqs sequences. Q is odd
+// (lanes on consecutive k read distinct banks); P puts S consecutive
+// sequences of one index on the banks that S neighbours leave free (a wave
+// walks sequences fastest when it reads or writes columns).
+template <typename T>
+static inline Fft2Raw fft2_shape(const FftRaw& f, int S) {
+  Fft2Raw t = f.two;
+  constexpr int U = 256 / int(2 * sizeof(T));  // complex values across the 64 banks
+  t.Q = t.r2 | 1;
+  t.ls = 0;
+  while ((1 << t.ls) < S) ++t.ls;
+  t.P = t.r1 * t.Q;
+  if (S > 1 && S <= U)
+    while (t.P % (2 * U / S) != U / S) ++t.P;
+  return t;
+}
+static inline size_t fft2_slots(const Fft2Raw& t) { return size_t(t.P) << t.ls; }
+static inline int fft2_threads(const Fft2Raw& t) { return ((reg_larger(t) << t.ls) + 63) / 64 * 64; }
 
 // Transform the nseq sequences of length fd.n in LDS. Sequences of at most
 // 1024 points are each owned by one wave (no work-group barriers inside the

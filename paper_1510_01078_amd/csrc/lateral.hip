@@ -12,14 +12,58 @@ namespace patk {
 // Stage 2: FFT along x of every grid row, keeping the Nx centred modes.
 // U[b][py][px] -> V[b][jj][py], jj = j mod Nx for j in [-Nx/2, Nx/2).
 // ---------------------------------------------------------------------------
-template <typename T, int NCT = 0>
+// Two-pass register transform: the first pass loads straight from the grid
+// rows (a wave walks along a row), the second stores straight to the columns
+// (a wave walks S rows of one mode, so S*8 bytes of one line). Bound by HBM
+// (the grid is read once) and by the vector ALU's DFT arithmetic; LDS is
+// crossed once.
+template <typename T, int CLS>
+__device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int n_y, int Nx, int b_begin,
+                                               const Fft2<T>& f, cx<T>* __restrict__ V, int bx, int by,
+                                               const int* __restrict__ brange, int tid) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
+  const int S = 1 << f.ls;
+  const int n_x = f.r1 * f.r2;
+  const int b = b_begin + by;
+  const int py0 = bx << f.ls;
+  const int nr = min(S, n_y - py0);
+  const cx<T>* src = U + (size_t(by) * n_y + py0) * n_x;
+  {
+    const int s = small_div(tid, f.r2), i = tid - s * f.r2;
+    if (s < nr)
+      reg_first_any<T, CLS, false>(f, buf + s * f.P, i, [&](int e) { return cx_at(src, unsigned(s * n_x + e)); });
+  }
+  __syncthreads();
+  const int s = tid & (S - 1), k = tid >> f.ls;
+  if (k < f.r1 && s < nr) {
+    // modes j = 0 .. Nx/2-1 sit at column j, j = -Nx/2 .. -1 (element
+    // n_x + j) at column Nx + j; only those whose band range holds bin b
+    // (|j| in [J0, J1]) are written: the y-FFT and the interpolation read no
+    // others
+    const int J0 = brange ? brange[2 * b] : 0, J1 = brange ? brange[2 * b + 1] : Nx;
+    const int p0 = J0, p1 = min(J1, Nx / 2 - 1);                    // elements of the non-negative modes
+    const int m0 = n_x - min(J1, Nx / 2), m1 = n_x - max(J0, 1);    // and of the negative ones
+    cx<T>* dst = V + size_t(b) * Nx * n_y + py0 + s;
+    reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
+      const int e = k + q * f.r1;
+      if (e >= p0 && e <= p1)
+        cx_at(dst, unsigned(e * n_y)) = v;
+      else if (e >= m0 && e <= m1)
+        cx_at(dst, unsigned((e - (n_x - Nx)) * n_y)) = v;
+    });
+  }
+}
+
+// Longer lengths: passes in LDS, runtime plan.
+template <typename T>
 __device__ __forceinline__ void fft_x_body(const cx<T>* __restrict__ U, int n_y, int Nx, int rows,
                                            int b_begin, FftDesc<T> fd, cx<T>* __restrict__ V, int wm, int bx, int by,
                                            const int* __restrict__ brange = nullptr, int tid = threadIdx.x) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   const int nthr = blockDim.x;
-  const int n_x = NCT > 0 ? NCT : fd.n;
+  const int n_x = fd.n;
   const int bstride = lseq(n_x);
   const int b = b_begin + by;
   const int py0 = bx * rows;
@@ -39,80 +83,74 @@ __device__ __forceinline__ void fft_x_body(const cx<T>* __restrict__ U, int n_y,
     return aj >= J0 && aj <= J1;
   };
   cx<T>* twl = buf + rows * bstride;
-  if constexpr (NCT > 0) {
-    // compile-time geometry (rows = ROWS, 256 threads): no index divisions
-    constexpr int ROWS = ct_maxb(NCT, kFftCap), BS = lseq(NCT);
-    staged_rows<ROWS, NCT, kFftThreads>(
-        nr, tid, [&](int r, int c) { return src[r * NCT + c]; },
-        [&](int r, int c, cx<T> v) { buf[r * BS + lpos(c)] = v; });
-    for (int t = tid; t < NCT; t += kFftThreads) twl[t] = fd.tw[t];
-    __syncthreads();
-    fft_ct<T, NCT, kFftThreads, ROWS, false>(buf, nr, twl, tid);
-    __syncthreads();
-    // V[b][jj][py0 + r]: neighbouring threads write neighbouring rows
-    cx<T>* d0 = dst + size_t(tid / ROWS) * n_y + tid % ROWS;
-    const size_t step = size_t(kFftThreads / ROWS) * n_y;
-    staged_cols<ROWS, kFftThreads, (NCT * ROWS + kFftThreads - 1) / kFftThreads>(  // Nx < n_x = NCT
-        Nx, nr, tid,
-        [&](int jj, int r, int) { return kept(jj) ? buf[r * BS + slot(jj)] : cx<T>{T(0), T(0)}; },
-        [&](int jj, int, int u, cx<T> v) {
-          if (kept(jj)) d0[u * step] = v;
-        });
-  } else {
-    const FastDiv div_nx(n_x), div_nr(nr);
-    staged_copy<kFftMaxV>(
-        nr * n_x, tid, nthr, [&](int q) { return src[q]; },
-        [&](int q, cx<T> v) {
-          const int r = div_nx(q);
-          buf[r * bstride + lpos(q - r * n_x)] = v;
-        });
-    // the twiddles go to LDS behind the rows (every pass reads them)
-    for (int t = tid; t < fd.n; t += nthr) twl[t] = fd.tw[t];
-    __syncthreads();
-    fft_group<T, false>(buf, lds_twiddles(fd, twl), nr, bstride, tid, nthr, wm);
-    __syncthreads();
-    staged_copy<kFftMaxV>(
-        nr * Nx, tid, nthr,
-        [&](int q) {
-          const int jj = div_nr(q);
-          return kept(jj) ? buf[(q - jj * nr) * bstride + slot(jj)] : cx<T>{T(0), T(0)};
-        },
-        [&](int q, cx<T> v) {
-          const int jj = div_nr(q);
-          if (kept(jj)) dst[size_t(jj) * n_y + (q - jj * nr)] = v;
-        });
-  }
+  const FastDiv div_nx(n_x), div_nr(nr);
+  staged_copy<kFftMaxV>(
+      nr * n_x, tid, nthr, [&](int q) { return src[q]; },
+      [&](int q, cx<T> v) {
+        const int r = div_nx(q);
+        buf[r * bstride + lpos(q - r * n_x)] = v;
+      });
+  // the twiddles go to LDS behind the rows (every pass reads them)
+  for (int t = tid; t < fd.n; t += nthr) twl[t] = fd.tw[t];
+  __syncthreads();
+  fft_group<T, false>(buf, lds_twiddles(fd, twl), nr, bstride, tid, nthr, wm);
+  __syncthreads();
+  staged_copy<kFftMaxV>(
+      nr * Nx, tid, nthr,
+      [&](int q) {
+        const int jj = div_nr(q);
+        return kept(jj) ? buf[(q - jj * nr) * bstride + slot(jj)] : cx<T>{T(0), T(0)};
+      },
+      [&](int q, cx<T> v) {
+        const int jj = div_nr(q);
+        if (kept(jj)) dst[size_t(jj) * n_y + (q - jj * nr)] = v;
+      });
 }
 
-template <typename T, int NCT>
+template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_fft_x(const cx<T>* __restrict__ U, int n_y, int Nx, int rows,
                                                      int b_begin, FftDesc<T> fd, cx<T>* __restrict__ V, int wm,
                                                      const int* __restrict__ brange) {
   // neighbouring groups write the two halves of each 128-byte output line:
   // keep them on one XCD so its L2 merges the halves
   const int gl = xcd_linear();
-  fft_x_body<T, NCT>(U, n_y, Nx, rows, b_begin, fd, V, wm, gl % gridDim.x, gl / gridDim.x, brange);
+  fft_x_body<T>(U, n_y, Nx, rows, b_begin, fd, V, wm, gl % gridDim.x, gl / gridDim.x, brange);
+}
+
+template <typename T, int CLS>
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_x_reg(const cx<T>* __restrict__ U, int n_y, int Nx, int b_begin,
+                                                           Fft2Raw f, cx<T>* __restrict__ V,
+                                                           const int* __restrict__ brange) {
+  const int gl = xcd_linear();
+  fft_x_reg_body<T, CLS>(U, n_y, Nx, b_begin, as_fft2<T>(f), V, gl % gridDim.x, gl / gridDim.x, brange, threadIdx.x);
 }
 
 template <typename T>
 hipError_t launch_fft_x(const DevPlan& p, const void* U, void* V, int b_begin, int b_end, hipStream_t s) {
+  if (b_begin < 0 || b_end > p.nb || b_begin >= b_end) return hipErrorInvalidValue;
   const FftCfg cfg = fft_cfg();
-  const int rows = fft_batch<T>(p.n_x, cfg.threads, cfg.cap);
+  const int rows = fft_seqs<T>(p.f_nx, cfg.threads, cfg.cap);
+  const dim3 grid((p.n_y + rows - 1) / rows, b_end - b_begin);
+  if (p.f_nx.two.r1) {
+    const Fft2Raw f = fft2_shape<T>(p.f_nx, rows);
+    const size_t lds = fft2_slots(f) * sizeof(cx<T>);
+    return class_pick(f, [&](auto c) {
+      constexpr auto kern = &k_fft_x_reg<T, decltype(c)::value>;
+      hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(kern, grid, dim3(fft2_threads(f)), lds, s, static_cast<const cx<T>*>(U), p.n_y, p.Nx, b_begin,
+                         f, static_cast<cx<T>*>(V), p.brange);
+      return hipGetLastError();
+    });
+  }
   const size_t lds = (size_t(rows) * lseq(p.n_x) + p.n_x) * sizeof(cx<T>);
-  if (size_t(rows) * p.n_x > size_t(kFftMaxV) * cfg.threads || size_t(rows) * p.Nx > size_t(kFftMaxV) * cfg.threads ||
-      b_begin < 0 || b_end > p.nb || b_begin >= b_end)
+  if (size_t(rows) * p.n_x > size_t(kFftMaxV) * cfg.threads || size_t(rows) * p.Nx > size_t(kFftMaxV) * cfg.threads)
     return hipErrorInvalidValue;
-  auto go = [&](auto kern, int nct) {
-    // the compile-time kernels take their geometry from the length
-    if (nct > 0 && (rows != ct_maxb(nct, kFftCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
-    hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
-    if (e != hipSuccess) return e;
-    dim3 grid((p.n_y + rows - 1) / rows, b_end - b_begin);
-    hipLaunchKernelGGL(kern, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(U), p.n_y, p.Nx, rows,
-                       b_begin, as_desc<T>(p.f_nx), static_cast<cx<T>*>(V), cfg.wave, p.brange);
-    return hipGetLastError();
-  };
-  return ct_pick(CtLateral{}, p.n_x, [&](auto c) { return go(&k_fft_x<T, decltype(c)::value>, decltype(c)::value); });
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_fft_x<T>), lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_fft_x<T>, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(U), p.n_y, p.Nx, rows,
+                     b_begin, as_desc<T>(p.f_nx), static_cast<cx<T>*>(V), cfg.wave, p.brange);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -122,7 +160,49 @@ hipError_t launch_fft_x(const DevPlan& p, const void* U, void* V, int b_begin, i
 // ---------------------------------------------------------------------------
 // jrange (may be nullptr): groups of bins outside the x-mode's range are
 // skipped (the interpolation never reads them).
-template <typename T, int NCT = 0>
+//
+// Two-pass register transform (as the x pass): rows in along a row, out with
+// a wave on S bins of one mode. Non-temporal loads: each band row is read
+// once, and keeping it out of the caches leaves them to the spectra this
+// kernel writes, which the gather reads next.
+template <typename T, int CLS>
+__device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int nb, int Nx, int Ny,
+                                               const T* __restrict__ dcx, const T* __restrict__ dcy,
+                                               const Fft2<T>& f, cx<T>* __restrict__ Gh, int bx, int jj,
+                                               const int* __restrict__ jrange, int tid) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
+  const int S = 1 << f.ls;
+  const int n_y = f.r1 * f.r2;
+  const int b0 = bx << f.ls;
+  const int nbc = min(S, nb - b0);
+  if (jrange && (b0 + nbc - 1 < jrange[2 * jj] || b0 > jrange[2 * jj + 1])) return;
+  {
+    const int s = small_div(tid, f.r2), i = tid - s * f.r2;
+    if (s < nbc) {
+      const cx<T>* src = V + (size_t(b0) * Nx + jj) * n_y;  // bin b0 + s at src + s * Nx * n_y
+      const unsigned at = unsigned(s) * unsigned(Nx * n_y);
+      reg_first_any<T, CLS, false>(f, buf + s * f.P, i, [&](int e) { return nt_load(&cx_at(src, at + unsigned(e))); });
+    }
+  }
+  __syncthreads();
+  const int s = tid & (S - 1), k = tid >> f.ls;
+  if (k < f.r1 && s < nbc) {
+    const T cxj = dcx[jj];
+    cx<T>* dst = Gh + size_t(jj) * Ny * nb + b0 + s;
+    reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
+      // element e holds mode e below Ny/2 and e - n_y from -Ny/2 on
+      const int e = k + q * f.r1;
+      const int kk = e < Ny / 2 ? e : e - (n_y - Ny);
+      if (e < Ny / 2 || e >= n_y - Ny / 2) {
+        const T sc = cxj * dcy[kk];
+        cx_at(dst, unsigned(kk * nb)) = cx<T>{v.x * sc, v.y * sc};
+      }
+    });
+  }
+}
+
+template <typename T>
 __device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, int Nx, int Ny, int bins,
                                            const T* __restrict__ dcx, const T* __restrict__ dcy,
                                            FftDesc<T> fd, cx<T>* __restrict__ Gh, int wm, int bx, int by,
@@ -130,7 +210,7 @@ __device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, 
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   const int nthr = blockDim.x;
-  const int n_y = NCT > 0 ? NCT : fd.n;
+  const int n_y = fd.n;
   const int bstride = lseq(n_y);
   const int jj = by;
   const int b0 = bx * bins;
@@ -146,99 +226,101 @@ __device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, 
     return lpos(k < 0 ? k + n_y : k);
   };
   cx<T>* twl = buf + bins * bstride;
-  if constexpr (NCT > 0) {
-    // compile-time geometry (bins = ROWS, 256 threads): no index divisions
-    constexpr int ROWS = ct_maxb(NCT, kFftCap), BS = lseq(NCT);
-    // non-temporal loads: each band row is read once, and keeping it out of
-    // the caches leaves them to the spectra this kernel writes, which the
-    // gather reads next (y-FFT 0.106 -> 0.104 ms, gather 0.077 -> 0.072 ms)
-    staged_rows<ROWS, NCT, kFftThreads>(
-        nbc, tid, [&](int r, int c) { return nt_load(src + r * bin_stride + c); },
-        [&](int r, int c, cx<T> v) { buf[r * BS + lpos(c)] = v; });
-    for (int t = tid; t < NCT; t += kFftThreads) twl[t] = fd.tw[t];
-    __syncthreads();
-    fft_ct<T, NCT, kFftThreads, ROWS, false>(buf, nbc, twl, tid);
-    __syncthreads();
-    // Gh[jj][kk][b0 + bi]: neighbouring threads write neighbouring bins
-    cx<T>* d0 = dst + size_t(tid / ROWS) * nb + tid % ROWS;
-    const size_t step = size_t(kFftThreads / ROWS) * nb;
-    staged_cols<ROWS, kFftThreads, (NCT * ROWS + kFftThreads - 1) / kFftThreads>(  // Ny < n_y = NCT
-        Ny, nbc, tid,
-        [&](int kk, int bi, int) {
-          const T sc = cxj * dcy[kk];
-          const cx<T> v = buf[bi * BS + slot(kk)];
-          return cx<T>{v.x * sc, v.y * sc};
-        },
-        [&](int, int, int u, cx<T> v) { d0[u * step] = v; });
+  const FastDiv div_ny(n_y), div_nbc(nbc);
+  staged_copy<kFftMaxV>(
+      nbc * n_y, tid, nthr,
+      [&](int q) {
+        const int bi = div_ny(q);
+        return src[bi * bin_stride + (q - bi * n_y)];
+      },
+      [&](int q, cx<T> v) {
+        const int bi = div_ny(q);
+        buf[bi * bstride + lpos(q - bi * n_y)] = v;
+      });
+  for (int t = tid; t < fd.n; t += nthr) twl[t] = fd.tw[t];
+  __syncthreads();
+  fft_group<T, false>(buf, lds_twiddles(fd, twl), nbc, bstride, tid, nthr, wm);
+  __syncthreads();
+  staged_copy<kFftMaxV>(
+      nbc * Ny, tid, nthr,
+      [&](int q) {
+        const int kk = div_nbc(q);
+        const int bi = q - kk * nbc;
+        const T sc = cxj * dcy[kk];
+        const cx<T> v = buf[bi * bstride + slot(kk)];
+        return cx<T>{v.x * sc, v.y * sc};
+      },
+      [&](int q, cx<T> v) {
+        const int kk = div_nbc(q);
+        dst[size_t(kk) * nb + (q - kk * nbc)] = v;
+      });
+}
+
+// (x mode, bin group) of a work-group: from the list of work items inside the
+// ranges, or the two-dimensional grid of all
+__device__ __forceinline__ void y_item(const int* __restrict__ ylist, int gl, int& bx, int& by) {
+  if (ylist) {
+    const int e = ylist[gl];
+    by = e >> 16;
+    bx = e & 0xffff;
   } else {
-    const FastDiv div_ny(n_y), div_nbc(nbc);
-    staged_copy<kFftMaxV>(
-        nbc * n_y, tid, nthr,
-        [&](int q) {
-          const int bi = div_ny(q);
-          return src[bi * bin_stride + (q - bi * n_y)];
-        },
-        [&](int q, cx<T> v) {
-          const int bi = div_ny(q);
-          buf[bi * bstride + lpos(q - bi * n_y)] = v;
-        });
-    for (int t = tid; t < fd.n; t += nthr) twl[t] = fd.tw[t];
-    __syncthreads();
-    fft_group<T, false>(buf, lds_twiddles(fd, twl), nbc, bstride, tid, nthr, wm);
-    __syncthreads();
-    staged_copy<kFftMaxV>(
-        nbc * Ny, tid, nthr,
-        [&](int q) {
-          const int kk = div_nbc(q);
-          const int bi = q - kk * nbc;
-          const T sc = cxj * dcy[kk];
-          const cx<T> v = buf[bi * bstride + slot(kk)];
-          return cx<T>{v.x * sc, v.y * sc};
-        },
-        [&](int q, cx<T> v) {
-          const int kk = div_nbc(q);
-          dst[size_t(kk) * nb + (q - kk * nbc)] = v;
-        });
+    bx = gl % gridDim.x;
+    by = gl / gridDim.x;
   }
 }
 
-template <typename T, int NCT>
+template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_fft_y(const cx<T>* __restrict__ V, int nb, int Nx, int Ny, int bins,
                                                      const T* __restrict__ dcx, const T* __restrict__ dcy,
                                                      FftDesc<T> fd, cx<T>* __restrict__ Gh, int wm,
                                                      const int* __restrict__ jrange, const int* __restrict__ ylist) {
   // neighbouring groups write the two halves of each 128-byte output line:
   // keep them on one XCD so its L2 merges the halves
-  const int gl = xcd_linear();
-  int bx = gl % gridDim.x, by = gl / gridDim.x;
-  if (ylist) {  // one-dimensional grid over the work items inside the ranges
-    const int e = ylist[gl];
-    by = e >> 16;
-    bx = e & 0xffff;
-  }
-  fft_y_body<T, NCT>(V, nb, Nx, Ny, bins, dcx, dcy, fd, Gh, wm, bx, by, jrange);
+  int bx, by;
+  y_item(ylist, xcd_linear(), bx, by);
+  fft_y_body<T>(V, nb, Nx, Ny, bins, dcx, dcy, fd, Gh, wm, bx, by, jrange);
+}
+
+template <typename T, int CLS>
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_y_reg(const cx<T>* __restrict__ V, int nb, int Nx, int Ny,
+                                                           const T* __restrict__ dcx, const T* __restrict__ dcy,
+                                                           Fft2Raw f, cx<T>* __restrict__ Gh,
+                                                           const int* __restrict__ jrange,
+                                                           const int* __restrict__ ylist) {
+  int bx, by;
+  y_item(ylist, xcd_linear(), bx, by);
+  fft_y_reg_body<T, CLS>(V, nb, Nx, Ny, dcx, dcy, as_fft2<T>(f), Gh, bx, by, jrange, threadIdx.x);
 }
 
 template <typename T>
 hipError_t launch_fft_y(const DevPlan& p, const void* V, void* Gh, hipStream_t s) {
   const FftCfg cfg = fft_cfg();
-  const int bins = fft_batch<T>(p.n_y, cfg.threads, cfg.cap);
+  const int bins = fft_bins<T>(p.f_ny, cfg.threads, cfg.cap);
+  const bool listed = p.ylist && p.ylist_n > 0 && p.jrange;
+  const dim3 grid = listed ? dim3(p.ylist_n) : dim3((p.nb + bins - 1) / bins, p.Nx);
+  const int* ylist = listed ? p.ylist : nullptr;
+  if (p.f_ny.two.r1) {
+    const Fft2Raw f = fft2_shape<T>(p.f_ny, bins);
+    const size_t lds = fft2_slots(f) * sizeof(cx<T>);
+    return class_pick(f, [&](auto c) {
+      constexpr auto kern = &k_fft_y_reg<T, decltype(c)::value>;
+      hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(kern, grid, dim3(fft2_threads(f)), lds, s, static_cast<const cx<T>*>(V), p.nb, p.Nx, p.Ny,
+                         static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), f, static_cast<cx<T>*>(Gh),
+                         p.jrange, ylist);
+      return hipGetLastError();
+    });
+  }
   const size_t lds = (size_t(bins) * lseq(p.n_y) + p.n_y) * sizeof(cx<T>);
   if (size_t(bins) * p.n_y > size_t(kFftMaxV) * cfg.threads || size_t(bins) * p.Ny > size_t(kFftMaxV) * cfg.threads)
     return hipErrorInvalidValue;
-  auto go = [&](auto kern, int nct) {
-    // the compile-time kernels take their geometry from the length
-    if (nct > 0 && (bins != ct_maxb(nct, kFftCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
-    hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
-    if (e != hipSuccess) return e;
-    const bool listed = p.ylist && p.ylist_n > 0 && p.jrange;
-    const dim3 grid = listed ? dim3(p.ylist_n) : dim3((p.nb + bins - 1) / bins, p.Nx);
-    hipLaunchKernelGGL(kern, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(V), p.nb, p.Nx, p.Ny,
-                       bins, static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), as_desc<T>(p.f_ny),
-                       static_cast<cx<T>*>(Gh), cfg.wave, p.jrange, listed ? p.ylist : nullptr);
-    return hipGetLastError();
-  };
-  return ct_pick(CtLateral{}, p.n_y, [&](auto c) { return go(&k_fft_y<T, decltype(c)::value>, decltype(c)::value); });
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_fft_y<T>), lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_fft_y<T>, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(V), p.nb, p.Nx, p.Ny,
+                     bins, static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), as_desc<T>(p.f_ny),
+                     static_cast<cx<T>*>(Gh), cfg.wave, p.jrange, ylist);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -338,7 +420,7 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_y_t(const cx<T>* __restrict
 template <typename T>
 hipError_t launch_fft_y_t(const DevPlan& p, const void* Gh, void* V, hipStream_t s) {
   const FftCfg cfg = fft_cfg();
-  const int bins = fft_batch<T>(p.n_y, cfg.threads, cfg.cap);
+  const int bins = fft_bins<T>(p.f_ny, cfg.threads, cfg.cap);
   const size_t lds = (size_t(bins) * lseq(p.n_y) + p.n_y) * sizeof(cx<T>);
   if (size_t(bins) * p.n_y > size_t(kFftMaxV) * cfg.threads || size_t(bins) * p.Ny > size_t(kFftMaxV) * cfg.threads)
     return hipErrorInvalidValue;
@@ -416,9 +498,14 @@ hipError_t launch_fft_x_t(const DevPlan& p, const void* V, void* U, int b_begin,
   return hipGetLastError();
 }
 
-// Batched forms of the x and y passes.
-template <typename T>
-__global__ __launch_bounds__(kFftThreads) void k_fft_x_batch(const FftXBA* __restrict__ args,
+// Batched forms of the x and y passes: a launch holds the problems of one
+// variant, CLS the class of their two-pass transforms or 0 for the longer
+// lengths.
+template <typename T, int CLS>
+constexpr int batch_waves() { return CLS > 0 ? reg_waves<T, CLS ? CLS : 16>() : 1; }
+
+template <typename T, int CLS>
+__global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_x_batch(const FftXBA* __restrict__ args,
                                                              const int* __restrict__ prefix, int nprob, int total,
                                                              BatchIO io) {
   __shared__ BatchMeta<FftXBA> meta;
@@ -429,14 +516,18 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_x_batch(const FftXBA* __res
     const FftXBA a = batch_args(meta, p);
     const int local = w - meta.prefix[p];
     const int by = local / a.gx;
-    fft_x_body<T>(static_cast<const cx<T>*>(a.U), a.n_y, a.Nx, a.rows, 0, view_desc<T>(a.fd),
-                  static_cast<cx<T>*>(a.V), 0, local - by * a.gx, by, a.brange, loop_lane());
+    if constexpr (CLS > 0)
+      fft_x_reg_body<T, CLS>(static_cast<const cx<T>*>(a.U), a.n_y, a.Nx, 0, as_fft2<T>(a.f2),
+                             static_cast<cx<T>*>(a.V), local - by * a.gx, by, a.brange, loop_lane());
+    else
+      fft_x_body<T>(static_cast<const cx<T>*>(a.U), a.n_y, a.Nx, a.rows, 0, view_desc<T>(a.fd),
+                    static_cast<cx<T>*>(a.V), 0, local - by * a.gx, by, a.brange, loop_lane());
     __syncthreads();
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kFftThreads) void k_fft_y_batch(const FftYBA* __restrict__ args,
+template <typename T, int CLS>
+__global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_y_batch(const FftYBA* __restrict__ args,
                                                              const int* __restrict__ prefix, int nprob, int total,
                                                              BatchIO io) {
   __shared__ BatchMeta<FftYBA> meta;
@@ -452,31 +543,47 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_y_batch(const FftYBA* __res
       by = e >> 16;
       bx = e & 0xffff;
     }
-    fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.Nx, a.Ny, a.bins, static_cast<const T*>(a.dcx),
-                  static_cast<const T*>(a.dcy), view_desc<T>(a.fd), static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
-                  loop_lane());
+    if constexpr (CLS > 0)
+      fft_y_reg_body<T, CLS>(static_cast<const cx<T>*>(a.V), a.nb, a.Nx, a.Ny, static_cast<const T*>(a.dcx),
+                             static_cast<const T*>(a.dcy), as_fft2<T>(a.f2), static_cast<cx<T>*>(a.Gh), bx, by,
+                             a.jrange, loop_lane());
+    else
+      fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.Nx, a.Ny, a.bins, static_cast<const T*>(a.dcx),
+                    static_cast<const T*>(a.dcy), view_desc<T>(a.fd), static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
+                    loop_lane());
     __syncthreads();
   }
+}
+
+template <typename A, typename K>
+static hipError_t launch_batch_kernel(K kern, const BatchStage& st, const BatchIO& io, hipStream_t s) {
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), st.lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(batch_grid(st)), dim3(st.threads), st.lds, s, static_cast<const A*>(st.args),
+                     st.prefix, st.nprob, st.total, io);
+  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_fft_x_batch(const BatchStage& st, const BatchIO& io, hipStream_t s) {
   if (st.total <= 0) return hipSuccess;
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_fft_x_batch<T>), st.lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_fft_x_batch<T>), dim3(batch_grid(st)), dim3(kFftThreads), st.lds, s,
-                     static_cast<const FftXBA*>(st.args), st.prefix, st.nprob, st.total, io);
-  return hipGetLastError();
+  switch (st.variant) {
+    case 16: return launch_batch_kernel<FftXBA>(&k_fft_x_batch<T, 16>, st, io, s);
+    case 20: return launch_batch_kernel<FftXBA>(&k_fft_x_batch<T, 20>, st, io, s);
+    case 32: return launch_batch_kernel<FftXBA>(&k_fft_x_batch<T, 32>, st, io, s);
+    default: return launch_batch_kernel<FftXBA>(&k_fft_x_batch<T, 0>, st, io, s);
+  }
 }
 
 template <typename T>
 hipError_t launch_fft_y_batch(const BatchStage& st, const BatchIO& io, hipStream_t s) {
   if (st.total <= 0) return hipSuccess;
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_fft_y_batch<T>), st.lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_fft_y_batch<T>), dim3(batch_grid(st)), dim3(kFftThreads), st.lds, s,
-                     static_cast<const FftYBA*>(st.args), st.prefix, st.nprob, st.total, io);
-  return hipGetLastError();
+  switch (st.variant) {
+    case 16: return launch_batch_kernel<FftYBA>(&k_fft_y_batch<T, 16>, st, io, s);
+    case 20: return launch_batch_kernel<FftYBA>(&k_fft_y_batch<T, 20>, st, io, s);
+    case 32: return launch_batch_kernel<FftYBA>(&k_fft_y_batch<T, 32>, st, io, s);
+    default: return launch_batch_kernel<FftYBA>(&k_fft_y_batch<T, 0>, st, io, s);
+  }
 }
 
 #define PATK_INST(T)                                                                    \
