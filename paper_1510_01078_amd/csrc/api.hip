@@ -349,7 +349,23 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
         sk16[size_t(q) * 64 + lane] = v;
       }
   P->spread_slots = (int64_t)(ssens.size() / SK);
-  const size_t o_soff = blob.add(soff.data(), soff.size() * sizeof(int));
+  // the patches' slot ranges, those of several rounds of slots first and the
+  // longest ahead: their items take the longest, so a launch starts with them
+  std::vector<int> order(npatch);
+  for (int i = 0; i < npatch; ++i) order[i] = i;
+  auto rounds_of = [&](int pt) { return (soff[pt + 1] - soff[pt] + patk::kSlotBatch - 1) / patk::kSlotBatch; };
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return std::max(1, rounds_of(a)) > std::max(1, rounds_of(b)); });
+  std::vector<int> srng(4 * size_t(npatch));
+  dp.spread_heavy = 0;
+  for (int i = 0; i < npatch; ++i) {
+    const int pt = order[i];
+    srng[4 * i] = soff[pt];
+    srng[4 * i + 1] = soff[pt + 1];
+    srng[4 * i + 2] = pt;
+    dp.spread_heavy += rounds_of(pt) > 1;
+  }
+  const size_t o_srng = blob.add(srng.data(), srng.size() * sizeof(int));
   const size_t o_ssens = blob.add(ssens.data(), std::max<size_t>(1, ssens.size()) * sizeof(int));
   const size_t o_sw = add_real<T>(blob, sw.empty() ? std::vector<double>(1, 0.0) : sw);
   const size_t o_sk = blob.add(sk16.data(), std::max<size_t>(1, sk16.size()) * sizeof(unsigned));
@@ -496,7 +512,7 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   dp.sby = static_cast<const int*>(at(o_sby));
   dp.swx = at(o_swx);
   dp.swy = at(o_swy);
-  dp.slot_off = static_cast<const int*>(at(o_soff));
+  dp.slot_rng = static_cast<const int4*>(at(o_srng));
   dp.slot_sens = static_cast<const int*>(at(o_ssens));
   dp.slot_w = at(o_sw);
   dp.slot_k = static_cast<const unsigned*>(at(o_sk));

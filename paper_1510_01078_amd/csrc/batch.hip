@@ -130,8 +130,11 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     lds[0][p] = size_t(patk::temporal_lds_slots(d.n_t)) * c;
     // stage 1: spread, all bins in one round
     const int nchunks = (d.nb + 15) / 16;
-    a1[p] = patk::SpreadBA{C, d.slot_off, d.slot_sens, d.slot_w, d.slot_k, d.nb, d.n_x, d.n_y, d.tiles_x, nchunks, A};
-    pre[1][p] = d.tiles_x * d.patches_y * ((nchunks + patk::kSpreadGroups - 1) / patk::kSpreadGroups);
+    a1[p] = patk::SpreadBA{C,     d.slot_rng, d.slot_sens, d.slot_w,       d.slot_k,          d.nb, d.n_x,
+                           d.n_y, d.tiles_x,  nchunks,     d.spread_heavy, patk::kSpreadGroups, 0,  A};
+    const long long items1 = patk::spread_items(d, nchunks, patk::kSpreadGroups);
+    if (items1 > 0x7fffffffLL) return PAT_ERR_UNSUPPORTED;
+    pre[1][p] = int(items1);
     // stage 2: FFT along x
     const int rows = patk::fft_seqs<T>(d.f_nx, cfg.threads, cfg.cap);
     const patk::Fft2Raw fx = d.f_nx.two.r1 ? patk::fft2_shape<T>(d.f_nx, rows) : d.f_nx.two;

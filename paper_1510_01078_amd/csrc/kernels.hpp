@@ -62,7 +62,9 @@ struct DevPlan {
   const int* sby = nullptr;       // [M]
   const void* swx = nullptr;      // [M][w] x weights
   const void* swy = nullptr;      // [M][w]
-  const int* slot_off = nullptr;  // [tiles_x*patches_y+1] packed slots of each 16 x kPatchRows patch (CSR)
+  const int4* slot_rng = nullptr; // [tiles_x*patches_y] first and past-the-end packed slot of each 16 x kPatchRows
+                                  // patch and the patch's index, patches of several rounds of slots first
+  int spread_heavy = 0;           // patches of more than one round (kSlotBatch slots)
   const int* slot_sens = nullptr; // [slots][kSlotK] sensor ids of each slot, -1 for an empty place
   const void* slot_w = nullptr;   // [slots][64] each lane's weight wx*wy (0 where no sensor covers it)
   const unsigned* slot_k = nullptr;       // [slots][64] places in their slots of the lane's sensors for the
@@ -85,8 +87,22 @@ struct DevPlan {
 constexpr int kSpreadTile = 16;  // spread tile edge (grid points)
 constexpr int kPatchRows = 4;    // rows of the spread's one-wave patch (16 x 4 grid points)
 constexpr int kSlotK = 4;        // sensors per packed spread slot
-constexpr int kSpreadGroups = 2; // spread bin groups (16 bins each) per work-group
+constexpr int kSpreadGroups = 2; // most spread bin groups (16 bins each) per work-group
 constexpr int kSlotBatch = 8;    // spread slots staged per round (their places fit one 32-bit word)
+
+// Work items of the spread over `nchunks` bin groups: a patch of several
+// rounds of slots takes one bin group per item (it reads its lane tables again
+// for every bin group anyway), the others `groups`.
+inline long long spread_items(const DevPlan& p, int nchunks, int groups) {
+  return (long long)p.spread_heavy * nchunks +
+         ((long long)p.tiles_x * p.patches_y - p.spread_heavy) * ((nchunks + groups - 1) / groups);
+}
+// Two bin groups per item (one read of the lane tables for both) once that
+// leaves enough one-wave items to fill the device's wave slots (256 CUs with
+// 20 each); smaller problems spread the bin groups over more waves.
+inline int spread_groups(const DevPlan& p, int nchunks) {
+  return spread_items(p, nchunks, kSpreadGroups) >= 5120 ? kSpreadGroups : 1;
+}
 
 // Stage launchers; T = float or double. Buffers are device pointers.
 //
@@ -182,8 +198,8 @@ struct TemporalBA {
   const void* hw; const void* deap; FftView fd; int M, Nt, n0, b_lo, nb; void* Gt;
 };
 struct SpreadBA {
-  const void* Gt; const int* slot_off; const int* slot_sens; const void* slot_w; const unsigned* slot_k;
-  int nb, n_x, n_y, tiles_x, nchunks; void* U;
+  const void* Gt; const int4* slot_rng; const int* slot_sens; const void* slot_w; const unsigned* slot_k;
+  int nb, n_x, n_y, tiles_x, nchunks, heavy, groups, pad; void* U;
 };
 struct FftXBA {
   const void* U; FftView fd; Fft2Raw f2; int n_y, Nx, rows, gx; void* V; const int* brange;

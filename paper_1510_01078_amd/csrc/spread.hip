@@ -61,11 +61,11 @@ __device__ __forceinline__ void accum(cx<T>& a, cx<T>& c, T wt, cx<T> g) {
 
 template <typename T, bool KAHAN>
 __device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, int nb,
-                                                 const int* __restrict__ slot_off,
+                                                 const int4* __restrict__ slot_rng,
                                                  const int* __restrict__ slot_sens, const T* __restrict__ slot_w,
                                                  const unsigned* __restrict__ slot_k, int n_x, int n_y,
-                                                 int tiles_x, int nchunks, int b_begin, int b_end,
-                                                 cx<T>* __restrict__ U, int bx) {
+                                                 int tiles_x, int nchunks, int heavy, int groups, int b_begin,
+                                                 int b_end, cx<T>* __restrict__ U, int bx) {
   constexpr int BC = kSpreadBins, K = kSlotK, SB = kSlotBatch;
   constexpr int ROWS = SB * K;
   constexpr int LPR = 64 / ROWS;  // lanes staging one row
@@ -75,22 +75,33 @@ __device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, i
   constexpr int LSTRIDE = 64 * EL;               // elements between two loads' blocks
   static_assert(ROWS * LPR == 64 && BC % LPR == 0 && EPL % EL == 0 && SB * 2 <= 32 && K <= 4, "staging layout");
   __shared__ __align__(16) cx<T> s_g[NLD * LSTRIDE];
-  const int ngroups = (nchunks + kSpreadGroups - 1) / kSpreadGroups;
-  const int grp = bx % ngroups;  // bin groups vary fastest: neighbours share the patch's slots
-  const int patch = bx / ngroups;
+  // item bx: one bin group of a patch of several rounds, or `groups` of
+  // another (bin groups vary fastest: neighbours share the patch's slots)
+  const int nheavy = heavy * nchunks;
+  int at, c_first, c_end;
+  if (bx < nheavy) {
+    at = bx / nchunks;
+    c_first = bx - at * nchunks;
+    c_end = c_first + 1;
+  } else {
+    const int ngroups = (nchunks + groups - 1) / groups;
+    at = (bx - nheavy) / ngroups;
+    c_first = (bx - nheavy - at * ngroups) * groups;
+    c_end = min(nchunks, c_first + groups);
+    at += heavy;
+  }
+  const int4 rng = slot_rng[at];
+  const int patch = rng.z;
   const int prg = patch / tiles_x;
   const int pcol = patch - prg * tiles_x;
   const int lane = threadIdx.x;
   const int px = pcol * kSpreadTile + (lane & 15);
   const int py = prg * kPatchRows + (lane >> 4);
-  const int q_begin = slot_off[patch];
-  const int q_end = slot_off[patch + 1];
+  const int q_begin = rng.x, q_end = rng.y;
   const bool one_round = q_end - q_begin <= SB;
   const int row = lane / LPR, part = lane - (lane / LPR) * LPR;
   T wq[SB];
   unsigned kq = 0;  // 2-bit places of the round's slots
-  const int c_first = grp * kSpreadGroups;
-  const int c_end = min(nchunks, c_first + kSpreadGroups);
   for (int c = c_first; c < c_end; ++c) {
     const int b0 = b_begin + c * BC;
     const int nbc = min(BC, b_end - b0);
@@ -149,33 +160,33 @@ __device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, i
 
 template <typename T, bool KAHAN>
 __global__ __launch_bounds__(64) void k_spread_slots(const cx<T>* __restrict__ Gt, int nb,
-                                                     const int* __restrict__ slot_off,
+                                                     const int4* __restrict__ slot_rng,
                                                      const int* __restrict__ slot_sens,
                                                      const T* __restrict__ slot_w,
                                                      const unsigned* __restrict__ slot_k, int n_x, int n_y,
-                                                     int tiles_x, int nchunks, int b_begin, int b_end,
-                                                     cx<T>* __restrict__ U) {
-  spread_slot_body<T, KAHAN>(Gt, nb, slot_off, slot_sens, slot_w, slot_k, n_x, n_y, tiles_x, nchunks, b_begin,
-                             b_end, U, blockIdx.x);
+                                                     int tiles_x, int nchunks, int heavy, int groups, int b_begin,
+                                                     int b_end, cx<T>* __restrict__ U) {
+  spread_slot_body<T, KAHAN>(Gt, nb, slot_rng, slot_sens, slot_w, slot_k, n_x, n_y, tiles_x, nchunks, heavy, groups,
+                             b_begin, b_end, U, blockIdx.x);
 }
 
 template <typename T>
 hipError_t launch_spread(const DevPlan& p, const void* Gt, void* U, int b_begin, int b_end, hipStream_t s) {
   if (p.w_xy > kMaxW || b_begin < 0 || b_end > p.nb || b_begin >= b_end) return hipErrorInvalidValue;
   const int nchunks = (b_end - b_begin + kSpreadBins - 1) / kSpreadBins;
-  const long long blocks =
-      (long long)p.tiles_x * p.patches_y * ((nchunks + kSpreadGroups - 1) / kSpreadGroups);
+  const int groups = spread_groups(p, nchunks);
+  const long long blocks = spread_items(p, nchunks, groups);
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (p.kahan)
     hipLaunchKernelGGL((k_spread_slots<T, true>), dim3((unsigned)blocks), dim3(64), 0, s,
-                       static_cast<const cx<T>*>(Gt), p.nb, p.slot_off, p.slot_sens,
-                       static_cast<const T*>(p.slot_w), p.slot_k, p.n_x, p.n_y, p.tiles_x, nchunks, b_begin,
-                       b_end, static_cast<cx<T>*>(U));
+                       static_cast<const cx<T>*>(Gt), p.nb, p.slot_rng, p.slot_sens,
+                       static_cast<const T*>(p.slot_w), p.slot_k, p.n_x, p.n_y, p.tiles_x, nchunks, p.spread_heavy,
+                       groups, b_begin, b_end, static_cast<cx<T>*>(U));
   else
     hipLaunchKernelGGL((k_spread_slots<T, false>), dim3((unsigned)blocks), dim3(64), 0, s,
-                       static_cast<const cx<T>*>(Gt), p.nb, p.slot_off, p.slot_sens,
-                       static_cast<const T*>(p.slot_w), p.slot_k, p.n_x, p.n_y, p.tiles_x, nchunks, b_begin,
-                       b_end, static_cast<cx<T>*>(U));
+                       static_cast<const cx<T>*>(Gt), p.nb, p.slot_rng, p.slot_sens,
+                       static_cast<const T*>(p.slot_w), p.slot_k, p.n_x, p.n_y, p.tiles_x, nchunks, p.spread_heavy,
+                       groups, b_begin, b_end, static_cast<cx<T>*>(U));
   return hipGetLastError();
 }
 
@@ -190,9 +201,9 @@ __global__ __launch_bounds__(64) void k_spread_batch(const SpreadBA* __restrict_
     const int w = batch_item(slot, total);
     const int p = __builtin_amdgcn_readfirstlane(batch_locate(meta.prefix, nprob, w));
     const SpreadBA a = batch_args(meta, p);
-    spread_slot_body<T, KAHAN>(static_cast<const cx<T>*>(a.Gt), a.nb, a.slot_off, a.slot_sens,
-                               static_cast<const T*>(a.slot_w), a.slot_k, a.n_x, a.n_y, a.tiles_x, a.nchunks, 0,
-                               a.nb, static_cast<cx<T>*>(a.U), w - meta.prefix[p]);
+    spread_slot_body<T, KAHAN>(static_cast<const cx<T>*>(a.Gt), a.nb, a.slot_rng, a.slot_sens,
+                               static_cast<const T*>(a.slot_w), a.slot_k, a.n_x, a.n_y, a.tiles_x, a.nchunks,
+                               a.heavy, a.groups, 0, a.nb, static_cast<cx<T>*>(a.U), w - meta.prefix[p]);
     __syncthreads();
   }
 }
