@@ -238,7 +238,7 @@ pat_status pat_forward_dxy(pat_plan* plan, const void* f, int32_t axis, void* g,
  * stay within group_bytes (meant for handing each stage's output to the next
  * through the last-level cache; on MI355X this measured slower than one
  * group, so 0, no budget, is the default). Groups run one after another
- * (eight launches each) and share one workspace (the largest group's).
+ * (a launch per stage; one per class of FFT length in the lateral FFTs) and share one workspace (the largest group's).
  *
  * pat_batch_create builds one plan per descriptor (as nufft_plan), uploads
  * per-group argument tables and allocates the workspace through descs[0]'s
@@ -251,21 +251,21 @@ typedef struct pat_batch pat_batch;
 pat_status pat_batch_create(const pat_plan_desc* descs, int32_t count, size_t group_bytes, void* stream,
                             pat_batch** out);
 
-/* Number of problem groups the batch runs (each: eight launches). */
+/* Number of problem groups the batch runs. */
 pat_status pat_batch_groups(const pat_batch* batch, int32_t* groups);
 
 /* Plan of problem `index` (read-only, e.g. for pat_plan_get_info). */
 pat_status pat_batch_get_plan(const pat_batch* batch, int32_t index, const pat_plan** plan);
 
-/* Grid of the batched launches: blocks > 0 (default 16384) launches at most
- * that many work-groups, each loading the group's arguments into LDS once and
- * looping over the work items (a persistent launch); 0 launches one
- * work-group per work item. Results do not depend on it. */
+/* Grid of the batched launches: 0 (the default) launches one work-group per
+ * work item; blocks > 0 launches at most that many work-groups, which loop
+ * over the work items (a persistent launch). Results do not depend on it. */
 pat_status pat_batch_set_grid(pat_batch* batch, int32_t blocks);
 
 /* f[p] = R g[p] for every problem p: g and f are HOST arrays of `count`
- * DEVICE pointers with the layouts of pat_reconstruct. Enqueues eight kernels
- * per group on `stream` (no allocation, no synchronisation), so the call can
+ * DEVICE pointers with the layouts of pat_reconstruct. Enqueues a kernel per
+ * stage and group on `stream` (two to four for the lateral FFTs where the
+ * problems' lengths fall into several classes; no allocation, no synchronisation), so the call can
  * be captured into a HIP graph. Inputs and outputs must not overlap. */
 pat_status pat_batch_reconstruct(pat_batch* batch, const void* const* g, void* const* f, void* stream);
 

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cstdint>
 #include <cstring>
 #include <new>
@@ -22,10 +23,11 @@ using namespace patint;
 
 namespace {
 constexpr int kStages = 7;  // temporal, spread, fft x, fft y, gather + inverse x, inverse y, c2r z
-// default persistent grid: 64 work-groups per CU of a 256-CU MI355X, each
-// looping over the work items after loading the group's arguments once
-// (measured best among 0, 4096, 16384 and 65536 on the 32-problem batch)
-constexpr int kPersistentBlocks = 16384;
+// default grid: one work-group per work item (0), which finds its problem and
+// arguments by scalar loads. A batch of 16 problems took 4.19 ms so, 4.22,
+// 4.30, 4.50 and 4.73 ms on persistent grids of 65536, 16384, 4096 and 2048
+// work-groups, which wait for an item's stores before they start the next.
+constexpr int kDefaultGrid = 0;
 }
 
 // Problems are run in groups of at most kGroupMax, optionally also bounded by
@@ -207,10 +209,11 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
       }
       st.nprob = int(part.size());
       st.total = prefix.back();
-      st.grid = kPersistentBlocks;
+      st.grid = kDefaultGrid;
       st.kahan = kahan;
       st.variant = kind;
       const size_t oa = blob.add(part.data(), part.size() * sizeof(part[0]));
+      prefix.resize(patk::kGroupMax + 1, INT_MAX);
       at[i].emplace_back(oa, blob.add(prefix.data(), prefix.size() * sizeof(int)));
       G.st[i].push_back(st);
     }

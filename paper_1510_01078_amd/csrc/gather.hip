@@ -558,17 +558,16 @@ __device__ __forceinline__ void gather_batch_item(const GatherBA& a, T* coefs, i
 
 template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_gather_batch(const GatherBA* __restrict__ args,
-                                                            const int* __restrict__ prefix, int nprob, int total,
+                                                            const int* __restrict__ prefix, int total,
                                                             BatchIO io) {
-  __shared__ BatchMeta<GatherBA> meta;
   __shared__ T coefs[kMaxTapCoefs];
-  batch_meta_load(meta, args, prefix, nprob);
   int staged = -1;
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
+    if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
-    const int p = __builtin_amdgcn_readfirstlane(batch_locate(meta.prefix, nprob, w));
-    const GatherBA a = batch_args(meta, p);
-    const int local = w - meta.prefix[p];
+    const int p = batch_locate(prefix, w);
+    const GatherBA a = args[p];
+    const int local = w - prefix[p];
     static_assert(kBatchTaps[0] == 6 && kBatchTaps[1] == 8 && kBatchTaps[2] == 10 && kBatchTaps[3] == 12,
                   "tap instantiations");
     switch (a.wt_ct) {
@@ -578,7 +577,6 @@ __global__ __launch_bounds__(kFftThreads) void k_gather_batch(const GatherBA* __
       case 12: gather_batch_item<T, 12>(a, coefs, staged, p, local); break;
       default: gather_batch_item<T, 0>(a, coefs, staged, p, local); break;
     }
-    __syncthreads();
   }
 }
 
@@ -588,7 +586,7 @@ hipError_t launch_gather_batch(const BatchStage& st, const BatchIO& io, hipStrea
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_gather_batch<T>), st.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_gather_batch<T>), dim3(batch_grid(st)), dim3(256), st.lds, s,
-                     static_cast<const GatherBA*>(st.args), st.prefix, st.nprob, st.total, io);
+                     static_cast<const GatherBA*>(st.args), st.prefix, st.total, io);
   return hipGetLastError();
 }
 

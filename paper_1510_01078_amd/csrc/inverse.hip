@@ -366,35 +366,31 @@ hipError_t launch_forward3d(const DevPlan& p, const T* f, void* Dh, hipStream_t 
 // Batched forms of the inverse passes.
 template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_cfft_y_inv_batch(const CfftBA* __restrict__ args,
-                                                                  const int* __restrict__ prefix, int nprob, int total,
+                                                                  const int* __restrict__ prefix, int total,
                                                                   BatchIO io) {
-  __shared__ BatchMeta<CfftBA> meta;
-  batch_meta_load(meta, args, prefix, nprob);
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
+    if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
-    const int p = __builtin_amdgcn_readfirstlane(batch_locate(meta.prefix, nprob, w));
-    const CfftBA a = batch_args(meta, p);
-    const int local = w - meta.prefix[p];
+    const int p = batch_locate(prefix, w);
+    const CfftBA a = args[p];
+    const int local = w - prefix[p];
     const int by = local / a.gx;
     cfft_y_body<T, true>(static_cast<cx<T>*>(a.F), a.Lh, a.lchunk, view_desc<T>(a.fd), 0, local - by * a.gx, by,
                          loop_lane());
-    __syncthreads();
   }
 }
 
 template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_c2r_z_batch(const C2rBA* __restrict__ args,
-                                                             const int* __restrict__ prefix, int nprob, int total,
+                                                             const int* __restrict__ prefix, int total,
                                                              BatchIO io) {
-  __shared__ BatchMeta<C2rBA> meta;
-  batch_meta_load(meta, args, prefix, nprob);
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
+    if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
-    const int p = __builtin_amdgcn_readfirstlane(batch_locate(meta.prefix, nprob, w));
-    const C2rBA a = batch_args(meta, p);
+    const int p = batch_locate(prefix, w);
+    const C2rBA a = args[p];
     c2r_z_body<T>(static_cast<const cx<T>*>(a.F), a.nrows, a.rows, view_desc<T>(a.fd), static_cast<T*>(io.out[p]), 0,
-                  w - meta.prefix[p]);  // (a re-read lane index raised its registers here)
-    __syncthreads();
+                  w - prefix[p]);  // (a re-read lane index raised its registers here)
   }
 }
 
@@ -404,7 +400,7 @@ hipError_t launch_cfft_y_inv_batch(const BatchStage& st, const BatchIO& io, hipS
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_cfft_y_inv_batch<T>), st.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_cfft_y_inv_batch<T>), dim3(batch_grid(st)), dim3(kFftThreads), st.lds, s,
-                     static_cast<const CfftBA*>(st.args), st.prefix, st.nprob, st.total, io);
+                     static_cast<const CfftBA*>(st.args), st.prefix, st.total, io);
   return hipGetLastError();
 }
 
@@ -414,7 +410,7 @@ hipError_t launch_c2r_z_batch(const BatchStage& st, const BatchIO& io, hipStream
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_c2r_z_batch<T>), st.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_c2r_z_batch<T>), dim3(batch_grid(st)), dim3(kFftThreads), st.lds, s,
-                     static_cast<const C2rBA*>(st.args), st.prefix, st.nprob, st.total, io);
+                     static_cast<const C2rBA*>(st.args), st.prefix, st.total, io);
   return hipGetLastError();
 }
 

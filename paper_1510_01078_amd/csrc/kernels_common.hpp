@@ -198,36 +198,17 @@ __host__ __device__ inline FftDesc<T> view_desc(const FftView& v) {
   return d;
 }
 
-// A batched launch's per-problem arguments and work-item prefix sums, copied
-// into LDS once per work-group; each work item then finds its problem with
-// an LDS search and takes the arguments into scalar registers (as kernel
-// arguments would be), so no work item waits on dependent global loads.
-template <class A>
-struct BatchMeta {
-  int prefix[kGroupMax + 1];
-  A args[kGroupMax];
-};
-
-template <class A>
-__device__ __forceinline__ void batch_meta_load(BatchMeta<A>& m, const A* __restrict__ args,
-                                                const int* __restrict__ prefix, int nprob) {
-  static_assert(sizeof(A) % 4 == 0, "argument words");
-  const int nw = nprob * int(sizeof(A) / 4);
-  const int* src = reinterpret_cast<const int*>(args);
-  int* dst = reinterpret_cast<int*>(m.args);
-  for (int i = threadIdx.x; i < nw; i += blockDim.x) dst[i] = src[i];
-  for (int i = threadIdx.x; i <= nprob; i += blockDim.x) m.prefix[i] = prefix[i];
-  __syncthreads();
-}
-
-template <class A>
-__device__ __forceinline__ A batch_args(const BatchMeta<A>& m, int p) {
-  A a;
-  const int* src = reinterpret_cast<const int*>(&m.args[p]);
-  int* dst = reinterpret_cast<int*>(&a);
+// Problem of batched work item w (uniform over the work-group): the number of
+// later problems whose first item is at or below w. prefix holds kGroupMax + 1
+// entries (INT_MAX past the last problem), read by two wide scalar loads and
+// compared without a branch, and the problem's arguments come by scalar loads
+// as kernel arguments would: nothing waits on LDS, so a work-group per item
+// costs two scalar round trips.
+__device__ __forceinline__ int batch_locate(const int* __restrict__ prefix, int w) {
+  int p = 0;
 #pragma unroll
-  for (int i = 0; i < int(sizeof(A) / 4); ++i) dst[i] = __builtin_amdgcn_readfirstlane(src[i]);
-  return a;
+  for (int i = 1; i < kGroupMax; ++i) p += w >= prefix[i] ? 1 : 0;
+  return p;
 }
 
 // Linear index of this work-group in a 2-D grid with the hardware's
@@ -238,16 +219,6 @@ __device__ __forceinline__ int xcd_linear() {
   const int b = blockIdx.x + gridDim.x * blockIdx.y;
   const int per = int(gridDim.x * gridDim.y) / 8;
   return b < per * 8 ? (b % 8) * per + b / 8 : b;
-}
-
-// Problem of batched work item w: the largest p with prefix[p] <= w.
-__device__ __forceinline__ int batch_locate(const int* prefix, int nprob, int w) {
-  int lo = 0, hi = nprob - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (prefix[mid] <= w) lo = mid; else hi = mid - 1;
-  }
-  return lo;
 }
 
 // LDS slots of a complex-to-real z work-group of `rows` real rows: two rows

@@ -506,15 +506,14 @@ constexpr int batch_waves() { return CLS > 0 ? reg_waves<T, CLS ? CLS : 16>() : 
 
 template <typename T, int CLS>
 __global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_x_batch(const FftXBA* __restrict__ args,
-                                                             const int* __restrict__ prefix, int nprob, int total,
+                                                             const int* __restrict__ prefix, int total,
                                                              BatchIO io) {
-  __shared__ BatchMeta<FftXBA> meta;
-  batch_meta_load(meta, args, prefix, nprob);
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
+    if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
-    const int p = __builtin_amdgcn_readfirstlane(batch_locate(meta.prefix, nprob, w));
-    const FftXBA a = batch_args(meta, p);
-    const int local = w - meta.prefix[p];
+    const int p = batch_locate(prefix, w);
+    const FftXBA a = args[p];
+    const int local = w - prefix[p];
     const int by = local / a.gx;
     if constexpr (CLS > 0)
       fft_x_reg_body<T, CLS>(static_cast<const cx<T>*>(a.U), a.n_y, a.Nx, 0, as_fft2<T>(a.f2),
@@ -522,21 +521,19 @@ __global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_x_
     else
       fft_x_body<T>(static_cast<const cx<T>*>(a.U), a.n_y, a.Nx, a.rows, 0, view_desc<T>(a.fd),
                     static_cast<cx<T>*>(a.V), 0, local - by * a.gx, by, a.brange, loop_lane());
-    __syncthreads();
   }
 }
 
 template <typename T, int CLS>
 __global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_y_batch(const FftYBA* __restrict__ args,
-                                                             const int* __restrict__ prefix, int nprob, int total,
+                                                             const int* __restrict__ prefix, int total,
                                                              BatchIO io) {
-  __shared__ BatchMeta<FftYBA> meta;
-  batch_meta_load(meta, args, prefix, nprob);
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
+    if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
-    const int p = __builtin_amdgcn_readfirstlane(batch_locate(meta.prefix, nprob, w));
-    const FftYBA a = batch_args(meta, p);
-    const int local = w - meta.prefix[p];
+    const int p = batch_locate(prefix, w);
+    const FftYBA a = args[p];
+    const int local = w - prefix[p];
     int by = local / a.gx, bx = local - by * a.gx;
     if (a.ylist) {  // the problem's work items inside its ranges
       const int e = a.ylist[local];
@@ -551,7 +548,6 @@ __global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_y_
       fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.Nx, a.Ny, a.bins, static_cast<const T*>(a.dcx),
                     static_cast<const T*>(a.dcy), view_desc<T>(a.fd), static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
                     loop_lane());
-    __syncthreads();
   }
 }
 
@@ -560,7 +556,7 @@ static hipError_t launch_batch_kernel(K kern, const BatchStage& st, const BatchI
   hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), st.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(batch_grid(st)), dim3(st.threads), st.lds, s, static_cast<const A*>(st.args),
-                     st.prefix, st.nprob, st.total, io);
+                     st.prefix, st.total, io);
   return hipGetLastError();
 }
 

@@ -194,17 +194,15 @@ hipError_t launch_spread(const DevPlan& p, const void* Gt, void* U, int b_begin,
 // problem, each item as in the single-problem launch (same sums, same order).
 template <typename T, bool KAHAN>
 __global__ __launch_bounds__(64) void k_spread_batch(const SpreadBA* __restrict__ args,
-                                                     const int* __restrict__ prefix, int nprob, int total, BatchIO io) {
-  __shared__ BatchMeta<SpreadBA> meta;
-  batch_meta_load(meta, args, prefix, nprob);
+                                                     const int* __restrict__ prefix, int total, BatchIO io) {
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
+    if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
-    const int p = __builtin_amdgcn_readfirstlane(batch_locate(meta.prefix, nprob, w));
-    const SpreadBA a = batch_args(meta, p);
+    const int p = batch_locate(prefix, w);
+    const SpreadBA a = args[p];
     spread_slot_body<T, KAHAN>(static_cast<const cx<T>*>(a.Gt), a.nb, a.slot_rng, a.slot_sens,
                                static_cast<const T*>(a.slot_w), a.slot_k, a.n_x, a.n_y, a.tiles_x, a.nchunks,
-                               a.heavy, a.groups, 0, a.nb, static_cast<cx<T>*>(a.U), w - meta.prefix[p]);
-    __syncthreads();
+                               a.heavy, a.groups, 0, a.nb, static_cast<cx<T>*>(a.U), w - prefix[p]);
   }
 }
 
@@ -213,10 +211,10 @@ hipError_t launch_spread_batch(const BatchStage& st, const BatchIO& io, hipStrea
   if (st.total <= 0) return hipSuccess;
   if (st.kahan)
     hipLaunchKernelGGL((k_spread_batch<T, true>), dim3(batch_grid(st)), dim3(64), 0, s,
-                       static_cast<const SpreadBA*>(st.args), st.prefix, st.nprob, st.total, io);
+                       static_cast<const SpreadBA*>(st.args), st.prefix, st.total, io);
   else
     hipLaunchKernelGGL((k_spread_batch<T, false>), dim3(batch_grid(st)), dim3(64), 0, s,
-                       static_cast<const SpreadBA*>(st.args), st.prefix, st.nprob, st.total, io);
+                       static_cast<const SpreadBA*>(st.args), st.prefix, st.total, io);
   return hipGetLastError();
 }
 

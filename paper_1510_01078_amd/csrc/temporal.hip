@@ -180,18 +180,16 @@ hipError_t launch_temporal_t(const DevPlan& p, const void* Gt, T* g, hipStream_t
 // Batched form: one launch over the sensor pairs of every problem.
 template <typename T>
 __global__ __launch_bounds__(kTemporalThreads) void k_temporal_batch(const TemporalBA* __restrict__ args,
-                                                                     const int* __restrict__ prefix, int nprob, int total,
+                                                                     const int* __restrict__ prefix, int total,
                                                                      BatchIO io) {
-  __shared__ BatchMeta<TemporalBA> meta;
-  batch_meta_load(meta, args, prefix, nprob);
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
+    if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
-    const int p = __builtin_amdgcn_readfirstlane(batch_locate(meta.prefix, nprob, w));
-    const TemporalBA a = batch_args(meta, p);
+    const int p = batch_locate(prefix, w);
+    const TemporalBA a = args[p];
     temporal_body<T>(static_cast<const T*>(io.in[p]), a.M, a.Nt, a.n0, static_cast<const T*>(a.hw),
                      static_cast<const T*>(a.deap), view_desc<T>(a.fd), a.b_lo, a.nb, static_cast<cx<T>*>(a.Gt),
-                     w - meta.prefix[p], loop_lane());
-    __syncthreads();
+                     w - prefix[p], loop_lane());
   }
 }
 
@@ -201,7 +199,7 @@ hipError_t launch_temporal_batch(const BatchStage& st, const BatchIO& io, hipStr
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_temporal_batch<T>), st.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_temporal_batch<T>), dim3(batch_grid(st)), dim3(kTemporalThreads), st.lds, s,
-                     static_cast<const TemporalBA*>(st.args), st.prefix, st.nprob, st.total, io);
+                     static_cast<const TemporalBA*>(st.args), st.prefix, st.total, io);
   return hipGetLastError();
 }
 
