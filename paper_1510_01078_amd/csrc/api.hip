@@ -551,22 +551,35 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   // workspace: region A = grid chunk U, later the lateral spectra Gh;
   // region B = x-transformed rows V, later the spectrum F; region C = Gt.
   const size_t c = cxb;
-  const size_t sz_Gt = size_t(M) * dp.nb * c;
-  const size_t sz_U = size_t(dp.chunk_bins) * dp.n_y * dp.n_x * c;
-  const size_t sz_V = size_t(dp.nb) * d.nx * dp.n_y * c;
-  const size_t sz_Gh = size_t(d.nx) * d.ny * dp.nb * c;
   const size_t sz_F = size_t(d.nx) * d.ny * (d.nz / 2 + 1) * c;
+  auto layout = [&](int unit) {
+    auto up = [&](int n) { return (n + unit - 1) / unit * unit; };
+    dp.pitch_u = up(dp.n_x);
+    dp.pitch_v = up(dp.n_y);
+    dp.pitch_g = up(dp.nb);
+    dp.pitch_t = up(dp.nb);
+    const size_t sz_U = size_t(dp.chunk_bins) * dp.n_y * dp.pitch_u * c;
+    const size_t sz_V = size_t(dp.nb) * d.nx * dp.pitch_v * c;
+    const size_t sz_Gh = size_t(d.nx) * d.ny * dp.pitch_g * c;
+    P->off_B = align_up(std::max(sz_U, sz_Gh));
+    P->off_C = P->off_B + align_up(std::max(sz_V, sz_F));
+    P->ws_bytes = P->off_C + align_up(size_t(M) * dp.pitch_t * c);
+  };
+  // rows on 128-byte lines, so that the spread's runs of 16 points, the x and
+  // y passes' runs of 8 rows and bins and the spread's 16-bin reads do not
+  // straddle lines: the non-temporal partial lines of 270-point rows cost the
+  // spread half of its rate. A plan that fits the allocation-free call's
+  // scratch only without the padding keeps its rows packed.
+  layout(1);
+  const size_t packed = P->ws_bytes;
+  layout(int(128 / cxb));
+  if (packed <= PAT_NOALLOC_SCRATCH_BYTES && P->ws_bytes > PAT_NOALLOC_SCRATCH_BYTES) layout(1);
   P->forward_ok = patk::scatter_lds_bytes<T>(dp) + patk::kStaticLdsMargin <= (size_t)lds_limit;
   P->forward_fused = patk::fused_interp_ok<T>(dp, (size_t)lds_limit - patk::kStaticLdsMargin);
   // two home-tile rows per fused strip (32 + w - 1 grid rows for 32: less
   // halo recomputation, measured faster) where the work-group LDS holds them
   dp.fused_strip =
       dp.tiles_y >= 2 && patk::fused_interp_lds<T>(dp, 2) + patk::kStaticLdsMargin <= (size_t)lds_limit ? 2 : 1;
-  const size_t szA = align_up(std::max(sz_U, sz_Gh));
-  const size_t szB = align_up(std::max(sz_V, sz_F));
-  P->off_B = szA;
-  P->off_C = szA + szB;
-  P->ws_bytes = szA + szB + align_up(sz_Gt);
   return PAT_OK;
 }
 

@@ -85,9 +85,9 @@ template <typename T>
 void problem_regions(const patk::DevPlan& d, size_t& a, size_t& b, size_t& cc) {
   const size_t c = sizeof(patk::cx<T>);
   const size_t lh = size_t(d.Nz / 2 + 1);
-  a = align_up(std::max(size_t(d.nb) * d.n_y * d.n_x * c, size_t(d.Nx) * d.Ny * d.nb * c));
-  b = align_up(std::max(size_t(d.nb) * d.Nx * d.n_y * c, size_t(d.Nx) * d.Ny * lh * c));
-  cc = align_up(size_t(d.M) * d.nb * c);
+  a = align_up(std::max(size_t(d.nb) * d.n_y * d.pitch_u * c, size_t(d.Nx) * d.Ny * d.pitch_g * c));
+  b = align_up(std::max(size_t(d.nb) * d.Nx * d.pitch_v * c, size_t(d.Nx) * d.Ny * lh * c));
+  cc = align_up(size_t(d.M) * d.pitch_t * c);
 }
 
 // Stage tables of one group, with workspace pointers into `ws`.
@@ -127,13 +127,13 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     const int Lh = d.Nz / 2 + 1;
     if (d.n_t > patk::kFftMaxV * 512) return PAT_ERR_UNSUPPORTED;
     // stage 0: temporal FFT, one block per sensor pair
-    a0[p] = patk::TemporalBA{d.hw, d.deap, patk::as_view(d.f_nt), d.M, d.Nt, d.n0, d.b_lo, d.nb, C};
+    a0[p] = patk::TemporalBA{d.hw, d.deap, patk::as_view(d.f_nt), d.M, d.Nt, d.n0, d.b_lo, d.nb, d.pitch_t, C};
     pre[0][p] = (d.M + 1) / 2;
     lds[0][p] = size_t(patk::temporal_lds_slots(d.n_t)) * c;
     // stage 1: spread, all bins in one round
     const int nchunks = (d.nb + 15) / 16;
     a1[p] = patk::SpreadBA{C,     d.slot_rng, d.slot_sens, d.slot_w,       d.slot_k,          d.nb, d.n_x,
-                           d.n_y, d.tiles_x,  nchunks,     d.spread_heavy, patk::kSpreadGroups, 0,  A};
+                           d.n_y, d.tiles_x,  nchunks,     d.spread_heavy, patk::kSpreadGroups, d.pitch_t, d.pitch_u, 0, A};
     const long long items1 = patk::spread_items(d, nchunks, patk::kSpreadGroups);
     if (items1 > 0x7fffffffLL) return PAT_ERR_UNSUPPORTED;
     pre[1][p] = int(items1);
@@ -142,7 +142,7 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     const patk::Fft2Raw fx = d.f_nx.two.r1 ? patk::fft2_shape<T>(d.f_nx, rows) : d.f_nx.two;
     if (!fx.r1 && (rows * d.n_x > kFft || rows * d.Nx > kFft)) return PAT_ERR_UNSUPPORTED;
     const int gx2 = (d.n_y + rows - 1) / rows;
-    a2[p] = patk::FftXBA{A, patk::as_view(d.f_nx), fx, d.n_y, d.Nx, rows, gx2, Bw, d.jrange ? d.brange : nullptr};
+    a2[p] = patk::FftXBA{A, patk::as_view(d.f_nx), fx, d.n_y, d.Nx, rows, gx2, d.pitch_u, d.pitch_v, Bw, d.jrange ? d.brange : nullptr};
     pre[2][p] = gx2 * d.nb;
     lds[2][p] = (fx.r1 ? patk::fft2_slots(fx) : size_t(rows) * patk::lseq(d.n_x) + d.n_x) * c;
     variant[2][p] = fx.r1 ? patk::reg_class(fx) : 0;
@@ -153,7 +153,7 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     if (!fy.r1 && (bins * d.n_y > kFft || bins * d.Ny > kFft)) return PAT_ERR_UNSUPPORTED;
     const int gx3 = (d.nb + bins - 1) / bins;
     const bool listed = d.ylist && d.ylist_n > 0 && d.jrange;
-    a3[p] = patk::FftYBA{Bw, d.dcx, d.dcy, patk::as_view(d.f_ny), fy, d.nb, d.Nx, d.Ny, bins, gx3, A, d.jrange,
+    a3[p] = patk::FftYBA{Bw, d.dcx, d.dcy, patk::as_view(d.f_ny), fy, d.nb, d.Nx, d.Ny, bins, gx3, d.pitch_v, d.pitch_g, A, d.jrange,
                          listed ? d.ylist : nullptr};
     pre[3][p] = listed ? d.ylist_n : gx3 * d.Nx;
     lds[3][p] = (fy.r1 ? patk::fft2_slots(fy) : size_t(bins) * patk::lseq(d.n_y) + d.n_y) * c;
@@ -166,7 +166,7 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     int wt_ct = 0;
     for (int t : patk::kBatchTaps)
       if (d.w_t == t && d.w_t * (d.hdeg + 1) <= patk::kMaxTapCoefs) wt_ct = t;
-    a4[p] = patk::GatherBA{A, d.hcoef, d.nb, d.b_lo, d.Nx, d.Ny, d.Nz, d.w_t, d.hdeg, wt_ct, 0,
+    a4[p] = patk::GatherBA{A, d.hcoef, d.nb, d.b_lo, d.Nx, d.Ny, d.Nz, d.w_t, d.hdeg, wt_ct, d.pitch_g,
                            d.s_per_k, d.kxu, d.kyu, d.kzu, d.two_c, d.n0_over_nt, d.inv_vol, Bw,
                            patk::as_view(d.f_Nx), lcx, gx5};
     pre[4][p] = gx5 * d.Ny;

@@ -114,7 +114,7 @@ enum { MODE_IMAGE = 0, MODE_PHYSICAL = 1, MODE_ADJOINT = 2 };
 // read from hcoef.
 // One spectrum value F(jj, kk, l) of the given mode.
 template <typename T, int MODE, int WT = 0>
-__device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int nb, int b_lo, int Nx, int Ny, int Nz,
+__device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
                                               double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                               double n0_over_nt, double scale, int wt, int deg,
                                               const T* __restrict__ hcoef, int jj, int kk, int l,
@@ -129,8 +129,8 @@ __device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int 
   const double Kabs = lattice_kabs(Kx, Ky, Kz, rK);
   const TapPoint tp = tap_point<T>(Kabs, s_per_k, n0_over_nt, wt, b_lo, nb);
   const T y = T(tp.y);
-  const cx<T>* src = Gh + col * nb + tp.base;
-  const cx<T>* src2 = Gh + ((long long)((Nx - jj) % Nx) * Ny + (Ny - kk) % Ny) * nb + tp.base;
+  const cx<T>* src = Gh + col * pitch + tp.base;
+  const cx<T>* src2 = Gh + ((long long)((Nx - jj) % Nx) * Ny + (Ny - kk) % Ny) * pitch + tp.base;
   cx<T> acc{T(0), T(0)}, acc2{T(0), T(0)};
   if constexpr (WT > 0) {
     cx<T> gv[WT], gv2[MODE == MODE_ADJOINT ? WT : 1];
@@ -175,7 +175,7 @@ __device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int 
 }
 
 template <typename T, int MODE, int WT = 0>
-__device__ __forceinline__ void gather_body(const cx<T>* __restrict__ Gh, int nb, int b_lo, int Nx, int Ny, int Nz,
+__device__ __forceinline__ void gather_body(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
                                             double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                             double n0_over_nt, double scale, int wt, int deg,
                                             const T* __restrict__ hcoef, cx<T>* __restrict__ Fh, int bx,
@@ -188,19 +188,19 @@ __device__ __forceinline__ void gather_body(const cx<T>* __restrict__ Gh, int nb
   const long long col = idx / Lh;
   const int kk = int(col % Ny);
   const int jj = int(col / Ny);
-  Fh[idx] = gather_point<T, MODE, WT>(Gh, nb, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt,
+  Fh[idx] = gather_point<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt,
                                       deg, hcoef, jj, kk, l, coefs);
 }
 
 template <typename T, int MODE, int WT>
-__global__ __launch_bounds__(256) void k_gather(const cx<T>* __restrict__ Gh, int nb, int b_lo, int Nx, int Ny, int Nz,
+__global__ __launch_bounds__(256) void k_gather(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
                                                 double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                                 double n0_over_nt, double scale, int wt, int deg,
                                                 const T* __restrict__ hcoef, cx<T>* __restrict__ Fh) {
   __shared__ T coefs[kMaxTapCoefs];
   stage_tap_coefs<T, WT>(coefs, hcoef, deg);
   __syncthreads();
-  gather_body<T, MODE, WT>(Gh, nb, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg, hcoef,
+  gather_body<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg, hcoef,
                            Fh, blockIdx.x, coefs);
 }
 
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256) void k_gather(const cx<T>* __restrict__ Gh, in
 // there (the same transform and layout as the inverse x pass) and writes the
 // x-transformed values once. The spectrum itself never goes through HBM.
 template <typename T, int MODE, int WT, int NCT>
-__device__ __forceinline__ void gather_x_body(const cx<T>* __restrict__ Gh, int nb, int b_lo, int Nx, int Ny, int Nz,
+__device__ __forceinline__ void gather_x_body(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
                                               double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                               double n0_over_nt, double scale, int wt, int deg,
                                               const T* __restrict__ hcoef, int lchunk, FftDesc<T> fd, int wm,
@@ -233,7 +233,7 @@ __device__ __forceinline__ void gather_x_body(const cx<T>* __restrict__ Gh, int 
     const int jj = div_nl(q);
     const int li = q - jj * nl;
     buf[li * bstride + lpos(jj)] =
-        gather_point<T, MODE, WT>(Gh, nb, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt,
+        gather_point<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt,
                                   deg, hcoef, jj, kk, l0 + li, coefs);
   }
   __syncthreads();
@@ -265,7 +265,7 @@ __device__ __forceinline__ void gather_x_body(const cx<T>* __restrict__ Gh, int 
 }
 
 template <typename T, int MODE, int WT, int NCT>
-__global__ __launch_bounds__(kFftThreads) void k_gather_x(const cx<T>* __restrict__ Gh, int nb, int b_lo, int Nx,
+__global__ __launch_bounds__(kFftThreads) void k_gather_x(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx,
                                                         int Ny, int Nz, double s_per_k, double kxu, double kyu,
                                                         double kzu, double two_c, double n0_over_nt, double scale,
                                                         int wt, int deg, const T* __restrict__ hcoef, int lchunk,
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kFftThreads) void k_gather_x(const cx<T>* __restric
   // neighbouring groups share the 128-byte lines of the z runs: keep them on one XCD
   const int gl = xcd_linear();
   const int kk = gl / int(gridDim.x);
-  gather_x_body<T, MODE, WT, NCT>(Gh, nb, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg,
+  gather_x_body<T, MODE, WT, NCT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg,
                                   hcoef, lchunk, fd, wm, F, gl - kk * int(gridDim.x), kk, coefs);
 }
 
@@ -320,11 +320,11 @@ hipError_t launch_gather_x(const DevPlan& p, const void* Gh, void* F, int mode, 
       hipError_t e = allow_lds(kern, lds);
       if (e != hipSuccess) return e;
       if (adj)
-        hipLaunchKernelGGL((k_gather_x<T, MODE_ADJOINT, WT, NCT>), grid, dim3(cfg.threads), lds, s, in, p.nb, p.b_lo,
+        hipLaunchKernelGGL((k_gather_x<T, MODE_ADJOINT, WT, NCT>), grid, dim3(cfg.threads), lds, s, in, p.nb, p.pitch_g, p.b_lo,
                            p.Nx, p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, scale, p.w_t,
                            p.hdeg, hc, lc, as_desc<T>(p.f_Nx), cfg.wave, out);
       else
-        hipLaunchKernelGGL((k_gather_x<T, MODE_IMAGE, WT, NCT>), grid, dim3(cfg.threads), lds, s, in, p.nb, p.b_lo,
+        hipLaunchKernelGGL((k_gather_x<T, MODE_IMAGE, WT, NCT>), grid, dim3(cfg.threads), lds, s, in, p.nb, p.pitch_g, p.b_lo,
                            p.Nx, p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, scale, p.w_t,
                            p.hdeg, hc, lc, as_desc<T>(p.f_Nx), cfg.wave, out);
       return hipGetLastError();
@@ -344,17 +344,17 @@ hipError_t launch_gather(const DevPlan& p, const void* Gh, void* Fh, int mode, h
     constexpr int WT = decltype(c)::value;
     switch (mode) {
       case GATHER_IMAGE:
-        hipLaunchKernelGGL((k_gather<T, MODE_IMAGE, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.b_lo, p.Nx,
+        hipLaunchKernelGGL((k_gather<T, MODE_IMAGE, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.pitch_g, p.b_lo, p.Nx,
                            p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, p.inv_vol, p.w_t, p.hdeg,
                            hc, out);
         break;
       case GATHER_PHYSICAL:
-        hipLaunchKernelGGL((k_gather<T, MODE_PHYSICAL, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.b_lo, p.Nx,
+        hipLaunchKernelGGL((k_gather<T, MODE_PHYSICAL, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.pitch_g, p.b_lo, p.Nx,
                            p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, 1.0, p.w_t, p.hdeg, hc,
                            out);
         break;
       case GATHER_ADJOINT:
-        hipLaunchKernelGGL((k_gather<T, MODE_ADJOINT, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.b_lo, p.Nx,
+        hipLaunchKernelGGL((k_gather<T, MODE_ADJOINT, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.pitch_g, p.b_lo, p.Nx,
                            p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, p.adj_scale, p.w_t,
                            p.hdeg, hc, out);
         break;
@@ -550,7 +550,7 @@ __device__ __forceinline__ void gather_batch_item(const GatherBA& a, T* coefs, i
     }
   }
   const int kk = local / a.gx;
-  gather_x_body<T, MODE_IMAGE, WT, 0>(static_cast<const cx<T>*>(a.Gh), a.nb, a.b_lo, a.Nx, a.Ny, a.Nz, a.s_per_k,
+  gather_x_body<T, MODE_IMAGE, WT, 0>(static_cast<const cx<T>*>(a.Gh), a.nb, a.pitch_g, a.b_lo, a.Nx, a.Ny, a.Nz, a.s_per_k,
                                       a.kxu, a.kyu, a.kzu, a.two_c, a.n0_over_nt, a.scale, a.wt, a.deg,
                                       static_cast<const T*>(a.hcoef), a.lchunk, view_desc<T>(a.fd), 0,
                                       static_cast<cx<T>*>(a.Fh), local - kk * a.gx, kk, coefs);

@@ -49,6 +49,9 @@ struct DevPlan {
   int tiles_x = 0, tiles_y = 0;
   int chunk_bins = 0;          // bins per spread / x-FFT round (the grid buffer holds this many)
   bool kahan = false;
+  // row pitches (elements) of the reconstruction's intermediate arrays: grid
+  // rows U, x-transformed rows V, lateral spectra Gh, band values Gt
+  int pitch_u = 0, pitch_v = 0, pitch_g = 0, pitch_t = 0;
   double s_per_k = 0.0;        // c*dt*n_t/(2 pi): oversampled bin per unit |K|
   double kxu = 0, kyu = 0, kzu = 0;  // 2 pi/X, 2 pi/Y, 2 pi/Z
   double two_c = 0.0;          // 2c of W(K) = 2c|Kz|/|K|
@@ -195,23 +198,23 @@ struct FftView {  // plain data (it also lives in LDS)
 };
 
 struct TemporalBA {
-  const void* hw; const void* deap; FftView fd; int M, Nt, n0, b_lo, nb; void* Gt;
+  const void* hw; const void* deap; FftView fd; int M, Nt, n0, b_lo, nb, pitch_t; void* Gt;
 };
 struct SpreadBA {
   const void* Gt; const int4* slot_rng; const int* slot_sens; const void* slot_w; const unsigned* slot_k;
-  int nb, n_x, n_y, tiles_x, nchunks, heavy, groups, pad; void* U;
+  int nb, n_x, n_y, tiles_x, nchunks, heavy, groups, pitch_t, pitch_u, pad; void* U;
 };
 struct FftXBA {
-  const void* U; FftView fd; Fft2Raw f2; int n_y, Nx, rows, gx; void* V; const int* brange;
+  const void* U; FftView fd; Fft2Raw f2; int n_y, Nx, rows, gx, pitch_u, pitch_v; void* V; const int* brange;
 };
 struct FftYBA {
-  const void* V; const void* dcx; const void* dcy; FftView fd; Fft2Raw f2; int nb, Nx, Ny, bins, gx; void* Gh;
+  const void* V; const void* dcx; const void* dcy; FftView fd; Fft2Raw f2; int nb, Nx, Ny, bins, gx, pitch_v, pitch_g; void* Gh;
   const int* jrange;  // per x-mode band range (bin groups outside it are skipped)
   const int* ylist;   // the work items inside the ranges (jj << 16 | bin group), or nullptr: gx * Nx items
 };
 struct GatherBA {  // the gather fused with the inverse transform along x
   const void* Gh; const void* hcoef; int nb, b_lo, Nx, Ny, Nz, wt, deg;
-  int wt_ct, pad;  // compile-time tap count to run (kBatchTaps member equal to wt, else 0: runtime taps)
+  int wt_ct, pitch_g;  // compile-time tap count to run (kBatchTaps member equal to wt, else 0: runtime taps)
   double s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale; void* Fh;
   FftView fd; int lchunk, gx;  // x transform (length Nx), z modes per group, groups along z
 };

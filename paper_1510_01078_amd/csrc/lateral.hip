@@ -18,7 +18,7 @@ namespace patk {
 // (the grid is read once) and by the vector ALU's DFT arithmetic; LDS is
 // crossed once.
 template <typename T, int CLS>
-__device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int n_y, int Nx, int b_begin,
+__device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx, int b_begin,
                                                const Fft2<T>& f, cx<T>* __restrict__ V, int bx, int by,
                                                const int* __restrict__ brange, int tid) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -28,11 +28,11 @@ __device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int 
   const int b = b_begin + by;
   const int py0 = bx << f.ls;
   const int nr = min(S, n_y - py0);
-  const cx<T>* src = U + (size_t(by) * n_y + py0) * n_x;
+  const cx<T>* src = U + (size_t(by) * n_y + py0) * pu;
   {
     const int s = small_div(tid, f.r2), i = tid - s * f.r2;
     if (s < nr)
-      reg_first_any<T, CLS, false>(f, buf + s * f.P, i, [&](int e) { return cx_at(src, unsigned(s * n_x + e)); });
+      reg_first_any<T, CLS, false>(f, buf + s * f.P, i, [&](int e) { return cx_at(src, unsigned(s * pu + e)); });
   }
   __syncthreads();
   const int s = tid & (S - 1), k = tid >> f.ls;
@@ -44,20 +44,20 @@ __device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int 
     const int J0 = brange ? brange[2 * b] : 0, J1 = brange ? brange[2 * b + 1] : Nx;
     const int p0 = J0, p1 = min(J1, Nx / 2 - 1);                    // elements of the non-negative modes
     const int m0 = n_x - min(J1, Nx / 2), m1 = n_x - max(J0, 1);    // and of the negative ones
-    cx<T>* dst = V + size_t(b) * Nx * n_y + py0 + s;
+    cx<T>* dst = V + size_t(b) * Nx * pv + py0 + s;
     reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
       const int e = k + q * f.r1;
       if (e >= p0 && e <= p1)
-        cx_at(dst, unsigned(e * n_y)) = v;
+        cx_at(dst, unsigned(e * pv)) = v;
       else if (e >= m0 && e <= m1)
-        cx_at(dst, unsigned((e - (n_x - Nx)) * n_y)) = v;
+        cx_at(dst, unsigned((e - (n_x - Nx)) * pv)) = v;
     });
   }
 }
 
 // Longer lengths: passes in LDS, runtime plan.
 template <typename T>
-__device__ __forceinline__ void fft_x_body(const cx<T>* __restrict__ U, int n_y, int Nx, int rows,
+__device__ __forceinline__ void fft_x_body(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx, int rows,
                                            int b_begin, FftDesc<T> fd, cx<T>* __restrict__ V, int wm, int bx, int by,
                                            const int* __restrict__ brange = nullptr, int tid = threadIdx.x) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -68,8 +68,8 @@ __device__ __forceinline__ void fft_x_body(const cx<T>* __restrict__ U, int n_y,
   const int b = b_begin + by;
   const int py0 = bx * rows;
   const int nr = min(rows, n_y - py0);
-  const cx<T>* src = U + (size_t(b - b_begin) * n_y + py0) * n_x;
-  cx<T>* dst = V + size_t(b) * Nx * n_y + py0;
+  const cx<T>* src = U + (size_t(b - b_begin) * n_y + py0) * pu;
+  cx<T>* dst = V + size_t(b) * Nx * pv + py0;
   // output mode jj of the Nx kept, centred, at its slot of the n_x transform
   auto slot = [&](int jj) {
     const int j = jj < Nx / 2 ? jj : jj - Nx;
@@ -85,7 +85,11 @@ __device__ __forceinline__ void fft_x_body(const cx<T>* __restrict__ U, int n_y,
   cx<T>* twl = buf + rows * bstride;
   const FastDiv div_nx(n_x), div_nr(nr);
   staged_copy<kFftMaxV>(
-      nr * n_x, tid, nthr, [&](int q) { return src[q]; },
+      nr * n_x, tid, nthr,
+      [&](int q) {
+        const int r = div_nx(q);
+        return src[size_t(r) * pu + (q - r * n_x)];
+      },
       [&](int q, cx<T> v) {
         const int r = div_nx(q);
         buf[r * bstride + lpos(q - r * n_x)] = v;
@@ -103,26 +107,26 @@ __device__ __forceinline__ void fft_x_body(const cx<T>* __restrict__ U, int n_y,
       },
       [&](int q, cx<T> v) {
         const int jj = div_nr(q);
-        if (kept(jj)) dst[size_t(jj) * n_y + (q - jj * nr)] = v;
+        if (kept(jj)) dst[size_t(jj) * pv + (q - jj * nr)] = v;
       });
 }
 
 template <typename T>
-__global__ __launch_bounds__(kFftThreads) void k_fft_x(const cx<T>* __restrict__ U, int n_y, int Nx, int rows,
+__global__ __launch_bounds__(kFftThreads) void k_fft_x(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx, int rows,
                                                      int b_begin, FftDesc<T> fd, cx<T>* __restrict__ V, int wm,
                                                      const int* __restrict__ brange) {
   // neighbouring groups write the two halves of each 128-byte output line:
   // keep them on one XCD so its L2 merges the halves
   const int gl = xcd_linear();
-  fft_x_body<T>(U, n_y, Nx, rows, b_begin, fd, V, wm, gl % gridDim.x, gl / gridDim.x, brange);
+  fft_x_body<T>(U, n_y, pu, pv, Nx, rows, b_begin, fd, V, wm, gl % gridDim.x, gl / gridDim.x, brange);
 }
 
 template <typename T, int CLS>
-__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_x_reg(const cx<T>* __restrict__ U, int n_y, int Nx, int b_begin,
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_x_reg(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx, int b_begin,
                                                            Fft2Raw f, cx<T>* __restrict__ V,
                                                            const int* __restrict__ brange) {
   const int gl = xcd_linear();
-  fft_x_reg_body<T, CLS>(U, n_y, Nx, b_begin, as_fft2<T>(f), V, gl % gridDim.x, gl / gridDim.x, brange, threadIdx.x);
+  fft_x_reg_body<T, CLS>(U, n_y, pu, pv, Nx, b_begin, as_fft2<T>(f), V, gl % gridDim.x, gl / gridDim.x, brange, threadIdx.x);
 }
 
 template <typename T>
@@ -138,7 +142,8 @@ hipError_t launch_fft_x(const DevPlan& p, const void* U, void* V, int b_begin, i
       constexpr auto kern = &k_fft_x_reg<T, decltype(c)::value>;
       hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(kern, grid, dim3(fft2_threads(f)), lds, s, static_cast<const cx<T>*>(U), p.n_y, p.Nx, b_begin,
+      hipLaunchKernelGGL(kern, grid, dim3(fft2_threads(f)), lds, s, static_cast<const cx<T>*>(U), p.n_y, p.pitch_u,
+                         p.pitch_v, p.Nx, b_begin,
                          f, static_cast<cx<T>*>(V), p.brange);
       return hipGetLastError();
     });
@@ -148,7 +153,8 @@ hipError_t launch_fft_x(const DevPlan& p, const void* U, void* V, int b_begin, i
     return hipErrorInvalidValue;
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_fft_x<T>), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_fft_x<T>, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(U), p.n_y, p.Nx, rows,
+  hipLaunchKernelGGL(k_fft_x<T>, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(U), p.n_y, p.pitch_u,
+                     p.pitch_v, p.Nx, rows,
                      b_begin, as_desc<T>(p.f_nx), static_cast<cx<T>*>(V), cfg.wave, p.brange);
   return hipGetLastError();
 }
@@ -166,7 +172,7 @@ hipError_t launch_fft_x(const DevPlan& p, const void* U, void* V, int b_begin, i
 // once, and keeping it out of the caches leaves them to the spectra this
 // kernel writes, which the gather reads next.
 template <typename T, int CLS>
-__device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int nb, int Nx, int Ny,
+__device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny,
                                                const T* __restrict__ dcx, const T* __restrict__ dcy,
                                                const Fft2<T>& f, cx<T>* __restrict__ Gh, int bx, int jj,
                                                const int* __restrict__ jrange, int tid) {
@@ -180,8 +186,8 @@ __device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int 
   {
     const int s = small_div(tid, f.r2), i = tid - s * f.r2;
     if (s < nbc) {
-      const cx<T>* src = V + (size_t(b0) * Nx + jj) * n_y;  // bin b0 + s at src + s * Nx * n_y
-      const unsigned at = unsigned(s) * unsigned(Nx * n_y);
+      const cx<T>* src = V + (size_t(b0) * Nx + jj) * pv;  // bin b0 + s at src + s * Nx * pv
+      const unsigned at = unsigned(s) * unsigned(Nx * pv);
       reg_first_any<T, CLS, false>(f, buf + s * f.P, i, [&](int e) { return nt_load(&cx_at(src, at + unsigned(e))); });
     }
   }
@@ -189,21 +195,21 @@ __device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int 
   const int s = tid & (S - 1), k = tid >> f.ls;
   if (k < f.r1 && s < nbc) {
     const T cxj = dcx[jj];
-    cx<T>* dst = Gh + size_t(jj) * Ny * nb + b0 + s;
+    cx<T>* dst = Gh + size_t(jj) * Ny * pg + b0 + s;
     reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
       // element e holds mode e below Ny/2 and e - n_y from -Ny/2 on
       const int e = k + q * f.r1;
       const int kk = e < Ny / 2 ? e : e - (n_y - Ny);
       if (e < Ny / 2 || e >= n_y - Ny / 2) {
         const T sc = cxj * dcy[kk];
-        cx_at(dst, unsigned(kk * nb)) = cx<T>{v.x * sc, v.y * sc};
+        cx_at(dst, unsigned(kk * pg)) = cx<T>{v.x * sc, v.y * sc};
       }
     });
   }
 }
 
 template <typename T>
-__device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, int Nx, int Ny, int bins,
+__device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny, int bins,
                                            const T* __restrict__ dcx, const T* __restrict__ dcy,
                                            FftDesc<T> fd, cx<T>* __restrict__ Gh, int wm, int bx, int by,
                                            const int* __restrict__ jrange = nullptr, int tid = threadIdx.x) {
@@ -216,10 +222,10 @@ __device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, 
   const int b0 = bx * bins;
   const int nbc = min(bins, nb - b0);
   if (jrange && (b0 + nbc - 1 < jrange[2 * jj] || b0 > jrange[2 * jj + 1])) return;
-  const cx<T>* src = V + (size_t(b0) * Nx + jj) * n_y;  // bin b0 + bi at src + bi * Nx * n_y
-  const size_t bin_stride = size_t(Nx) * n_y;
+  const cx<T>* src = V + (size_t(b0) * Nx + jj) * pv;  // bin b0 + bi at src + bi * Nx * pv
+  const size_t bin_stride = size_t(Nx) * pv;
   const T cxj = dcx[jj];
-  cx<T>* dst = Gh + size_t(jj) * Ny * nb + b0;
+  cx<T>* dst = Gh + size_t(jj) * Ny * pg + b0;
   // output mode kk of the Ny kept, centred, at its slot of the n_y transform
   auto slot = [&](int kk) {
     const int k = kk < Ny / 2 ? kk : kk - Ny;
@@ -252,7 +258,7 @@ __device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, 
       },
       [&](int q, cx<T> v) {
         const int kk = div_nbc(q);
-        dst[size_t(kk) * nb + (q - kk * nbc)] = v;
+        dst[size_t(kk) * pg + (q - kk * nbc)] = v;
       });
 }
 
@@ -270,7 +276,7 @@ __device__ __forceinline__ void y_item(const int* __restrict__ ylist, int gl, in
 }
 
 template <typename T>
-__global__ __launch_bounds__(kFftThreads) void k_fft_y(const cx<T>* __restrict__ V, int nb, int Nx, int Ny, int bins,
+__global__ __launch_bounds__(kFftThreads) void k_fft_y(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny, int bins,
                                                      const T* __restrict__ dcx, const T* __restrict__ dcy,
                                                      FftDesc<T> fd, cx<T>* __restrict__ Gh, int wm,
                                                      const int* __restrict__ jrange, const int* __restrict__ ylist) {
@@ -278,18 +284,18 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_y(const cx<T>* __restrict__
   // keep them on one XCD so its L2 merges the halves
   int bx, by;
   y_item(ylist, xcd_linear(), bx, by);
-  fft_y_body<T>(V, nb, Nx, Ny, bins, dcx, dcy, fd, Gh, wm, bx, by, jrange);
+  fft_y_body<T>(V, nb, pv, pg, Nx, Ny, bins, dcx, dcy, fd, Gh, wm, bx, by, jrange);
 }
 
 template <typename T, int CLS>
-__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_y_reg(const cx<T>* __restrict__ V, int nb, int Nx, int Ny,
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_y_reg(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny,
                                                            const T* __restrict__ dcx, const T* __restrict__ dcy,
                                                            Fft2Raw f, cx<T>* __restrict__ Gh,
                                                            const int* __restrict__ jrange,
                                                            const int* __restrict__ ylist) {
   int bx, by;
   y_item(ylist, xcd_linear(), bx, by);
-  fft_y_reg_body<T, CLS>(V, nb, Nx, Ny, dcx, dcy, as_fft2<T>(f), Gh, bx, by, jrange, threadIdx.x);
+  fft_y_reg_body<T, CLS>(V, nb, pv, pg, Nx, Ny, dcx, dcy, as_fft2<T>(f), Gh, bx, by, jrange, threadIdx.x);
 }
 
 template <typename T>
@@ -306,7 +312,8 @@ hipError_t launch_fft_y(const DevPlan& p, const void* V, void* Gh, hipStream_t s
       constexpr auto kern = &k_fft_y_reg<T, decltype(c)::value>;
       hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(kern, grid, dim3(fft2_threads(f)), lds, s, static_cast<const cx<T>*>(V), p.nb, p.Nx, p.Ny,
+      hipLaunchKernelGGL(kern, grid, dim3(fft2_threads(f)), lds, s, static_cast<const cx<T>*>(V), p.nb, p.pitch_v,
+                         p.pitch_g, p.Nx, p.Ny,
                          static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), f, static_cast<cx<T>*>(Gh),
                          p.jrange, ylist);
       return hipGetLastError();
@@ -317,7 +324,8 @@ hipError_t launch_fft_y(const DevPlan& p, const void* V, void* Gh, hipStream_t s
     return hipErrorInvalidValue;
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_fft_y<T>), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_fft_y<T>, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(V), p.nb, p.Nx, p.Ny,
+  hipLaunchKernelGGL(k_fft_y<T>, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(V), p.nb, p.pitch_v,
+                     p.pitch_g, p.Nx, p.Ny,
                      bins, static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), as_desc<T>(p.f_ny),
                      static_cast<cx<T>*>(Gh), cfg.wave, p.jrange, ylist);
   return hipGetLastError();
@@ -516,10 +524,10 @@ __global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_x_
     const int local = w - prefix[p];
     const int by = local / a.gx;
     if constexpr (CLS > 0)
-      fft_x_reg_body<T, CLS>(static_cast<const cx<T>*>(a.U), a.n_y, a.Nx, 0, as_fft2<T>(a.f2),
+      fft_x_reg_body<T, CLS>(static_cast<const cx<T>*>(a.U), a.n_y, a.pitch_u, a.pitch_v, a.Nx, 0, as_fft2<T>(a.f2),
                              static_cast<cx<T>*>(a.V), local - by * a.gx, by, a.brange, loop_lane());
     else
-      fft_x_body<T>(static_cast<const cx<T>*>(a.U), a.n_y, a.Nx, a.rows, 0, view_desc<T>(a.fd),
+      fft_x_body<T>(static_cast<const cx<T>*>(a.U), a.n_y, a.pitch_u, a.pitch_v, a.Nx, a.rows, 0, view_desc<T>(a.fd),
                     static_cast<cx<T>*>(a.V), 0, local - by * a.gx, by, a.brange, loop_lane());
   }
 }
@@ -541,11 +549,11 @@ __global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_y_
       bx = e & 0xffff;
     }
     if constexpr (CLS > 0)
-      fft_y_reg_body<T, CLS>(static_cast<const cx<T>*>(a.V), a.nb, a.Nx, a.Ny, static_cast<const T*>(a.dcx),
+      fft_y_reg_body<T, CLS>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, static_cast<const T*>(a.dcx),
                              static_cast<const T*>(a.dcy), as_fft2<T>(a.f2), static_cast<cx<T>*>(a.Gh), bx, by,
                              a.jrange, loop_lane());
     else
-      fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.Nx, a.Ny, a.bins, static_cast<const T*>(a.dcx),
+      fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, a.bins, static_cast<const T*>(a.dcx),
                     static_cast<const T*>(a.dcy), view_desc<T>(a.fd), static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
                     loop_lane());
   }

@@ -60,7 +60,7 @@ __device__ __forceinline__ void accum(cx<T>& a, cx<T>& c, T wt, cx<T> g) {
 // and XCD-contiguous or patch-major block orders were slower.
 
 template <typename T, bool KAHAN>
-__device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, int nb,
+__device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, int nb, int pitch_t, int pitch_u,
                                                  const int4* __restrict__ slot_rng,
                                                  const int* __restrict__ slot_sens, const T* __restrict__ slot_w,
                                                  const unsigned* __restrict__ slot_k, int n_x, int n_y,
@@ -123,7 +123,7 @@ __device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, i
       // an empty place loads sensor 0's row: no lane reads it
       const int rq = min(row / K, nq - 1);
       const int sid = row / K < nq ? max(0, slot_sens[size_t(qb + rq) * K + (row - (row / K) * K)]) : 0;
-      const cx<T>* gs = Gt + size_t(sid) * nb;
+      const cx<T>* gs = Gt + size_t(sid) * pitch_t;
       __syncthreads();  // the previous round has been consumed
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
@@ -149,8 +149,8 @@ __device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, i
     if (px < n_x && py < n_y) {
       // non-temporal stores: the grid streams out once (read back by the
       // x-FFT only); measured 17 % faster at the headline size
-      cx<T>* out = U + (size_t(b0 - b_begin) * n_y + py) * n_x + px;
-      const size_t slice = size_t(n_y) * n_x;
+      cx<T>* out = U + (size_t(b0 - b_begin) * n_y + py) * pitch_u + px;
+      const size_t slice = size_t(n_y) * pitch_u;
 #pragma unroll
       for (int b = 0; b < BC; ++b)
         if (b < nbc) nt_store(out + b * slice, acc[b]);
@@ -159,14 +159,14 @@ __device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, i
 }
 
 template <typename T, bool KAHAN>
-__global__ __launch_bounds__(64) void k_spread_slots(const cx<T>* __restrict__ Gt, int nb,
+__global__ __launch_bounds__(64) void k_spread_slots(const cx<T>* __restrict__ Gt, int nb, int pitch_t, int pitch_u,
                                                      const int4* __restrict__ slot_rng,
                                                      const int* __restrict__ slot_sens,
                                                      const T* __restrict__ slot_w,
                                                      const unsigned* __restrict__ slot_k, int n_x, int n_y,
                                                      int tiles_x, int nchunks, int heavy, int groups, int b_begin,
                                                      int b_end, cx<T>* __restrict__ U) {
-  spread_slot_body<T, KAHAN>(Gt, nb, slot_rng, slot_sens, slot_w, slot_k, n_x, n_y, tiles_x, nchunks, heavy, groups,
+  spread_slot_body<T, KAHAN>(Gt, nb, pitch_t, pitch_u, slot_rng, slot_sens, slot_w, slot_k, n_x, n_y, tiles_x, nchunks, heavy, groups,
                              b_begin, b_end, U, blockIdx.x);
 }
 
@@ -179,12 +179,12 @@ hipError_t launch_spread(const DevPlan& p, const void* Gt, void* U, int b_begin,
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   if (p.kahan)
     hipLaunchKernelGGL((k_spread_slots<T, true>), dim3((unsigned)blocks), dim3(64), 0, s,
-                       static_cast<const cx<T>*>(Gt), p.nb, p.slot_rng, p.slot_sens,
+                       static_cast<const cx<T>*>(Gt), p.nb, p.pitch_t, p.pitch_u, p.slot_rng, p.slot_sens,
                        static_cast<const T*>(p.slot_w), p.slot_k, p.n_x, p.n_y, p.tiles_x, nchunks, p.spread_heavy,
                        groups, b_begin, b_end, static_cast<cx<T>*>(U));
   else
     hipLaunchKernelGGL((k_spread_slots<T, false>), dim3((unsigned)blocks), dim3(64), 0, s,
-                       static_cast<const cx<T>*>(Gt), p.nb, p.slot_rng, p.slot_sens,
+                       static_cast<const cx<T>*>(Gt), p.nb, p.pitch_t, p.pitch_u, p.slot_rng, p.slot_sens,
                        static_cast<const T*>(p.slot_w), p.slot_k, p.n_x, p.n_y, p.tiles_x, nchunks, p.spread_heavy,
                        groups, b_begin, b_end, static_cast<cx<T>*>(U));
   return hipGetLastError();
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(64) void k_spread_batch(const SpreadBA* __restrict_
     const int w = batch_item(slot, total);
     const int p = batch_locate(prefix, w);
     const SpreadBA a = args[p];
-    spread_slot_body<T, KAHAN>(static_cast<const cx<T>*>(a.Gt), a.nb, a.slot_rng, a.slot_sens,
+    spread_slot_body<T, KAHAN>(static_cast<const cx<T>*>(a.Gt), a.nb, a.pitch_t, a.pitch_u, a.slot_rng, a.slot_sens,
                                static_cast<const T*>(a.slot_w), a.slot_k, a.n_x, a.n_y, a.tiles_x, a.nchunks,
                                a.heavy, a.groups, 0, a.nb, static_cast<cx<T>*>(a.U), w - prefix[p]);
   }

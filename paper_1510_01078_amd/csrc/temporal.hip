@@ -29,7 +29,7 @@ constexpr int temporal_threads() { return NCT > 0 ? kTemporalCtThreads : kTempor
 template <typename T, int NCT = 0>
 __device__ __forceinline__ void temporal_body(const T* __restrict__ g, int M, int Nt, int n0,
                                               const T* __restrict__ hw, const T* __restrict__ deap,
-                                              FftDesc<T> fd, int b_lo, int nb, cx<T>* __restrict__ Gt, int bx,
+                                              FftDesc<T> fd, int b_lo, int nb, int pitch, cx<T>* __restrict__ Gt, int bx,
                                               int tid = threadIdx.x) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
@@ -75,17 +75,17 @@ __device__ __forceinline__ void temporal_body(const T* __restrict__ g, int M, in
     const cx<T> z = buf[lpos(pb)];
     const cx<T> zm = buf[lpos(mb)];
     // transform of the real part: (Z_b + conj Z_-b)/2; of the imaginary part: (Z_b - conj Z_-b)/(2i)
-    Gt[size_t(m0) * nb + i] = cx<T>{T(0.5) * (z.x + zm.x), T(0.5) * (z.y - zm.y)};
-    if (has1) Gt[size_t(m0 + 1) * nb + i] = cx<T>{T(0.5) * (z.y + zm.y), T(-0.5) * (z.x - zm.x)};
+    Gt[size_t(m0) * pitch + i] = cx<T>{T(0.5) * (z.x + zm.x), T(0.5) * (z.y - zm.y)};
+    if (has1) Gt[size_t(m0 + 1) * pitch + i] = cx<T>{T(0.5) * (z.y + zm.y), T(-0.5) * (z.x - zm.x)};
   }
 }
 
 template <typename T, int NCT>
 __global__ __launch_bounds__(temporal_threads<NCT>()) void k_temporal(const T* __restrict__ g, int M, int Nt, int n0,
                                                              const T* __restrict__ hw, const T* __restrict__ deap,
-                                                             FftDesc<T> fd, int b_lo, int nb,
+                                                             FftDesc<T> fd, int b_lo, int nb, int pitch,
                                                              cx<T>* __restrict__ Gt) {
-  temporal_body<T, NCT>(g, M, Nt, n0, hw, deap, fd, b_lo, nb, Gt, blockIdx.x);
+  temporal_body<T, NCT>(g, M, Nt, n0, hw, deap, fd, b_lo, nb, pitch, Gt, blockIdx.x);
 }
 
 template <typename T>
@@ -100,7 +100,7 @@ hipError_t launch_temporal(const DevPlan& p, const T* g, void* Gt, bool weighted
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_temporal<T, NCT>), dim3(blocks), dim3(NT), lds, s, g, p.M,
                        p.Nt, p.n0, weighted ? static_cast<const T*>(p.hw) : nullptr, static_cast<const T*>(p.deap),
-                       as_desc<T>(p.f_nt), p.b_lo, p.nb, static_cast<cx<T>*>(Gt));
+                       as_desc<T>(p.f_nt), p.b_lo, p.nb, p.pitch_t, static_cast<cx<T>*>(Gt));
     return hipGetLastError();
   });
 }
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kTemporalThreads) void k_temporal_batch(const Tempo
     const int p = batch_locate(prefix, w);
     const TemporalBA a = args[p];
     temporal_body<T>(static_cast<const T*>(io.in[p]), a.M, a.Nt, a.n0, static_cast<const T*>(a.hw),
-                     static_cast<const T*>(a.deap), view_desc<T>(a.fd), a.b_lo, a.nb, static_cast<cx<T>*>(a.Gt),
+                     static_cast<const T*>(a.deap), view_desc<T>(a.fd), a.b_lo, a.nb, a.pitch_t, static_cast<cx<T>*>(a.Gt),
                      w - prefix[p], loop_lane());
   }
 }
