@@ -551,16 +551,18 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   // workspace: region A = grid chunk U, later the lateral spectra Gh;
   // region B = x-transformed rows V, later the spectrum F; region C = Gt.
   const size_t c = cxb;
-  const size_t sz_F = size_t(d.nx) * d.ny * (d.nz / 2 + 1) * c;
   auto layout = [&](int unit) {
     auto up = [&](int n) { return (n + unit - 1) / unit * unit; };
     dp.pitch_u = up(dp.n_x);
     dp.pitch_v = up(dp.n_y);
     dp.pitch_g = up(dp.nb);
     dp.pitch_t = up(dp.nb);
+    dp.pitch_f = up(d.nz / 2);
     const size_t sz_U = size_t(dp.chunk_bins) * dp.n_y * dp.pitch_u * c;
     const size_t sz_V = size_t(dp.nb) * d.nx * dp.pitch_v * c;
     const size_t sz_Gh = size_t(d.nx) * d.ny * dp.pitch_g * c;
+    // F, and the forward model's transformed image with its l = Nz/2 plane
+    const size_t sz_F = size_t(d.nx) * d.ny * std::max(dp.pitch_f, d.nz / 2 + 1) * c;
     P->off_B = align_up(std::max(sz_U, sz_Gh));
     P->off_C = P->off_B + align_up(std::max(sz_V, sz_F));
     P->ws_bytes = P->off_C + align_up(size_t(M) * dp.pitch_t * c);
@@ -640,7 +642,7 @@ pat_status run_traces_in(pat_plan* P, const void* g, void* out, void* ws, hipStr
   const int mode = op == OP_ADJOINT ? patk::GATHER_ADJOINT : patk::GATHER_IMAGE;
   if ((e = patk::launch_gather_x<T>(dp, A, B, mode, s)) != hipSuccess) return to_status(e);
   mark(4, 5);
-  if ((e = patk::launch_inverse<T>(dp, B, static_cast<T*>(out), s, true)) != hipSuccess) return to_status(e);
+  if ((e = patk::launch_inverse<T>(dp, B, static_cast<T*>(out), s)) != hipSuccess) return to_status(e);
   mark(5, -1);
   return PAT_OK;
 }

@@ -84,7 +84,7 @@ void destroy_batch(pat_batch* B) {
 template <typename T>
 void problem_regions(const patk::DevPlan& d, size_t& a, size_t& b, size_t& cc) {
   const size_t c = sizeof(patk::cx<T>);
-  const size_t lh = size_t(d.Nz / 2 + 1);
+  const size_t lh = size_t(d.pitch_f);
   a = align_up(std::max(size_t(d.nb) * d.n_y * d.pitch_u * c, size_t(d.Nx) * d.Ny * d.pitch_g * c));
   b = align_up(std::max(size_t(d.nb) * d.Nx * d.pitch_v * c, size_t(d.Nx) * d.Ny * lh * c));
   cc = align_up(size_t(d.M) * d.pitch_t * c);
@@ -124,7 +124,7 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     void* Bw = ws + off + ra;
     void* C = ws + off + ra + rb;
     off += ra + rb + rc;
-    const int Lh = d.Nz / 2 + 1;
+    const int Lz = d.Nz / 2;
     if (d.n_t > patk::kFftMaxV * 512) return PAT_ERR_UNSUPPORTED;
     // stage 0: temporal FFT, one block per sensor pair
     a0[p] = patk::TemporalBA{d.hw, d.deap, patk::as_view(d.f_nt), d.M, d.Nt, d.n0, d.b_lo, d.nb, d.pitch_t, C};
@@ -161,29 +161,45 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     threads[3][p] = fy.r1 ? patk::fft2_threads(fy) : cfg.threads;
     // stage 4: temporal interpolation and weight (image-ready spectrum) fused
     // with the inverse transform along x
-    const int lcx = patk::fft_batch<T>(d.Nx, icfg.threads, patk::kGatherCap);
-    const int gx5 = (Lh + lcx - 1) / lcx;
+    int lcx;
+    patk::Fft2Raw f4;
+    size_t slots4;
+    patk::gather_shape<T>(d, lcx, f4, slots4);
+    const int gx5 = (Lz + lcx - 1) / lcx;
     int wt_ct = 0;
     for (int t : patk::kBatchTaps)
       if (d.w_t == t && d.w_t * (d.hdeg + 1) <= patk::kMaxTapCoefs) wt_ct = t;
     a4[p] = patk::GatherBA{A, d.hcoef, d.nb, d.b_lo, d.Nx, d.Ny, d.Nz, d.w_t, d.hdeg, wt_ct, d.pitch_g,
                            d.s_per_k, d.kxu, d.kyu, d.kzu, d.two_c, d.n0_over_nt, d.inv_vol, Bw,
-                           patk::as_view(d.f_Nx), lcx, gx5};
+                           patk::as_view(d.f_Nx), f4, lcx, gx5, d.pitch_f, 0};
     pre[4][p] = gx5 * d.Ny;
-    lds[4][p] = (size_t(lcx) * patk::lseq(d.Nx) + d.Nx) * c;
+    lds[4][p] = slots4 * c;
+    variant[4][p] = f4.r1 ? patk::reg_class(f4) : 0;
+    threads[4][p] = icfg.threads;
     // stage 5: inverse transform along y (in place on the spectrum)
-    const int lcy = patk::fft_batch<T>(d.Ny, icfg.threads, icfg.cap);
-    const int gx6 = (Lh + lcy - 1) / lcy;
-    a5[p] = patk::CfftBA{Bw, patk::as_view(d.f_Ny), d.Ny, Lh, lcy, gx6};
+    const int lcy = patk::fft_seqs<T>(d.f_Ny, d.f_Ny.two.r1 ? patk::kInvYThreads : icfg.threads, icfg.cap);
+    const patk::Fft2Raw f5 = d.f_Ny.two.r1 ? patk::fft2_shape<T>(d.f_Ny, lcy) : d.f_Ny.two;
+    const int gx6 = (Lz + lcy - 1) / lcy;
+    a5[p] = patk::CfftBA{Bw, patk::as_view(d.f_Ny), f5, Lz, d.pitch_f, lcy, gx6};
     pre[5][p] = gx6 * d.Nx;
-    lds[5][p] = (size_t(lcy) * patk::lseq(d.Ny) + d.Ny) * c;
+    lds[5][p] = (f5.r1 ? patk::fft2_slots(f5) : size_t(lcy) * patk::lseq(d.Ny) + d.Ny) * c;
+    variant[5][p] = f5.r1 ? patk::reg_class(f5) : 0;
+    threads[5][p] = f5.r1 ? patk::fft2_threads(f5) : icfg.threads;
     // stage 6: complex-to-real along z into the caller's image
-    const int rz = patk::fft_batch<T>(d.Nz, icfg.threads, icfg.cap);
     const long long nrows = (long long)d.Nx * d.Ny;
-    a6[p] = patk::C2rBA{Bw, patk::as_view(d.f_Nz), nrows, rz};
+    int rz = patk::fft_batch<T>(d.Nz, icfg.threads, icfg.cap);
+    patk::Fft2Raw f6 = d.f_Nz.two;
+    if (f6.r1) {
+      f6 = patk::fft2_shape<T>(d.f_Nz, patk::fft_seqs<T>(d.f_Nz, icfg.threads, patk::kC2rSeqs));
+      rz = 2 << f6.ls;
+    } else if ((rz + 1) / 2 * (d.Nz / 2 + 1) > patk::kC2rStage * icfg.threads) {
+      return PAT_ERR_UNSUPPORTED;
+    }
+    a6[p] = patk::C2rBA{Bw, patk::as_view(d.f_Nz), f6, nrows, rz, d.pitch_f, p, 0};
     pre[6][p] = int((nrows + rz - 1) / rz);
-    if ((rz + 1) / 2 * (d.Nz / 2 + 1) > patk::kC2rStage * icfg.threads) return PAT_ERR_UNSUPPORTED;
-    lds[6][p] = size_t(patk::c2r_lds_slots(rz, d.Nz)) * c;
+    lds[6][p] = (f6.r1 ? patk::fft2_slots(f6) : size_t(patk::c2r_lds_slots(rz, d.Nz))) * c;
+    variant[6][p] = f6.r1 ? patk::reg_class(f6) : 0;
+    threads[6][p] = f6.r1 ? patk::fft2_threads(f6) : icfg.threads;
   }
   // each stage's launches: the problems of one variant, their arguments and
   // the running sums of their work items

@@ -254,13 +254,16 @@ __device__ __forceinline__ cx<T>& cx_at(cx<T>* base, unsigned at) {
 
 // Kernels of two-pass transforms come in three classes by the larger radix,
 // since the largest radix a kernel holds sets its registers: up to 16 (72
-// registers in FP32: 7 waves per SIMD), 18 and 20 (5 waves), 24 to 32 (4
+// registers in FP32: 6 waves per SIMD), 18 and 20 (5 waves), 24 to 32 (4
 // waves). One kernel for all took 128 registers, and the batched x pass over
 // lengths of 96 to 288 points 1.19 instead of 0.93 ms.
 constexpr int reg_larger(const Fft2Raw& f) { return f.r1 > f.r2 ? f.r1 : f.r2; }
 constexpr int reg_class(const Fft2Raw& f) { return reg_larger(f) <= 16 ? 16 : reg_larger(f) <= 20 ? 20 : 32; }
 template <typename T, int CLS>
-constexpr int reg_waves() { return sizeof(T) == 4 ? (CLS == 16 ? 7 : CLS == 20 ? 5 : 4) : (CLS == 16 ? 3 : 2); }
+constexpr int reg_waves() { return sizeof(T) == 4 ? (CLS == 16 ? 6 : CLS == 20 ? 5 : 4) : (CLS == 16 ? 3 : 2); }
+// kernels that also come for lengths without a two-pass transform (CLS 0)
+template <typename T, int CLS>
+constexpr int any_waves() { return CLS > 0 ? reg_waves<T, CLS ? CLS : 16>() : 1; }
 
 // go(std::integral_constant<int, CLS>) for the class of a transform
 template <class F>
@@ -270,6 +273,11 @@ static inline hipError_t class_pick(const Fft2Raw& f, F&& go) {
     case 20: return go(std::integral_constant<int, 20>{});
     default: return go(std::integral_constant<int, 32>{});
   }
+}
+// the same, 0 for a length without a two-pass transform
+template <class F>
+static inline hipError_t class_pick_any(const Fft2Raw& f, F&& go) {
+  return f.r1 ? class_pick(f, go) : go(std::integral_constant<int, 0>{});
 }
 
 // tid / d for tid < 1024 and 1 < d <= 32 (exact: the error of m is below
@@ -292,6 +300,29 @@ __device__ __forceinline__ void reg_first(cx<T>* seq, int r2, int Q, const cx<T>
   seq[i] = v[0];
 #pragma unroll
   for (int r = 1; r < R; ++r) seq[i + r * Q] = twiddle<T, INV>(v[r], w[r]);
+}
+
+// First pass of sequences that already sit in LDS in natural order (element e
+// at seq[e]): every butterfly is in registers before the barrier, so the
+// exchange takes the same LDS. Called by the whole work-group; `active`
+// threads hold a butterfly.
+template <typename T, int R, bool INV>
+__device__ __forceinline__ void reg_first_in_lds(cx<T>* seq, int r2, int Q, const cx<T>* __restrict__ tw, int i,
+                                                 bool active) {
+  cx<T> v[R], w[R];
+  if (active) {
+#pragma unroll
+    for (int r = 1; r < R; ++r) w[r] = tw[i + r * r2];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = seq[i + r * r2];
+    RDft<T, R, INV>::run(v);
+  }
+  __syncthreads();
+  if (active) {
+    seq[i] = v[0];
+#pragma unroll
+    for (int r = 1; r < R; ++r) seq[i + r * Q] = twiddle<T, INV>(v[r], w[r]);
+  }
 }
 
 // Second pass for the index k: st(q, v) takes output k + r1*q.
@@ -317,6 +348,19 @@ __device__ __forceinline__ void reg_second(const cx<T>* seq, int Q, int k, Store
 template <typename T, int CLS, bool INV, typename Load>
 __device__ __forceinline__ void reg_first_any(const Fft2<T>& f, cx<T>* seq, int i, Load ld) {
 #define PATK_CASE(R) case R: reg_first<T, R, INV>(seq, f.r2, f.Q, f.tw, i, ld); break;
+  if constexpr (CLS == 16) {
+    switch (f.r1) { PATK_RADICES_16(PATK_CASE) default: break; }
+  } else if constexpr (CLS == 20) {
+    switch (f.r1) { PATK_FIRST_20(PATK_CASE) default: break; }
+  } else {
+    switch (f.r1) { PATK_FIRST_32(PATK_CASE) default: break; }
+  }
+#undef PATK_CASE
+}
+
+template <typename T, int CLS, bool INV>
+__device__ __forceinline__ void reg_first_in_lds_any(const Fft2<T>& f, cx<T>* seq, int i, bool active) {
+#define PATK_CASE(R) case R: reg_first_in_lds<T, R, INV>(seq, f.r2, f.Q, f.tw, i, active); break;
   if constexpr (CLS == 16) {
     switch (f.r1) { PATK_RADICES_16(PATK_CASE) default: break; }
   } else if constexpr (CLS == 20) {

@@ -207,50 +207,51 @@ __global__ __launch_bounds__(256) void k_gather(const cx<T>* __restrict__ Gh, in
 // Gather fused with the first pass of the inverse 3-D FFT (image and
 // adjoint modes): a work-group owns one y mode kk and a run of lchunk z
 // modes, computes the spectrum for every x mode into LDS, transforms along x
-// there (the same transform and layout as the inverse x pass) and writes the
-// x-transformed values once. The spectrum itself never goes through HBM.
-template <typename T, int MODE, int WT, int NCT>
-__device__ __forceinline__ void gather_x_body(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
-                                              double s_per_k, double kxu, double kyu, double kzu, double two_c,
-                                              double n0_over_nt, double scale, int wt, int deg,
-                                              const T* __restrict__ hcoef, int lchunk, FftDesc<T> fd, int wm,
-                                              cx<T>* __restrict__ F, int bx, int kk, const T* coefs) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
-  const int tid = threadIdx.x, nthr = blockDim.x;
-  const int Lh = Nz / 2 + 1;
-  const int bstride = lseq(Nx);
-  const int l0 = bx * lchunk;
-  const int nl = min(lchunk, Lh - l0);
-  cx<T>* twl = buf + lchunk * bstride;  // the twiddles go to LDS behind the rows
-  for (int t = tid; t < (NCT > 0 ? NCT : fd.n); t += nthr) twl[t] = fd.tw[t];
-  __syncthreads();
+// there and writes the x-transformed values F[jj][kk][l] once (l < Nz/2: the
+// plane l = Nz/2 is zero and not stored, so no run ends in one z mode). The
+// spectrum itself never goes through HBM. In two steps, so that a batch runs
+// one transform for all tap counts.
+template <typename T, int MODE, int WT>
+__device__ __forceinline__ void gather_fill(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny,
+                                            int Nz, double s_per_k, double kxu, double kyu, double kzu, double two_c,
+                                            double n0_over_nt, double scale, int wt, int deg,
+                                            const T* __restrict__ hcoef, int l0, int nl, bool padded, int stride,
+                                            cx<T>* buf, int kk, const T* coefs) {
   const FastDiv div_nl(nl);
   // (one loop form for every length: the batched reconstruction runs this
   // loop too, and the same code keeps the two paths' values bit for bit equal)
-  constexpr int ROWS = NCT > 0 ? ct_maxb(NCT, kGatherCap) : 1;
-  for (int q = tid; q < nl * Nx; q += nthr) {
+  for (int q = threadIdx.x; q < nl * Nx; q += blockDim.x) {
     const int jj = div_nl(q);
     const int li = q - jj * nl;
-    buf[li * bstride + lpos(jj)] =
-        gather_point<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt,
-                                  deg, hcoef, jj, kk, l0 + li, coefs);
+    buf[li * stride + (padded ? lpos(jj) : jj)] =
+        gather_point<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale,
+                                  wt, deg, hcoef, jj, kk, l0 + li, coefs);
   }
-  __syncthreads();
-  if constexpr (NCT > 0)
-    fft_ct<T, NCT, kFftThreads, ROWS, true>(buf, nl, twl, tid);
-  else
-    fft_group<T, true>(buf, lds_twiddles(fd, twl), nl, bstride, tid, nthr, wm);
-  __syncthreads();
-  cx<T>* base = F + size_t(kk) * Lh + l0;  // x mode jj, z mode l0 + li at base[jj * Ny * Lh + li]
-  const size_t col = size_t(Ny) * Lh;
-  if constexpr (NCT > 0) {
-    cx<T>* b0 = base + size_t(tid / ROWS) * col + tid % ROWS;
-    const size_t step = size_t(kFftThreads / ROWS) * col;
-    staged_cols<ROWS, kFftThreads, NCT * ROWS / kFftThreads>(  // Nx = NCT
-        NCT, nl, tid, [&](int jj, int li, int) { return buf[li * bstride + lpos(jj)]; },
-        [&](int, int, int u, cx<T> v) { b0[u * step] = v; });
+}
+
+// x transform of the nl rows and the write; CLS 0: passes in LDS with the
+// runtime plan and the twiddles behind the rows.
+template <typename T, int CLS>
+__device__ __forceinline__ void gather_transform(cx<T>* buf, const Fft2Raw& f2, const FftDesc<T>& fd, int lchunk,
+                                                 int Nx, int Ny, int nl, int wm, cx<T>* __restrict__ F, int pitch_f,
+                                                 int l0, int kk) {
+  const int tid = threadIdx.x, nthr = blockDim.x;
+  cx<T>* base = F + size_t(kk) * pitch_f + l0;  // x mode jj, z mode l0 + li at base[jj * Ny * pitch_f + li]
+  if constexpr (CLS > 0) {
+    const Fft2<T> f = as_fft2<T>(f2);
+    const int s = tid & ((1 << f.ls) - 1), i = tid >> f.ls;
+    cx<T>* seq = buf + s * f.P;
+    reg_first_in_lds_any<T, CLS, true>(f, seq, i, s < nl && i < f.r2);
+    __syncthreads();
+    if (s < nl && i < f.r1) {
+      const size_t col = size_t(Ny) * pitch_f;
+      reg_second_any<T, CLS, true>(f, seq, i, [&](int q, cx<T> v) { base[(i + q * f.r1) * col + s] = v; });
+    }
   } else {
+    const int bstride = lseq(Nx);
+    const FastDiv div_nl(nl);
+    fft_group<T, true>(buf, lds_twiddles(fd, buf + lchunk * bstride), nl, bstride, tid, nthr, wm);
+    __syncthreads();
     staged_copy<kFftMaxV>(
         nl * Nx, tid, nthr,
         [&](int q) {
@@ -259,24 +260,34 @@ __device__ __forceinline__ void gather_x_body(const cx<T>* __restrict__ Gh, int 
         },
         [&](int q, cx<T> v) {
           const int jj = div_nl(q);
-          base[jj * col + (q - jj * nl)] = v;
+          base[jj * size_t(Ny) * pitch_f + (q - jj * nl)] = v;
         });
   }
 }
 
-template <typename T, int MODE, int WT, int NCT>
-__global__ __launch_bounds__(kFftThreads) void k_gather_x(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx,
-                                                        int Ny, int Nz, double s_per_k, double kxu, double kyu,
-                                                        double kzu, double two_c, double n0_over_nt, double scale,
-                                                        int wt, int deg, const T* __restrict__ hcoef, int lchunk,
-                                                        FftDesc<T> fd, int wm, cx<T>* __restrict__ F) {
+template <typename T, int MODE, int WT, int CLS>
+__global__ __launch_bounds__(kFftThreads) void k_gather_x(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo,
+                                                        int Nx, int Ny, int Nz, double s_per_k, double kxu,
+                                                        double kyu, double kzu, double two_c, double n0_over_nt,
+                                                        double scale, int wt, int deg, const T* __restrict__ hcoef,
+                                                        int lchunk, FftDesc<T> fd, Fft2Raw f2, int wm,
+                                                        cx<T>* __restrict__ F, int pitch_f) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   __shared__ T coefs[kMaxTapCoefs];
-  stage_tap_coefs<T, WT>(coefs, hcoef, deg);  // visible after the body's first barrier
+  stage_tap_coefs<T, WT>(coefs, hcoef, deg);
+  if constexpr (CLS == 0)
+    for (int t = threadIdx.x; t < fd.n; t += blockDim.x) buf[lchunk * lseq(Nx) + t] = fd.tw[t];
+  __syncthreads();
   // neighbouring groups share the 128-byte lines of the z runs: keep them on one XCD
   const int gl = xcd_linear();
   const int kk = gl / int(gridDim.x);
-  gather_x_body<T, MODE, WT, NCT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg,
-                                  hcoef, lchunk, fd, wm, F, gl - kk * int(gridDim.x), kk, coefs);
+  const int l0 = (gl - kk * int(gridDim.x)) * lchunk;
+  const int nl = min(lchunk, Nz / 2 - l0);
+  gather_fill<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg,
+                           hcoef, l0, nl, CLS == 0, CLS == 0 ? lseq(Nx) : f2.P, buf, kk, coefs);
+  __syncthreads();
+  gather_transform<T, CLS>(buf, f2, fd, lchunk, Nx, Ny, nl, wm, F, pitch_f, l0, kk);
 }
 
 // Compile-time tap counts: every even w_t in 2..16 (the plan's range).
@@ -295,15 +306,26 @@ static hipError_t wt_pick(int wt, F&& f) {
   }
 }
 
+// Shape of the fused gather: z modes per group, the two-pass transform (r1 = 0
+// for longer lengths) and LDS slots.
+template <typename T>
+void gather_shape(const DevPlan& p, int& lchunk, Fft2Raw& f2, size_t& slots) {
+  lchunk = fft_seqs<T>(p.f_Nx, inv_cfg().threads, kGatherCap);
+  f2 = p.f_Nx.two.r1 ? fft2_shape<T>(p.f_Nx, lchunk) : p.f_Nx.two;
+  slots = f2.r1 ? fft2_slots(f2) : size_t(lchunk) * lseq(p.Nx) + p.Nx;
+}
+
 template <typename T>
 hipError_t launch_gather_x(const DevPlan& p, const void* Gh, void* F, int mode, hipStream_t s) {
   if (mode != GATHER_IMAGE && mode != GATHER_ADJOINT) return hipErrorInvalidValue;
   if (p.w_t * (p.hdeg + 1) > kMaxTapCoefs) return hipErrorInvalidValue;
-  const int Lh = p.Nz / 2 + 1;
   const FftCfg cfg = inv_cfg();
-  const int lc = fft_batch<T>(p.Nx, cfg.threads, kGatherCap);
-  const size_t lds = (size_t(lc) * lseq(p.Nx) + p.Nx) * sizeof(cx<T>);
-  const dim3 grid((Lh + lc - 1) / lc, p.Ny);
+  int lc;
+  Fft2Raw f2;
+  size_t slots;
+  gather_shape<T>(p, lc, f2, slots);
+  const size_t lds = slots * sizeof(cx<T>);
+  const dim3 grid((p.Nz / 2 + lc - 1) / lc, p.Ny);
   const cx<T>* in = static_cast<const cx<T>*>(Gh);
   cx<T>* out = static_cast<cx<T>*>(F);
   const T* hc = static_cast<const T*>(p.hcoef);
@@ -311,23 +333,17 @@ hipError_t launch_gather_x(const DevPlan& p, const void* Gh, void* F, int mode, 
   const double scale = adj ? p.adj_scale : p.inv_vol;
   return wt_pick(p.w_t, [&](auto w) {
     constexpr int WT = decltype(w)::value;
-    return ct_pick(CtInverse{}, p.Nx, [&](auto c) {
-      constexpr int NCT = decltype(c)::value;
-      // the compile-time kernels take their geometry from the length
-      if (NCT > 0 && (lc != ct_maxb(NCT, kGatherCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
-      const void* kern = adj ? reinterpret_cast<const void*>(&k_gather_x<T, MODE_ADJOINT, WT, NCT>)
-                             : reinterpret_cast<const void*>(&k_gather_x<T, MODE_IMAGE, WT, NCT>);
-      hipError_t e = allow_lds(kern, lds);
-      if (e != hipSuccess) return e;
-      if (adj)
-        hipLaunchKernelGGL((k_gather_x<T, MODE_ADJOINT, WT, NCT>), grid, dim3(cfg.threads), lds, s, in, p.nb, p.pitch_g, p.b_lo,
-                           p.Nx, p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, scale, p.w_t,
-                           p.hdeg, hc, lc, as_desc<T>(p.f_Nx), cfg.wave, out);
-      else
-        hipLaunchKernelGGL((k_gather_x<T, MODE_IMAGE, WT, NCT>), grid, dim3(cfg.threads), lds, s, in, p.nb, p.pitch_g, p.b_lo,
-                           p.Nx, p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, scale, p.w_t,
-                           p.hdeg, hc, lc, as_desc<T>(p.f_Nx), cfg.wave, out);
-      return hipGetLastError();
+    return class_pick_any(f2, [&](auto c) {
+      constexpr int CLS = decltype(c)::value;
+      auto go = [&](auto kern) {
+        hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, grid, dim3(cfg.threads), lds, s, in, p.nb, p.pitch_g, p.b_lo, p.Nx, p.Ny, p.Nz,
+                           p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, scale, p.w_t, p.hdeg, hc, lc,
+                           as_desc<T>(p.f_Nx), f2, cfg.wave, out, p.pitch_f);
+        return hipGetLastError();
+      };
+      return adj ? go(&k_gather_x<T, MODE_ADJOINT, WT, CLS>) : go(&k_gather_x<T, MODE_IMAGE, WT, CLS>);
     });
   });
 }
@@ -536,30 +552,28 @@ hipError_t launch_scatter(const DevPlan& p, const void* Dh, void* Gh, int deriv,
 
 // Batched form of the reconstruction's interpolation (image-ready spectrum)
 // fused with the inverse transform along x, each work item as in the
-// single-problem launch (same arithmetic; the runtime-planned transform, as
-// the problems' lengths differ). Each problem runs with its own tap count at
-// compile time when it is one of kBatchTaps (else the runtime-tap form); a
-// work-group restages the tap coefficients in LDS when its next work item
-// belongs to another problem.
+// single-problem launch (same arithmetic). Each problem runs with its own tap
+// count at compile time when it is one of kBatchTaps (else the runtime-tap
+// form); a work-group restages the tap coefficients in LDS when its next work
+// item belongs to another problem.
 template <typename T, int WT>
-__device__ __forceinline__ void gather_batch_item(const GatherBA& a, T* coefs, int& staged, int p, int local) {
+__device__ __forceinline__ void gather_batch_fill(const GatherBA& a, T* coefs, bool stage, int l0, int nl, bool padded,
+                                                  int stride, cx<T>* buf, int kk) {
   if constexpr (WT > 0) {
-    if (p != staged) {  // visible after the body's first barrier
-      stage_tap_coefs<T, WT>(coefs, static_cast<const T*>(a.hcoef), a.deg);
-      staged = p;
-    }
+    if (stage) stage_tap_coefs<T, WT>(coefs, static_cast<const T*>(a.hcoef), a.deg);
   }
-  const int kk = local / a.gx;
-  gather_x_body<T, MODE_IMAGE, WT, 0>(static_cast<const cx<T>*>(a.Gh), a.nb, a.pitch_g, a.b_lo, a.Nx, a.Ny, a.Nz, a.s_per_k,
-                                      a.kxu, a.kyu, a.kzu, a.two_c, a.n0_over_nt, a.scale, a.wt, a.deg,
-                                      static_cast<const T*>(a.hcoef), a.lchunk, view_desc<T>(a.fd), 0,
-                                      static_cast<cx<T>*>(a.Fh), local - kk * a.gx, kk, coefs);
+  __syncthreads();
+  gather_fill<T, MODE_IMAGE, WT>(static_cast<const cx<T>*>(a.Gh), a.nb, a.pitch_g, a.b_lo, a.Nx, a.Ny, a.Nz,
+                                 a.s_per_k, a.kxu, a.kyu, a.kzu, a.two_c, a.n0_over_nt, a.scale, a.wt, a.deg,
+                                 static_cast<const T*>(a.hcoef), l0, nl, padded, stride, buf, kk, coefs);
 }
 
-template <typename T>
+template <typename T, int CLS>
 __global__ __launch_bounds__(kFftThreads) void k_gather_batch(const GatherBA* __restrict__ args,
                                                             const int* __restrict__ prefix, int total,
                                                             BatchIO io) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   __shared__ T coefs[kMaxTapCoefs];
   int staged = -1;
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
@@ -568,31 +582,44 @@ __global__ __launch_bounds__(kFftThreads) void k_gather_batch(const GatherBA* __
     const int p = batch_locate(prefix, w);
     const GatherBA a = args[p];
     const int local = w - prefix[p];
+    const int kk = local / a.gx;
+    const int l0 = (local - kk * a.gx) * a.lchunk;
+    const int nl = min(a.lchunk, a.Nz / 2 - l0);
+    const FftDesc<T> fd = view_desc<T>(a.fd);
+    const int stride = CLS == 0 ? lseq(a.Nx) : a.f2.P;
+    if constexpr (CLS == 0)
+      for (int t = threadIdx.x; t < fd.n; t += blockDim.x) buf[a.lchunk * stride + t] = fd.tw[t];
     static_assert(kBatchTaps[0] == 6 && kBatchTaps[1] == 8 && kBatchTaps[2] == 10 && kBatchTaps[3] == 12,
                   "tap instantiations");
+    const bool stage = p != staged;
+    staged = p;
     switch (a.wt_ct) {
-      case 6: gather_batch_item<T, 6>(a, coefs, staged, p, local); break;
-      case 8: gather_batch_item<T, 8>(a, coefs, staged, p, local); break;
-      case 10: gather_batch_item<T, 10>(a, coefs, staged, p, local); break;
-      case 12: gather_batch_item<T, 12>(a, coefs, staged, p, local); break;
-      default: gather_batch_item<T, 0>(a, coefs, staged, p, local); break;
+      case 6: gather_batch_fill<T, 6>(a, coefs, stage, l0, nl, CLS == 0, stride, buf, kk); break;
+      case 8: gather_batch_fill<T, 8>(a, coefs, stage, l0, nl, CLS == 0, stride, buf, kk); break;
+      case 10: gather_batch_fill<T, 10>(a, coefs, stage, l0, nl, CLS == 0, stride, buf, kk); break;
+      case 12: gather_batch_fill<T, 12>(a, coefs, stage, l0, nl, CLS == 0, stride, buf, kk); break;
+      default: gather_batch_fill<T, 0>(a, coefs, stage, l0, nl, CLS == 0, stride, buf, kk); break;
     }
+    __syncthreads();
+    gather_transform<T, CLS>(buf, a.f2, fd, a.lchunk, a.Nx, a.Ny, nl, 0, static_cast<cx<T>*>(a.Fh), a.pitch_f, l0, kk);
   }
 }
 
 template <typename T>
 hipError_t launch_gather_batch(const BatchStage& st, const BatchIO& io, hipStream_t s) {
   if (st.total <= 0) return hipSuccess;
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_gather_batch<T>), st.lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_gather_batch<T>), dim3(batch_grid(st)), dim3(256), st.lds, s,
-                     static_cast<const GatherBA*>(st.args), st.prefix, st.total, io);
-  return hipGetLastError();
+  switch (st.variant) {
+    case 16: return launch_batch_kernel<GatherBA>(&k_gather_batch<T, 16>, st, io, s);
+    case 20: return launch_batch_kernel<GatherBA>(&k_gather_batch<T, 20>, st, io, s);
+    case 32: return launch_batch_kernel<GatherBA>(&k_gather_batch<T, 32>, st, io, s);
+    default: return launch_batch_kernel<GatherBA>(&k_gather_batch<T, 0>, st, io, s);
+  }
 }
 
 #define PATK_INST(T)                                                                     \
   template hipError_t launch_gather<T>(const DevPlan&, const void*, void*, int, hipStream_t); \
   template hipError_t launch_gather_x<T>(const DevPlan&, const void*, void*, int, hipStream_t); \
+  template void gather_shape<T>(const DevPlan&, int&, Fft2Raw&, size_t&);               \
   template size_t scatter_lds_bytes<T>(const DevPlan&);                                  \
   template hipError_t launch_scatter<T>(const DevPlan&, const void*, void*, int, hipStream_t); \
   template hipError_t launch_gather_batch<T>(const BatchStage&, const BatchIO&, hipStream_t);

@@ -9,10 +9,89 @@
 namespace patk {
 
 // ---------------------------------------------------------------------------
-// Stage 5: equispaced inverse 3-D FFT (step 3 of the NEDNER list) on the
-// half spectrum Fh[jj][kk][l], l = 0..Nz/2: in-place inverse transforms
-// along x and along y, then a complex-to-real transform along z.
+// Stage 5: equispaced inverse 3-D FFT (step 3 of the NEDNER list). The x pass
+// runs with the gather; here the in-place inverse transform along y of
+// F[jj][kk][l], l = 0..Nz/2-1 (rows of `pitch` elements; the plane l = Nz/2 is
+// zero and not stored), then a complex-to-real transform along z. The forward
+// model's transforms (below) keep the plane and the passes in LDS.
 // ---------------------------------------------------------------------------
+
+// Two-pass register transform along y, in place: each pass's threads walk the
+// S z modes of one y mode (one line of 128 bytes where S = 16). Bound by HBM.
+template <typename T, int CLS>
+__device__ __forceinline__ void cfft_y_reg_body(cx<T>* __restrict__ F, int Lz, int pitch, const Fft2<T>& f, int bx,
+                                                int jj, int tid) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
+  const int S = 1 << f.ls;
+  const int l0 = bx << f.ls;
+  const int s = tid & (S - 1), i = tid >> f.ls;
+  const bool in = s < min(S, Lz - l0);
+  cx<T>* base = F + size_t(jj) * (f.r1 * f.r2) * pitch + l0 + s;  // y mode kk at base[kk * pitch]
+  if (in && i < f.r2)
+    reg_first_any<T, CLS, true>(f, buf + s * f.P, i, [&](int e) { return cx_at(base, unsigned(e * pitch)); });
+  __syncthreads();
+  if (in && i < f.r1)
+    reg_second_any<T, CLS, true>(f, buf + s * f.P, i,
+                                 [&](int q, cx<T> v) { cx_at(base, unsigned((i + q * f.r1) * pitch)) = v; });
+}
+
+template <typename T, int CLS>
+__global__ __launch_bounds__(kInvYThreads, (reg_waves<T, CLS>())) void k_cfft_y_reg(cx<T>* __restrict__ F, int Lz,
+                                                                                   int pitch, Fft2Raw f) {
+  // neighbouring groups share the 128-byte lines of the z runs: keep them on one XCD
+  const int gl = xcd_linear();
+  cfft_y_reg_body<T, CLS>(F, Lz, pitch, as_fft2<T>(f), gl % gridDim.x, gl / gridDim.x, threadIdx.x);
+}
+
+// Two-pass register transform of pairs of rows along z to real: two real rows
+// share one complex transform, Z = X0 + i X1 (each Hermitian-extended, loaded
+// as the first pass's inputs) transforms to x0 + i x1. The DC bin keeps its
+// real part only, as the real part of a single row's transform would; the
+// Nyquist bin is zero.
+template <typename T, int CLS>
+__device__ __forceinline__ void c2r_reg_body(const cx<T>* __restrict__ F, long long nrows, int pitch, const Fft2<T>& f,
+                                             T* __restrict__ out, int bx, int tid) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
+  const int Nz = f.r1 * f.r2;
+  const long long r0 = (long long)bx * (2 << f.ls);  // the group's first row
+  const int nr = (int)min((long long)(2 << f.ls), nrows - r0);
+  {
+    const int s = small_div(tid, f.r2), i = tid - s * f.r2;
+    if (2 * s < nr) {
+      const cx<T>* row = F + r0 * pitch;
+      const bool two = 2 * s + 1 < nr;
+      const unsigned at = unsigned(2 * s * pitch);
+      reg_first_any<T, CLS, true>(f, buf + s * f.P, i, [&](int e) {
+        const int l = min(e, Nz - e);
+        if (l == Nz / 2) return cx<T>{T(0), T(0)};
+        const cx<T> a = cx_at(row, at + unsigned(l));
+        const cx<T> c = two ? cx_at(row, at + unsigned(l + pitch)) : cx<T>{T(0), T(0)};
+        if (e == 0) return cx<T>{a.x, c.x};
+        return e == l ? cx<T>{a.x - c.y, a.y + c.x} : cx<T>{a.x + c.y, c.x - a.y};
+      });
+    }
+  }
+  __syncthreads();
+  const int s = small_div(tid, f.r1), k = tid - s * f.r1;
+  if (2 * s < nr && s < (1 << f.ls)) {
+    T* o = out + (r0 + 2 * s) * Nz + k;
+    const bool two = 2 * s + 1 < nr;
+    reg_second_any<T, CLS, true>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
+      o[q * f.r1] = v.x;
+      if (two) o[q * f.r1 + Nz] = v.y;
+    });
+  }
+}
+
+template <typename T, int CLS>
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_c2r_reg(const cx<T>* __restrict__ F,
+                                                                               long long nrows, int pitch, Fft2Raw f,
+                                                                               T* __restrict__ out) {
+  c2r_reg_body<T, CLS>(F, nrows, pitch, as_fft2<T>(f), out, blockIdx.x, threadIdx.x);
+}
+
 template <typename T, bool INV, int NCT = 0>
 __device__ __forceinline__ void cfft_x_body(cx<T>* __restrict__ F, int Ny, int Lh, int lchunk,
                                             FftDesc<T> fd, int wm, int bx, int by) {
@@ -80,8 +159,8 @@ __global__ __launch_bounds__(kFftThreads) void k_cfft_x(cx<T>* __restrict__ F, i
 }
 
 template <typename T, bool INV, int NCT = 0>
-__device__ __forceinline__ void cfft_y_body(cx<T>* __restrict__ F, int Lh, int lchunk, FftDesc<T> fd, int wm, int bx,
-                                            int by, int tid = threadIdx.x) {
+__device__ __forceinline__ void cfft_y_body(cx<T>* __restrict__ F, int Lh, int pitch, int lchunk, FftDesc<T> fd, int wm,
+                                            int bx, int by, int tid = threadIdx.x) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   const int nthr = blockDim.x;
@@ -90,13 +169,13 @@ __device__ __forceinline__ void cfft_y_body(cx<T>* __restrict__ F, int Lh, int l
   const int jj = by;
   const int l0 = bx * lchunk;
   const int nl = min(lchunk, Lh - l0);
-  cx<T>* base = F + size_t(jj) * Ny * Lh + l0;
+  cx<T>* base = F + size_t(jj) * Ny * pitch + l0;
   cx<T>* twl = buf + lchunk * bstride;  // the twiddles go to LDS behind the rows
   if constexpr (NCT > 0) {
     // compile-time geometry (lchunk = ROWS z modes, 256 threads): no index divisions
     constexpr int ROWS = ct_maxb(NCT, kInvCap), BS = lseq(NCT), U = NCT * ROWS / kFftThreads;
-    cx<T>* b0 = base + size_t(tid / ROWS) * Lh + tid % ROWS;
-    const size_t step = size_t(kFftThreads / ROWS) * Lh;
+    cx<T>* b0 = base + size_t(tid / ROWS) * pitch + tid % ROWS;
+    const size_t step = size_t(kFftThreads / ROWS) * pitch;
     staged_cols<ROWS, kFftThreads, U>(
         NCT, nl, tid, [&](int, int, int u) { return b0[u * step]; },
         [&](int kk, int li, int, cx<T> v) { buf[li * BS + lpos(kk)] = v; });
@@ -113,7 +192,7 @@ __device__ __forceinline__ void cfft_y_body(cx<T>* __restrict__ F, int Lh, int l
         nl * Ny, tid, nthr,
         [&](int q) {
           const int kk = div_nl(q);
-          return base[size_t(kk) * Lh + (q - kk * nl)];
+          return base[size_t(kk) * pitch + (q - kk * nl)];
         },
         [&](int q, cx<T> v) {
           const int kk = div_nl(q);
@@ -131,75 +210,62 @@ __device__ __forceinline__ void cfft_y_body(cx<T>* __restrict__ F, int Lh, int l
         },
         [&](int q, cx<T> v) {
           const int kk = div_nl(q);
-          base[size_t(kk) * Lh + (q - kk * nl)] = v;
+          base[size_t(kk) * pitch + (q - kk * nl)] = v;
         });
   }
 }
 
 template <typename T, bool INV, int NCT>
-__global__ __launch_bounds__(kFftThreads) void k_cfft_y(cx<T>* __restrict__ F, int Lh, int lchunk, FftDesc<T> fd,
-                                                      int wm) {
+__global__ __launch_bounds__(kFftThreads) void k_cfft_y(cx<T>* __restrict__ F, int Lh, int pitch, int lchunk,
+                                                      FftDesc<T> fd, int wm) {
   // neighbouring groups share the 128-byte lines of the z runs: keep them on one XCD
   const int gl = xcd_linear();
-  cfft_y_body<T, INV, NCT>(F, Lh, lchunk, fd, wm, gl % gridDim.x, gl / gridDim.x);
+  cfft_y_body<T, INV, NCT>(F, Lh, pitch, lchunk, fd, wm, gl % gridDim.x, gl / gridDim.x);
 }
 
-template <typename T, int NCT = 0>
-__device__ __forceinline__ void c2r_z_body(const cx<T>* __restrict__ F, long long nrows, int rows,
+// Longer lengths: passes in LDS, runtime plan. Two real rows share one complex
+// transform as above.
+template <typename T>
+__device__ __forceinline__ void c2r_z_body(const cx<T>* __restrict__ F, long long nrows, int pitch, int rows,
                                            FftDesc<T> fd, T* __restrict__ f, int wm, int bx, int tid = threadIdx.x) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   const int nthr = blockDim.x;
-  const int Nz = NCT > 0 ? NCT : fd.n;
-  const int Lh = Nz / 2 + 1;
+  const int Nz = fd.n;
+  const int Lz = Nz / 2;
   const int bstride = lseq(Nz);
   const long long r0 = (long long)bx * rows;
   const int nr = (int)min((long long)rows, nrows - r0);
-  // two real rows per complex transform: Z = X0 + i X1 (each Hermitian-
-  // extended) transforms to x0 + i x1. The DC and Nyquist bins keep their
-  // real parts only, as the real part of a single row's transform would.
   const int np = (nr + 1) / 2;
-  const FastDiv fdiv_lh(Lh), fdiv_nz(Nz);
-  // compile-time lengths divide by constants (a shift for Nz)
-  auto div_lh = [&](int q) { return NCT > 0 ? int(unsigned(q) / unsigned(NCT / 2 + 1)) : fdiv_lh(q); };
-  auto div_nz = [&](int q) { return NCT > 0 ? int(unsigned(q) / unsigned(NCT > 0 ? NCT : 1)) : fdiv_nz(q); };
+  const FastDiv div_lz(Lz), div_nz(Nz);
   struct Two {
     cx<T> a, c;
   };
-  // values staged per thread: what the pairs of a compile-time length need
-  // (5 at 256 points), else kC2rStage; kFftMaxV held 64 registers for the
-  // pairs (launches check np * Lh <= kC2rStage * threads)
-  constexpr int UL = NCT > 0 ? ((ct_maxb(NCT, kInvCap) + 1) / 2 * (NCT / 2 + 1) + kFftThreads - 1) / kFftThreads
-                             : kC2rStage;
-  staged_copy<UL>(
-      np * Lh, tid, nthr,
+  // kC2rStage pairs staged per thread (launches check np * (Nz/2 + 1) <= kC2rStage * threads)
+  staged_copy<kC2rStage>(
+      np * Lz, tid, nthr,
       [&](int q) {
-        const int s = div_lh(q);
-        const long long at = (r0 + 2 * s) * Lh + (q - s * Lh);
-        return Two{F[at], 2 * s + 1 < nr ? F[at + Lh] : cx<T>{T(0), T(0)}};
+        const int s = div_lz(q);
+        const long long at = (r0 + 2 * s) * pitch + (q - s * Lz);
+        return Two{F[at], 2 * s + 1 < nr ? F[at + pitch] : cx<T>{T(0), T(0)}};
       },
       [&](int q, Two v) {
-        const int s = div_lh(q);
-        const int l = q - s * Lh;
+        const int s = div_lz(q);
+        const int l = q - s * Lz;
         cx<T>* row = buf + s * bstride;
-        if (l == 0 || l == Nz / 2) {
-          row[lpos(l)] = cx<T>{v.a.x, v.c.x};
+        if (l == 0) {
+          row[lpos(0)] = cx<T>{v.a.x, v.c.x};
+          row[lpos(Lz)] = cx<T>{T(0), T(0)};
         } else {
           row[lpos(l)] = cx<T>{v.a.x - v.c.y, v.a.y + v.c.x};
           row[lpos(Nz - l)] = cx<T>{v.a.x + v.c.y, v.c.x - v.a.y};
         }
       });
-  // the sequences hold (rows + 1) / 2 pairs: the twiddles go behind them,
-  // and the transform is compiled for that many (with LDS and registers for
-  // `rows` sequences, half unused, the kernel held 100 registers and 37 KiB
-  // of LDS per work-group at 256 points: 4 per CU)
+  // the sequences hold (rows + 1) / 2 pairs: the twiddles go behind them
   cx<T>* twl = buf + (rows + 1) / 2 * bstride;
-  for (int t = tid; t < (NCT > 0 ? NCT : fd.n); t += nthr) twl[t] = fd.tw[t];
+  for (int t = tid; t < fd.n; t += nthr) twl[t] = fd.tw[t];
   __syncthreads();
-  if constexpr (NCT > 0)
-    fft_ct<T, NCT, kFftThreads, (ct_maxb(NCT, kInvCap) + 1) / 2, true>(buf, np, twl, tid);
-  else
-    fft_group<T, true>(buf, lds_twiddles(fd, twl), np, bstride, tid, nthr, wm);
+  fft_group<T, true>(buf, lds_twiddles(fd, twl), np, bstride, tid, nthr, wm);
   __syncthreads();
   staged_copy<kFftMaxV>(
       nr * Nz, tid, nthr,
@@ -211,13 +277,13 @@ __device__ __forceinline__ void c2r_z_body(const cx<T>* __restrict__ F, long lon
       [&](int q, T v) { f[r0 * Nz + q] = v; });
 }
 
-template <typename T, int NCT>
-__global__ __launch_bounds__(kFftThreads) void k_c2r_z(const cx<T>* __restrict__ F, long long nrows, int rows,
-                                                     FftDesc<T> fd, T* __restrict__ f, int wm) {
-  c2r_z_body<T, NCT>(F, nrows, rows, fd, f, wm, blockIdx.x);
+template <typename T>
+__global__ __launch_bounds__(kFftThreads) void k_c2r_z(const cx<T>* __restrict__ F, long long nrows, int pitch,
+                                                     int rows, FftDesc<T> fd, T* __restrict__ f, int wm) {
+  c2r_z_body<T>(F, nrows, pitch, rows, fd, f, wm, blockIdx.x);
 }
 
-// Transpose of k_c2r_z for the forward model: real rows f[r][e] ->
+// Transpose of the complex-to-real pass for the forward model: real rows f[r][e] ->
 // Dh[r][l] = sum_e f[r][e] exp(-2 pi i l e/Nz), l = 0..Nz/2. Two real rows
 // share one complex transform, Z = FFT(x0 + i x1): X0[l] = (Z[l] + conj
 // Z[-l])/2 and X1[l] = (Z[l] - conj Z[-l])/(2i), so a work-group of `rows`
@@ -280,66 +346,86 @@ __global__ __launch_bounds__(kFftThreads) void k_r2c_z(const T* __restrict__ f, 
       [&](int q, cx<T> v) { D[r0 * Lh + q] = v; });
 }
 
-// In-place transforms of the half spectrum along x and y (INV: e^{+i}).
-template <typename T, bool INV>
-static hipError_t launch_xy(const DevPlan& p, cx<T>* F, bool x_first, hipStream_t s, int first_pass = 0) {
+// Forward model: in-place transforms of the half spectrum along y, then x.
+template <typename T>
+static hipError_t launch_forward_xy(const DevPlan& p, cx<T>* F, hipStream_t s) {
   const int Lh = p.Nz / 2 + 1;
   const FftCfg cfg = inv_cfg();
-  for (int pass = first_pass; pass < 2; ++pass) {
-    const bool along_x = (pass == 0) == x_first;
-    hipError_t e;
-    if (along_x) {
-      const int lc = fft_batch<T>(p.Nx, cfg.threads, cfg.cap);
-      const size_t lds = (size_t(lc) * lseq(p.Nx) + p.Nx) * sizeof(cx<T>);
-      e = ct_pick(CtInverse{}, p.Nx, [&](auto c) {
-        constexpr int NCT = decltype(c)::value;
-        // the compile-time kernels take their geometry from the length
-        if (NCT > 0 && (lc != ct_maxb(NCT, kInvCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
-        const void* kern = reinterpret_cast<const void*>(&k_cfft_x<T, INV, NCT>);
-        hipError_t e2 = allow_lds(kern, lds);
-        if (e2 != hipSuccess) return e2;
-        dim3 grid((Lh + lc - 1) / lc, p.Ny);
-        hipLaunchKernelGGL((k_cfft_x<T, INV, decltype(c)::value>), grid, dim3(cfg.threads), lds, s, F, p.Ny, Lh, lc,
-                           as_desc<T>(p.f_Nx), cfg.wave);
-        return hipGetLastError();
-      });
-    } else {
-      const int lc = fft_batch<T>(p.Ny, cfg.threads, cfg.cap);
-      const size_t lds = (size_t(lc) * lseq(p.Ny) + p.Ny) * sizeof(cx<T>);
-      e = ct_pick(CtInverse{}, p.Ny, [&](auto c) {
-        constexpr int NCT = decltype(c)::value;
-        if (NCT > 0 && (lc != ct_maxb(NCT, kInvCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
-        const void* kern = reinterpret_cast<const void*>(&k_cfft_y<T, INV, NCT>);
-        hipError_t e2 = allow_lds(kern, lds);
-        if (e2 != hipSuccess) return e2;
-        dim3 grid((Lh + lc - 1) / lc, p.Nx);
-        hipLaunchKernelGGL((k_cfft_y<T, INV, decltype(c)::value>), grid, dim3(cfg.threads), lds, s, F, Lh, lc,
-                           as_desc<T>(p.f_Ny), cfg.wave);
-        return hipGetLastError();
-      });
-    }
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  const int ly = fft_batch<T>(p.Ny, cfg.threads, cfg.cap);
+  const size_t lds_y = (size_t(ly) * lseq(p.Ny) + p.Ny) * sizeof(cx<T>);
+  hipError_t e = ct_pick(CtInverse{}, p.Ny, [&](auto c) {
+    constexpr int NCT = decltype(c)::value;
+    // the compile-time kernels take their geometry from the length
+    if (NCT > 0 && (ly != ct_maxb(NCT, kInvCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
+    hipError_t e2 = allow_lds(reinterpret_cast<const void*>(&k_cfft_y<T, false, NCT>), lds_y);
+    if (e2 != hipSuccess) return e2;
+    hipLaunchKernelGGL((k_cfft_y<T, false, NCT>), dim3((Lh + ly - 1) / ly, p.Nx), dim3(cfg.threads), lds_y, s, F, Lh,
+                       Lh, ly, as_desc<T>(p.f_Ny), cfg.wave);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  const int lx = fft_batch<T>(p.Nx, cfg.threads, cfg.cap);
+  const size_t lds_x = (size_t(lx) * lseq(p.Nx) + p.Nx) * sizeof(cx<T>);
+  return ct_pick(CtInverse{}, p.Nx, [&](auto c) {
+    constexpr int NCT = decltype(c)::value;
+    if (NCT > 0 && (lx != ct_maxb(NCT, kInvCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
+    hipError_t e2 = allow_lds(reinterpret_cast<const void*>(&k_cfft_x<T, false, NCT>), lds_x);
+    if (e2 != hipSuccess) return e2;
+    hipLaunchKernelGGL((k_cfft_x<T, false, NCT>), dim3((Lh + lx - 1) / lx, p.Ny), dim3(cfg.threads), lds_x, s, F,
+                       p.Ny, Lh, lx, as_desc<T>(p.f_Nx), cfg.wave);
+    return hipGetLastError();
+  });
 }
 
 template <typename T>
-hipError_t launch_inverse(const DevPlan& p, void* Fh, T* f, hipStream_t s, bool x_done) {
+hipError_t launch_inverse(const DevPlan& p, void* Fh, T* f, hipStream_t s) {
   cx<T>* F = static_cast<cx<T>*>(Fh);
-  hipError_t e = launch_xy<T, true>(p, F, true, s, x_done ? 1 : 0);
-  if (e != hipSuccess) return e;
+  const int Lz = p.Nz / 2;
   const FftCfg cfg = inv_cfg();
+  hipError_t e;
+  const int ly = fft_seqs<T>(p.f_Ny, p.f_Ny.two.r1 ? kInvYThreads : cfg.threads, cfg.cap);
+  const dim3 gy((Lz + ly - 1) / ly, p.Nx);
+  if (p.f_Ny.two.r1) {
+    const Fft2Raw t = fft2_shape<T>(p.f_Ny, ly);
+    const size_t lds = fft2_slots(t) * sizeof(cx<T>);
+    e = class_pick(t, [&](auto c) {
+      constexpr auto kern = &k_cfft_y_reg<T, decltype(c)::value>;
+      hipError_t e2 = allow_lds(reinterpret_cast<const void*>(kern), lds);
+      if (e2 != hipSuccess) return e2;
+      hipLaunchKernelGGL(kern, gy, dim3(fft2_threads(t)), lds, s, F, Lz, p.pitch_f, t);
+      return hipGetLastError();
+    });
+  } else {
+    const size_t lds = (size_t(ly) * lseq(p.Ny) + p.Ny) * sizeof(cx<T>);
+    e = allow_lds(reinterpret_cast<const void*>(&k_cfft_y<T, true, 0>), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_cfft_y<T, true, 0>), gy, dim3(cfg.threads), lds, s, F, Lz, p.pitch_f, ly,
+                       as_desc<T>(p.f_Ny), cfg.wave);
+    e = hipGetLastError();
+  }
+  if (e != hipSuccess) return e;
+  const long long nrows = (long long)p.Nx * p.Ny;
+  if (p.f_Nz.two.r1) {
+    const Fft2Raw t = fft2_shape<T>(p.f_Nz, fft_seqs<T>(p.f_Nz, cfg.threads, kC2rSeqs));
+    const size_t lds = fft2_slots(t) * sizeof(cx<T>);
+    const long long rows = 2LL << t.ls;
+    return class_pick(t, [&](auto c) {
+      constexpr auto kern = &k_c2r_reg<T, decltype(c)::value>;
+      hipError_t e2 = allow_lds(reinterpret_cast<const void*>(kern), lds);
+      if (e2 != hipSuccess) return e2;
+      hipLaunchKernelGGL(kern, dim3((unsigned)((nrows + rows - 1) / rows)), dim3(fft2_threads(t)), lds, s, F, nrows,
+                         p.pitch_f, t, f);
+      return hipGetLastError();
+    });
+  }
   const int rows = fft_batch<T>(p.Nz, cfg.threads, cfg.cap);
   const size_t lds = size_t(c2r_lds_slots(rows, p.Nz)) * sizeof(cx<T>);
-  const long long nrows = (long long)p.Nx * p.Ny;
   if ((rows + 1) / 2 * (p.Nz / 2 + 1) > kC2rStage * cfg.threads) return hipErrorInvalidValue;
-  return ct_pick(CtInverse{}, p.Nz, [&](auto c) {
-    hipError_t e2 = allow_lds(reinterpret_cast<const void*>(&k_c2r_z<T, decltype(c)::value>), lds);
-    if (e2 != hipSuccess) return e2;
-    hipLaunchKernelGGL((k_c2r_z<T, decltype(c)::value>), dim3((unsigned)((nrows + rows - 1) / rows)),
-                       dim3(cfg.threads), lds, s, F, nrows, rows, as_desc<T>(p.f_Nz), f, cfg.wave);
-    return hipGetLastError();
-  });
+  e = allow_lds(reinterpret_cast<const void*>(&k_c2r_z<T>), lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_c2r_z<T>, dim3((unsigned)((nrows + rows - 1) / rows)), dim3(cfg.threads), lds, s, F, nrows,
+                     p.pitch_f, rows, as_desc<T>(p.f_Nz), f, cfg.wave);
+  return hipGetLastError();
 }
 
 template <typename T>
@@ -359,15 +445,15 @@ hipError_t launch_forward3d(const DevPlan& p, const T* f, void* Dh, hipStream_t 
     return hipGetLastError();
   });
   if (e != hipSuccess) return e;
-  return launch_xy<T, false>(p, D, false, s);
+  return launch_forward_xy<T>(p, D, s);
 }
 
 
-// Batched forms of the inverse passes.
-template <typename T>
-__global__ __launch_bounds__(kFftThreads) void k_cfft_y_inv_batch(const CfftBA* __restrict__ args,
-                                                                  const int* __restrict__ prefix, int total,
-                                                                  BatchIO io) {
+// Batched forms of the inverse passes (one variant of problems per launch, as
+// the lateral passes).
+template <typename T, int CLS>
+__global__ __launch_bounds__(kInvYThreads, (any_waves<T, CLS>())) void k_cfft_y_inv_batch(
+    const CfftBA* __restrict__ args, const int* __restrict__ prefix, int total, BatchIO io) {
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
     if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
@@ -375,47 +461,58 @@ __global__ __launch_bounds__(kFftThreads) void k_cfft_y_inv_batch(const CfftBA* 
     const CfftBA a = args[p];
     const int local = w - prefix[p];
     const int by = local / a.gx;
-    cfft_y_body<T, true>(static_cast<cx<T>*>(a.F), a.Lh, a.lchunk, view_desc<T>(a.fd), 0, local - by * a.gx, by,
-                         loop_lane());
+    if constexpr (CLS > 0)
+      cfft_y_reg_body<T, CLS>(static_cast<cx<T>*>(a.F), a.Lz, a.pitch, as_fft2<T>(a.f2), local - by * a.gx, by,
+                              loop_lane());
+    else
+      cfft_y_body<T, true>(static_cast<cx<T>*>(a.F), a.Lz, a.pitch, a.lchunk, view_desc<T>(a.fd), 0,
+                           local - by * a.gx, by, loop_lane());
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kFftThreads) void k_c2r_z_batch(const C2rBA* __restrict__ args,
-                                                             const int* __restrict__ prefix, int total,
-                                                             BatchIO io) {
+template <typename T, int CLS>
+__global__ __launch_bounds__(kFftThreads, (any_waves<T, CLS>())) void k_c2r_z_batch(const C2rBA* __restrict__ args,
+                                                                                   const int* __restrict__ prefix,
+                                                                                   int total, BatchIO io) {
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
     if (slot != int(blockIdx.x)) __syncthreads();  // the previous item's LDS is done with
     const int w = batch_item(slot, total);
     const int p = batch_locate(prefix, w);
     const C2rBA a = args[p];
-    c2r_z_body<T>(static_cast<const cx<T>*>(a.F), a.nrows, a.rows, view_desc<T>(a.fd), static_cast<T*>(io.out[p]), 0,
-                  w - prefix[p]);  // (a re-read lane index raised its registers here)
+    T* out = static_cast<T*>(io.out[a.problem]);
+    if constexpr (CLS > 0)
+      c2r_reg_body<T, CLS>(static_cast<const cx<T>*>(a.F), a.nrows, a.pitch, as_fft2<T>(a.f2), out, w - prefix[p],
+                           loop_lane());
+    else
+      c2r_z_body<T>(static_cast<const cx<T>*>(a.F), a.nrows, a.pitch, a.rows, view_desc<T>(a.fd), out, 0,
+                    w - prefix[p]);
   }
 }
 
 template <typename T>
 hipError_t launch_cfft_y_inv_batch(const BatchStage& st, const BatchIO& io, hipStream_t s) {
   if (st.total <= 0) return hipSuccess;
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_cfft_y_inv_batch<T>), st.lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_cfft_y_inv_batch<T>), dim3(batch_grid(st)), dim3(kFftThreads), st.lds, s,
-                     static_cast<const CfftBA*>(st.args), st.prefix, st.total, io);
-  return hipGetLastError();
+  switch (st.variant) {
+    case 16: return launch_batch_kernel<CfftBA>(&k_cfft_y_inv_batch<T, 16>, st, io, s);
+    case 20: return launch_batch_kernel<CfftBA>(&k_cfft_y_inv_batch<T, 20>, st, io, s);
+    case 32: return launch_batch_kernel<CfftBA>(&k_cfft_y_inv_batch<T, 32>, st, io, s);
+    default: return launch_batch_kernel<CfftBA>(&k_cfft_y_inv_batch<T, 0>, st, io, s);
+  }
 }
 
 template <typename T>
 hipError_t launch_c2r_z_batch(const BatchStage& st, const BatchIO& io, hipStream_t s) {
   if (st.total <= 0) return hipSuccess;
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_c2r_z_batch<T>), st.lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_c2r_z_batch<T>), dim3(batch_grid(st)), dim3(kFftThreads), st.lds, s,
-                     static_cast<const C2rBA*>(st.args), st.prefix, st.total, io);
-  return hipGetLastError();
+  switch (st.variant) {
+    case 16: return launch_batch_kernel<C2rBA>(&k_c2r_z_batch<T, 16>, st, io, s);
+    case 20: return launch_batch_kernel<C2rBA>(&k_c2r_z_batch<T, 20>, st, io, s);
+    case 32: return launch_batch_kernel<C2rBA>(&k_c2r_z_batch<T, 32>, st, io, s);
+    default: return launch_batch_kernel<C2rBA>(&k_c2r_z_batch<T, 0>, st, io, s);
+  }
 }
 
 #define PATK_INST(T)                                                                \
-  template hipError_t launch_inverse<T>(const DevPlan&, void*, T*, hipStream_t, bool); \
+  template hipError_t launch_inverse<T>(const DevPlan&, void*, T*, hipStream_t); \
   template hipError_t launch_forward3d<T>(const DevPlan&, const T*, void*, hipStream_t); \
   template hipError_t launch_cfft_y_inv_batch<T>(const BatchStage&, const BatchIO&, hipStream_t); \
   template hipError_t launch_c2r_z_batch<T>(const BatchStage&, const BatchIO&, hipStream_t);

@@ -52,6 +52,7 @@ struct DevPlan {
   // row pitches (elements) of the reconstruction's intermediate arrays: grid
   // rows U, x-transformed rows V, lateral spectra Gh, band values Gt
   int pitch_u = 0, pitch_v = 0, pitch_g = 0, pitch_t = 0;
+  int pitch_f = 0;             // z modes' rows of the x-transformed spectrum F
   double s_per_k = 0.0;        // c*dt*n_t/(2 pi): oversampled bin per unit |K|
   double kxu = 0, kyu = 0, kzu = 0;  // 2 pi/X, 2 pi/Y, 2 pi/Z
   double two_c = 0.0;          // 2c of W(K) = 2c|Kz|/|K|
@@ -133,12 +134,15 @@ enum { GATHER_IMAGE = 0, GATHER_PHYSICAL = 1, GATHER_ADJOINT = 2 };
 template <typename T>
 hipError_t launch_gather(const DevPlan& p, const void* Gh, void* Fh, int mode, hipStream_t s);
 template <typename T>
-hipError_t launch_inverse(const DevPlan& p, void* Fh, T* f, hipStream_t s, bool x_done = false);
+hipError_t launch_inverse(const DevPlan& p, void* F, T* f, hipStream_t s);
 // Gather (GATHER_IMAGE or GATHER_ADJOINT) fused with the inverse transform
-// along x: leaves what launch_gather + the x pass of launch_inverse would;
-// finish with launch_inverse(..., x_done = true).
+// along x into F[jj][kk][l], l < Nz/2 (rows of pitch_f); launch_inverse
+// finishes along y and z.
 template <typename T>
 hipError_t launch_gather_x(const DevPlan& p, const void* Gh, void* F, int mode, hipStream_t s);
+
+template <typename T>
+void gather_shape(const DevPlan& p, int& lchunk, Fft2Raw& f2, size_t& slots);
 
 // Forward model. f -> Dh (real-to-complex along z, forward FFTs along y, x)
 template <typename T>
@@ -216,13 +220,14 @@ struct GatherBA {  // the gather fused with the inverse transform along x
   const void* Gh; const void* hcoef; int nb, b_lo, Nx, Ny, Nz, wt, deg;
   int wt_ct, pitch_g;  // compile-time tap count to run (kBatchTaps member equal to wt, else 0: runtime taps)
   double s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale; void* Fh;
-  FftView fd; int lchunk, gx;  // x transform (length Nx), z modes per group, groups along z
+  FftView fd; Fft2Raw f2; int lchunk, gx, pitch_f, pad;  // x transform (length Nx), z modes per group, groups along z
 };
 struct CfftBA {
-  void* F; FftView fd; int Ny, Lh, lchunk, gx;  // Ny is used by the x pass only
+  void* F; FftView fd; Fft2Raw f2; int Lz, pitch, lchunk, gx;
 };
 struct C2rBA {
-  const void* F; FftView fd; long long nrows; int rows;
+  const void* F; FftView fd; Fft2Raw f2; long long nrows; int rows, pitch;
+  int problem, pad;  // index into BatchIO
 };
 
 // One stage of a batched call: its argument table (one entry per problem),

@@ -31,12 +31,14 @@ static inline int fft_batch(int n, int nthr, int cap) {
 
 // Sequences per work-group of an FFT stage: a power of two for lengths with a
 // two-pass register transform (one butterfly per thread, so at most
-// nthr / the larger radix of them), else fft_batch.
+// nthr / the larger radix of them, within 80 KiB of LDS so that two work-groups
+// share a CU), else fft_batch.
 template <typename T>
 static inline int fft_seqs(const FftRaw& f, int nthr, int cap) {
   if (!f.two.r1) return fft_batch<T>(f.n, nthr, cap);
   int s = 1;
-  while (2 * s <= cap && 2 * s * reg_larger(f.two) <= nthr) s *= 2;
+  const size_t seq = size_t(f.two.r1) * (f.two.r2 | 1) * 2 * sizeof(T);
+  while (2 * s <= cap && 2 * s * reg_larger(f.two) <= nthr && 2 * s * seq <= 81920) s *= 2;
   return s;
 }
 
@@ -229,6 +231,13 @@ __host__ __device__ constexpr int c2r_lds_slots(int rows, int n) { return (rows 
 // stay within 8 * 256 for every n <= 2048 (at most 1366; 1032 at n = 256)
 constexpr int kC2rStage = 8;
 
+// most threads of the inverse y pass: its work-groups take 16 z modes, whole
+// 128-byte lines, also where that needs more than 256 butterflies (320 points:
+// 58 us, 69 us with 8 modes)
+constexpr int kInvYThreads = 512;
+// pairs of rows per work-group of the two-pass complex-to-real z pass
+constexpr int kC2rSeqs = 8;
+
 // LDS slots of one temporal work-group (a sensor pair): the sequence, then
 // the split twiddle tables (single-problem and batched launches).
 __host__ __device__ constexpr int temporal_lds_slots(int n_t) { return lseq(n_t) + tw_split_slots(n_t); }
@@ -260,6 +269,15 @@ __device__ __forceinline__ int batch_item(int L, int total) {
 // striding over the items.
 static inline unsigned batch_grid(const BatchStage& st) {
   return unsigned(st.grid > 0 && st.grid < st.total ? st.grid : st.total);
+}
+
+template <typename A, typename K>
+static inline hipError_t launch_batch_kernel(K kern, const BatchStage& st, const BatchIO& io, hipStream_t s) {
+  hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), st.lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(batch_grid(st)), dim3(st.threads), st.lds, s, static_cast<const A*>(st.args),
+                     st.prefix, st.total, io);
+  return hipGetLastError();
 }
 
 }  // namespace patk

@@ -510,10 +510,7 @@ hipError_t launch_fft_x_t(const DevPlan& p, const void* V, void* U, int b_begin,
 // variant, CLS the class of their two-pass transforms or 0 for the longer
 // lengths.
 template <typename T, int CLS>
-constexpr int batch_waves() { return CLS > 0 ? reg_waves<T, CLS ? CLS : 16>() : 1; }
-
-template <typename T, int CLS>
-__global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_x_batch(const FftXBA* __restrict__ args,
+__global__ __launch_bounds__(kFftThreads, (any_waves<T, CLS>())) void k_fft_x_batch(const FftXBA* __restrict__ args,
                                                              const int* __restrict__ prefix, int total,
                                                              BatchIO io) {
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
@@ -533,7 +530,7 @@ __global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_x_
 }
 
 template <typename T, int CLS>
-__global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_y_batch(const FftYBA* __restrict__ args,
+__global__ __launch_bounds__(kFftThreads, (any_waves<T, CLS>())) void k_fft_y_batch(const FftYBA* __restrict__ args,
                                                              const int* __restrict__ prefix, int total,
                                                              BatchIO io) {
   for (int slot = blockIdx.x; slot < total; slot += gridDim.x) {
@@ -557,15 +554,6 @@ __global__ __launch_bounds__(kFftThreads, (batch_waves<T, CLS>())) void k_fft_y_
                     static_cast<const T*>(a.dcy), view_desc<T>(a.fd), static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
                     loop_lane());
   }
-}
-
-template <typename A, typename K>
-static hipError_t launch_batch_kernel(K kern, const BatchStage& st, const BatchIO& io, hipStream_t s) {
-  hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), st.lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(batch_grid(st)), dim3(st.threads), st.lds, s, static_cast<const A*>(st.args),
-                     st.prefix, st.total, io);
-  return hipGetLastError();
 }
 
 template <typename T>

@@ -55,10 +55,10 @@ def _pairs():
     return out
 
 
-def _problem(nx_over, ny_over, sigma):
+def _problem(nx_over, ny_over, sigma, nz=4):
     rng = np.random.default_rng(nx_over * 1000 + ny_over)
-    shape = (round(nx_over / sigma), round(ny_over / sigma), 4)
-    ext = (shape[0] * 0.25e-3, shape[1] * 0.25e-3, 2e-3)
+    shape = (round(nx_over / sigma), round(ny_over / sigma), nz)
+    ext = (shape[0] * 0.25e-3, shape[1] * 0.25e-3, max(2e-3, nz * 0.25e-3))
     return inputs.random_problem(rng, 37, 45, shape, ext, dt=30e-9)
 
 
@@ -80,10 +80,29 @@ def test_lengths_vs_oracle(dev, nx_over, ny_over, sigma):
         assert err <= max(tol, 8 * np.exp(-np.pi * 8 * np.sqrt(1 - 1 / sigma)))
 
 
+@pytest.mark.parametrize("nx,ny,nz", [(4, 6, 640), (6, 4, 576), (10, 8, 486), (8, 12, 384), (640, 4, 16), (4, 640, 36),
+                                      (486, 6, 250), (6, 500, 8), (720, 4, 6), (4, 720, 10), (6, 8, 720), (288, 18, 90),
+                                      (18, 288, 162), (320, 20, 288), (20, 320, 400), (54, 50, 54)])
+def test_image_lengths_vs_oracle(dev, nx, ny, nz):
+    """The image's own transforms (gather's x pass, y pass, complex-to-real z
+    pass): each class of lengths per axis, z runs that are no multiple of a
+    group's 8 or 16 modes, the longest and the first past the range."""
+    from paper_1510_01078_amd import Plan
+    p = _problem(2 * nx, 2 * ny, 2.0, nz)
+    ref = oracle.reconstruct(p.xy, p.h, p.g, p.dt, p.c, p.shape, p.extent)
+    for precision, tol in (("fp32", 1e-5), ("fp64", 1e-6)):
+        pl = Plan(p.xy, p.nt, p.dt, p.c, p.shape, p.extent, sensor_h=p.h, precision=precision, **_kw(2.0))
+        err = rel_l2(pl.reconstruct(torch.from_numpy(p.g).to(dev, pl.dtype)).cpu().numpy().astype(np.float64), ref)
+        pl.close()
+        _say(f"[gpu] image {nx} x {ny} x {nz} {precision}: {err:.2e}")
+        assert err <= tol
+
+
 def test_batch_of_all_classes_equals_single(dev):
     from paper_1510_01078_amd import Plan
     from paper_1510_01078_amd.batch import Batch, problem_dict
-    probs = [_problem(n, m, 2.0) for n, m in ((64, 96), (256, 40), (320, 60), (40, 384), (480, 512), (640, 20), (720, 64))]
+    probs = [_problem(n, m, 2.0, z) for n, m, z in ((64, 96, 54), (256, 40, 288), (320, 60, 400), (40, 384, 4),
+                                                    (480, 512, 6), (640, 20, 720), (720, 64, 90), (1152, 12, 8))]
     b = Batch([problem_dict(p) for p in probs], precision="fp32", defaults=_kw(2.0))
     gs = [torch.from_numpy(p.g).to(dev, torch.float32) for p in probs]
     outs = b.reconstruct(gs)
