@@ -82,6 +82,38 @@ void two_pass_plan(int n, patk::Fft2Raw& f) {
   }
 }
 
+// Radices of the temporal FFT's register form: two passes where two_pass_plan
+// has them, else r1 <= r2 <= r3 with the smallest r3 (it sets the registers),
+// then the largest r1 (fewest threads). The smallest radix goes first, where a
+// butterfly holds its samples' loads and twiddles beside its values (84 us for
+// 16384 sensors at 2560 = 10 16 16, 99 us in any order that starts with 16).
+// Every even 2,3,5-smooth length up to 8192 has three but 6250 = 10 25 25,
+// whose first pass would take 625 butterflies.
+void three_pass_plan(int n, const patk::Fft2Raw& two, patk::Fft3Raw& f) {
+  f = patk::Fft3Raw{0, 0, 0, 0, 0, 0, 0, 0, nullptr, nullptr};
+  if (two.r1) {
+    f.r1 = two.r1;
+    f.r2 = two.r2;
+    f.r3 = 1;
+    return;
+  }
+  for (int r3 : {9, 10, 12, 15, 16, 18, 20, 24, 25, 27, 32}) {
+    if (n % r3) continue;
+    for (int r1 : {20, 18, 16, 15, 12, 10, 9, 8, 5}) {
+      if (r1 > r3 || (n / r3) % r1) continue;
+      const int r2 = n / r3 / r1;
+      if (r2 < r1 || r2 > r3 || n / r1 > 512) continue;
+      for (int r : {8, 9, 10, 12, 15, 16, 18, 20})
+        if (r2 == r) {
+          f.r1 = r1;
+          f.r2 = r2;
+          f.r3 = r3;
+          return;
+        }
+    }
+  }
+}
+
 struct HostBlob {
   std::vector<unsigned char> bytes;
   size_t add(const void* src, size_t n) {
@@ -109,15 +141,15 @@ size_t add_twiddles(HostBlob& b, int n) {
   return b.add(t.data(), t.size() * sizeof(T));
 }
 
-// tw[k*r2 + i] = exp(-2 pi i ik/n) of the two-pass transform
+// tw[k*cols + i] = exp(-2 pi i ik/n), k < rows, of the register transforms
 template <typename T>
-size_t add_twiddles2(HostBlob& b, int n, const patk::Fft2Raw& f) {
-  std::vector<T> t(2 * size_t(f.r1) * f.r2);
-  for (int k = 0; k < f.r1; ++k)
-    for (int i = 0; i < f.r2; ++i) {
+size_t add_twiddles2(HostBlob& b, int n, int rows, int cols) {
+  std::vector<T> t(2 * size_t(rows) * cols);
+  for (int k = 0; k < rows; ++k)
+    for (int i = 0; i < cols; ++i) {
       const double a = -2.0 * M_PI * double(i * k % n) / double(n);
-      t[2 * (size_t(k) * f.r2 + i)] = T(std::cos(a));
-      t[2 * (size_t(k) * f.r2 + i) + 1] = T(std::sin(a));
+      t[2 * (size_t(k) * cols + i)] = T(std::cos(a));
+      t[2 * (size_t(k) * cols + i) + 1] = T(std::sin(a));
     }
   return b.add(t.data(), t.size() * sizeof(T));
 }
@@ -486,6 +518,10 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   }
   const size_t o_br = blob.add(br.data(), br.size() * sizeof(int));
   // twiddles
+  three_pass_plan(dp.n_t, dp.f_nt.two, dp.f_nt3);
+  const patk::Fft3Raw& f3 = dp.f_nt3;
+  const size_t o_twA = add_twiddles2<T>(blob, dp.n_t, f3.r1, f3.r2 * f3.r3);
+  const size_t o_twB = add_twiddles2<T>(blob, f3.r2 * f3.r3, f3.r3 > 1 ? f3.r2 : 0, f3.r3);
   const size_t o_tw_nt = add_twiddles<T>(blob, dp.n_t);
   const size_t o_tw_nx = add_twiddles<T>(blob, dp.n_x);
   const size_t o_tw_ny = add_twiddles<T>(blob, dp.n_y);
@@ -494,7 +530,7 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   const size_t o_tw_Nz = add_twiddles<T>(blob, d.nz);
   patk::FftRaw* ffts[6] = {&dp.f_nt, &dp.f_nx, &dp.f_ny, &dp.f_Nx, &dp.f_Ny, &dp.f_Nz};
   size_t o_pass[6], o_tw2[6];
-  for (int i = 0; i < 6; ++i) o_tw2[i] = add_twiddles2<T>(blob, ffts[i]->n, ffts[i]->two);
+  for (int i = 0; i < 6; ++i) o_tw2[i] = add_twiddles2<T>(blob, ffts[i]->n, ffts[i]->two.r1, ffts[i]->two.r2);
   for (int i = 0; i < 6; ++i) o_pass[i] = blob.add(ffts[i]->pass, sizeof(patk::FftPassRaw) * ffts[i]->npass);
 
   P->dev_bytes = align_up(blob.bytes.size());
@@ -526,6 +562,8 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   dp.ylist_n = int(yl.size());
   dp.brange = static_cast<const int*>(at(o_br));
   dp.f_nt.tw = at(o_tw_nt);
+  dp.f_nt3.twA = at(o_twA);
+  dp.f_nt3.twB = at(o_twB);
   dp.f_nx.tw = at(o_tw_nx);
   dp.f_ny.tw = at(o_tw_ny);
   dp.f_Nx.tw = at(o_tw_Nx);

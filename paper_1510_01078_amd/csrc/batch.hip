@@ -126,10 +126,13 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     off += ra + rb + rc;
     const int Lz = d.Nz / 2;
     if (d.n_t > patk::kFftMaxV * 512) return PAT_ERR_UNSUPPORTED;
-    // stage 0: temporal FFT, one block per sensor pair
-    a0[p] = patk::TemporalBA{d.hw, d.deap, patk::as_view(d.f_nt), d.M, d.Nt, d.n0, d.b_lo, d.nb, d.pitch_t, C};
-    pre[0][p] = (d.M + 1) / 2;
-    lds[0][p] = size_t(patk::temporal_lds_slots(d.n_t)) * c;
+    // stage 0: temporal FFT, a block per sensor pair or a few
+    const patk::Fft3Raw f0 = patk::temporal_shape<T>(d);
+    a0[p] = patk::TemporalBA{d.hw, d.deap, patk::as_view(d.f_nt), f0, d.M, d.Nt, d.n0, d.b_lo, d.nb, d.pitch_t, C, p, 0};
+    pre[0][p] = ((d.M + 1) / 2 + (1 << f0.ls) - 1) >> f0.ls;
+    lds[0][p] = (f0.r1 ? size_t(f0.P) << f0.ls : size_t(patk::temporal_lds_slots(d.n_t))) * c;
+    variant[0][p] = f0.r1 ? patk::three_class(f0) + 64 * (f0.r3 == 1 ? 1 : patk::fft3_rounds(f0) ? 2 : 0) : 0;
+    threads[0][p] = f0.r1 ? patk::fft3_threads(f0) : 512;
     // stage 1: spread, all bins in one round
     const int nchunks = (d.nb + 15) / 16;
     a1[p] = patk::SpreadBA{C,     d.slot_rng, d.slot_sens, d.slot_w,       d.slot_k,          d.nb, d.n_x,

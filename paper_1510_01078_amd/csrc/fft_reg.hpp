@@ -337,6 +337,43 @@ __device__ __forceinline__ void reg_second(const cx<T>* seq, int Q, int k, Store
   for (int q = 0; q < R; ++q) st(q, v[q]);
 }
 
+// Three-pass transform of one length n = r1*r2*r3 (r3 = 1: two passes) for
+// sequences whose whole spectrum ends in LDS in natural order (the temporal
+// FFT): value k1 of sequence s, index i at s*P + k1*QA + i, within it value k2,
+// index i at k1*QA + k2*QB + i; twA[k1*m + i] = w_n^(i k1), m = r2*r3, and
+// twB[k2*r3 + i] = w_m^(i k2).
+template <typename T>
+struct Fft3 {
+  int n, r1, r2, r3;
+  int P, QA, QB;
+  int ls;
+  const cx<T>* twA;
+  const cx<T>* twB;
+};
+
+template <typename T>
+__host__ __device__ __forceinline__ Fft3<T> as_fft3(const Fft3Raw& f) {
+  return Fft3<T>{f.r1 * f.r2 * f.r3, f.r1, f.r2, f.r3, f.P, f.QA, f.QB, f.ls, static_cast<const cx<T>*>(f.twA),
+                 static_cast<const cx<T>*>(f.twB)};
+}
+
+// Pass over values in LDS at src[r*stride], R of them, by the `active`
+// threads; after the barrier value k goes to st(k, v).
+template <typename T, int R, bool INV, typename Store>
+__device__ __forceinline__ void reg_in_lds(const cx<T>* src, int stride, bool active, Store st) {
+  cx<T> v[R];
+  if (active) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = src[r * stride];
+    RDft<T, R, INV>::run(v);
+  }
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) st(r, v[r]);
+  }
+}
+
 // Radix by a uniform switch over those of the class (the host's table of
 // factorisations, two_pass_plan, pairs no others).
 #define PATK_RADICES_16(X) X(2) X(3) X(4) X(5) X(6) X(8) X(9) X(10) X(12) X(15) X(16)
@@ -344,6 +381,70 @@ __device__ __forceinline__ void reg_second(const cx<T>* seq, int Q, int k, Store
 #define PATK_SECOND_20(X) X(16) X(18) X(20)
 #define PATK_FIRST_32(X) X(10) X(16) X(18) X(20)
 #define PATK_SECOND_32(X) X(24) X(25) X(27) X(30) X(32)
+
+// and of the three-pass transforms (three_pass_plan): radices in ascending order
+#define PATK_THREE_A16(X) X(5) X(8) X(9) X(10) X(12) X(15) X(16)
+#define PATK_THREE_B16(X) X(8) X(9) X(10) X(12) X(15) X(16)
+#define PATK_THREE_C16(X) X(9) X(10) X(12) X(15) X(16)
+#define PATK_THREE_A20(X) X(9) X(10) X(12) X(15) X(16) X(18) X(20)
+#define PATK_THREE_C20(X) X(18) X(20)
+#define PATK_THREE_A32(X) X(5) X(9) X(10) X(15) X(16) X(18)
+#define PATK_THREE_B32(X) X(10) X(15) X(16) X(18) X(20)
+#define PATK_THREE_C32(X) X(24) X(25) X(27) X(32)
+
+template <typename T, int CLS, bool INV, typename Load>
+__device__ __forceinline__ void three_first_any(const Fft3<T>& f, cx<T>* seq, int i, Load ld) {
+  const int m = f.r2 * f.r3;
+#define PATK_CASE(R) case R: reg_first<T, R, INV>(seq, m, f.QA, f.twA, i, ld); break;
+  if constexpr (CLS == 16) {
+    switch (f.r1) { PATK_THREE_A16(PATK_CASE) default: break; }
+  } else if constexpr (CLS == 20) {
+    switch (f.r1) { PATK_THREE_A20(PATK_CASE) default: break; }
+  } else {
+    switch (f.r1) { PATK_THREE_A32(PATK_CASE) default: break; }
+  }
+#undef PATK_CASE
+}
+
+template <typename T, int CLS, bool INV, typename Store>
+__device__ __forceinline__ void three_mid_any(const Fft3<T>& f, const cx<T>* src, bool active, Store st) {
+#define PATK_CASE(R) case R: reg_in_lds<T, R, INV>(src, f.r3, active, st); break;
+  if constexpr (CLS == 16) {
+    switch (f.r2) { PATK_THREE_B16(PATK_CASE) default: break; }
+  } else if constexpr (CLS == 20) {
+    switch (f.r2) { PATK_THREE_A20(PATK_CASE) default: break; }
+  } else {
+    switch (f.r2) { PATK_THREE_B32(PATK_CASE) default: break; }
+  }
+#undef PATK_CASE
+}
+
+template <typename T, int CLS, bool INV, typename Store>
+__device__ __forceinline__ void three_last_any(const Fft3<T>& f, const cx<T>* src, bool active, Store st) {
+#define PATK_CASE(R) case R: reg_in_lds<T, R, INV>(src, 1, active, st); break;
+  if constexpr (CLS == 16) {
+    switch (f.r3) { PATK_THREE_C16(PATK_CASE) default: break; }
+  } else if constexpr (CLS == 20) {
+    switch (f.r3) { PATK_THREE_C20(PATK_CASE) default: break; }
+  } else {
+    switch (f.r3) { PATK_THREE_C32(PATK_CASE) default: break; }
+  }
+#undef PATK_CASE
+}
+
+// The last of two passes (r3 = 1) into natural order in LDS.
+template <typename T, int CLS, bool INV, typename Store>
+__device__ __forceinline__ void two_last_any(const Fft3<T>& f, const cx<T>* src, bool active, Store st) {
+#define PATK_CASE(R) case R: reg_in_lds<T, R, INV>(src, 1, active, st); break;
+  if constexpr (CLS == 16) {
+    switch (f.r2) { PATK_RADICES_16(PATK_CASE) default: break; }
+  } else if constexpr (CLS == 20) {
+    switch (f.r2) { PATK_SECOND_20(PATK_CASE) default: break; }
+  } else {
+    switch (f.r2) { PATK_SECOND_32(PATK_CASE) default: break; }
+  }
+#undef PATK_CASE
+}
 
 template <typename T, int CLS, bool INV, typename Load>
 __device__ __forceinline__ void reg_first_any(const Fft2<T>& f, cx<T>* seq, int i, Load ld) {

@@ -32,6 +32,16 @@ struct Fft2Raw {
   const void* tw;  // device, tw[k*r2 + i] = exp(-2 pi i ik/n), k < r1, i < r2
 };
 
+// Three-pass form (fft_reg.hpp) for the temporal FFT: n = r1*r2*r3, r3 = 1 for
+// lengths with two passes, r1 = 0 for none. P, QA, QB and ls are set at launch.
+struct Fft3Raw {
+  int r1, r2, r3;
+  int P, QA, QB, ls;
+  int pad;
+  const void* twA;  // device, [r1][r2*r3]
+  const void* twB;  // device, [r2][r3] (r3 > 1)
+};
+
 struct FftRaw {
   int n = 0;
   int npass = 0;
@@ -86,6 +96,7 @@ struct DevPlan {
   const void* dcy = nullptr;      // [Ny]
   const void* hcoef = nullptr;    // [w_t][hdeg+1] temporal tap polynomials
   FftRaw f_nt, f_nx, f_ny, f_Nx, f_Ny, f_Nz;
+  Fft3Raw f_nt3{0, 0, 0, 0, 0, 0, 0, 0, nullptr, nullptr};  // temporal FFT
 };
 
 constexpr int kSpreadTile = 16;  // spread tile edge (grid points)
@@ -117,6 +128,9 @@ inline int spread_groups(const DevPlan& p, int nchunks) {
 
 // weighted = true: traces scaled by h_m dt (reconstruction); false: unit
 // weights (adjoint of the forward model).
+// Launch shape of the register form (r1 = 0: passes in LDS).
+template <typename T>
+Fft3Raw temporal_shape(const DevPlan& p);
 template <typename T>
 hipError_t launch_temporal(const DevPlan& p, const T* g, void* Gt, bool weighted, hipStream_t s);
 // Bins [b_begin, b_end) of the band: U holds only those bins (U[b - b_begin]),
@@ -202,7 +216,8 @@ struct FftView {  // plain data (it also lives in LDS)
 };
 
 struct TemporalBA {
-  const void* hw; const void* deap; FftView fd; int M, Nt, n0, b_lo, nb, pitch_t; void* Gt;
+  const void* hw; const void* deap; FftView fd; Fft3Raw f3; int M, Nt, n0, b_lo, nb, pitch_t; void* Gt;
+  int problem, pad;  // index into BatchIO
 };
 struct SpreadBA {
   const void* Gt; const int4* slot_rng; const int* slot_sens; const void* slot_w; const unsigned* slot_k;

@@ -68,6 +68,23 @@ static inline Fft2Raw fft2_shape(const FftRaw& f, int S) {
     while (t.P % (2 * U / S) != U / S) ++t.P;
   return t;
 }
+constexpr int three_class(const Fft3Raw& f) {
+  const int r = f.r3 > 1 ? f.r3 : (f.r1 > f.r2 ? f.r1 : f.r2);  // radices ascend in three passes
+  return r <= 16 ? 16 : r <= 20 ? 20 : 32;
+}
+// Threads of a temporal work-group: a butterfly each in every pass, up to 512.
+// Where only the first pass (n / r1 butterflies, it does not work in place)
+// takes more than 256 and its radices are of the larger classes, it runs in
+// two rounds of 256 instead: 3200 points on five waves held 11 of 20 waves per
+// CU (190 us for 22500 sensors, 207 us; at the smaller radices the rounds' own
+// registers cost more).
+static inline bool fft3_rounds(const Fft3Raw& f) {
+  return f.r3 > 1 && three_class(f) > 16 && f.r2 * f.r3 > 256 && f.r1 * f.r3 <= 256;  // r2 <= r3
+}
+static inline int fft3_threads(const Fft3Raw& f) {
+  const int most = f.r3 > 1 ? f.r2 * f.r3 : (f.r1 > f.r2 ? f.r1 : f.r2) << f.ls;  // radices ascend in three passes
+  return fft3_rounds(f) ? 256 : (most + 63) / 64 * 64;
+}
 static inline size_t fft2_slots(const Fft2Raw& t) { return size_t(t.P) << t.ls; }
 static inline int fft2_threads(const Fft2Raw& t) { return ((reg_larger(t) << t.ls) + 63) / 64 * 64; }
 
