@@ -156,7 +156,7 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     if (!fy.r1 && (bins * d.n_y > kFft || bins * d.Ny > kFft)) return PAT_ERR_UNSUPPORTED;
     const int gx3 = (d.nb + bins - 1) / bins;
     const bool listed = d.ylist && d.ylist_n > 0 && d.jrange;
-    a3[p] = patk::FftYBA{Bw, d.dcx, d.dcy, patk::as_view(d.f_ny), fy, d.nb, d.Nx, d.Ny, bins, gx3, d.pitch_v, d.pitch_g, A, d.jrange,
+    a3[p] = patk::FftYBA{Bw, patk::as_view(d.f_ny), fy, d.nb, d.Nx, d.Ny, bins, gx3, d.pitch_v, d.pitch_g, A, d.jrange,
                          listed ? d.ylist : nullptr};
     pre[3][p] = listed ? d.ylist_n : gx3 * d.Nx;
     lds[3][p] = (fy.r1 ? patk::fft2_slots(fy) : size_t(bins) * patk::lseq(d.n_y) + d.n_y) * c;
@@ -172,7 +172,7 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     int wt_ct = 0;
     for (int t : patk::kBatchTaps)
       if (d.w_t == t && d.w_t * (d.hdeg + 1) <= patk::kMaxTapCoefs) wt_ct = t;
-    a4[p] = patk::GatherBA{A, d.hcoef, d.nb, d.b_lo, d.Nx, d.Ny, d.Nz, d.w_t, d.hdeg, wt_ct, d.pitch_g,
+    a4[p] = patk::GatherBA{A, d.hcoef, d.dcx, d.dcy, d.nb, d.b_lo, d.Nx, d.Ny, d.Nz, d.w_t, d.hdeg, wt_ct, d.pitch_g,
                            d.s_per_k, d.kxu, d.kyu, d.kzu, d.two_c, d.n0_over_nt, d.inv_vol, Bw,
                            patk::as_view(d.f_Nx), f4, lcx, gx5, d.pitch_f, 0};
     pre[4][p] = gx5 * d.Ny;

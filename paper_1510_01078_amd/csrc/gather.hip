@@ -112,13 +112,15 @@ enum { MODE_IMAGE = 0, MODE_PHYSICAL = 1, MODE_ADJOINT = 2 };
 // WT > 0: compile-time tap count with the coefficients staged in LDS at
 // `coefs` (stage_tap_coefs, before the call); WT = 0: runtime wt, coefficients
 // read from hcoef.
-// One spectrum value F(jj, kk, l) of the given mode.
+// One spectrum value F(jj, kk, l) of the given mode; deconv = 1/(phihat_x
+// phihat_y) of the column (even in j and k, so it holds for both terms of
+// MODE_ADJOINT).
 template <typename T, int MODE, int WT = 0>
 __device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
                                               double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                               double n0_over_nt, double scale, int wt, int deg,
                                               const T* __restrict__ hcoef, int jj, int kk, int l,
-                                              const T* coefs) {
+                                              double deconv, const T* coefs) {
   const bool zero_l = MODE == MODE_ADJOINT ? (l == Nz / 2) : (l == 0 || l == Nz / 2);
   if (zero_l || jj == Nx / 2 || kk == Ny / 2) return cx<T>{T(0), T(0)};
   const long long col = (long long)jj * Ny + kk;
@@ -164,11 +166,12 @@ __device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int 
     }
   }
   if (MODE == MODE_ADJOINT) {
-    const cx<T> ph{T(tp.cs * scale), T(tp.sn * scale)};
+    const double sc = scale * deconv;
+    const cx<T> ph{T(tp.cs * sc), T(tp.sn * sc)};
     const cx<T> a = cmul(acc, ph), b = cmul(acc2, ph);
     return cx<T>{a.x + b.x, a.y - b.y};
   }
-  double wgt = two_c * Kz * rK * scale;
+  double wgt = two_c * Kz * rK * scale * deconv;
   if (MODE == MODE_PHYSICAL && ((jj + kk) & 1)) wgt = -wgt;
   const cx<T> ph{T(wgt * tp.cs), T(wgt * tp.sn)};
   return cmul(acc, ph);
@@ -178,7 +181,8 @@ template <typename T, int MODE, int WT = 0>
 __device__ __forceinline__ void gather_body(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
                                             double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                             double n0_over_nt, double scale, int wt, int deg,
-                                            const T* __restrict__ hcoef, cx<T>* __restrict__ Fh, int bx,
+                                            const T* __restrict__ hcoef, const T* __restrict__ dcx,
+                                            const T* __restrict__ dcy, cx<T>* __restrict__ Fh, int bx,
                                             const T* coefs = nullptr) {
   const int Lh = Nz / 2 + 1;
   const long long total = (long long)Nx * Ny * Lh;
@@ -189,19 +193,20 @@ __device__ __forceinline__ void gather_body(const cx<T>* __restrict__ Gh, int nb
   const int kk = int(col % Ny);
   const int jj = int(col / Ny);
   Fh[idx] = gather_point<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt,
-                                      deg, hcoef, jj, kk, l, coefs);
+                                      deg, hcoef, jj, kk, l, double(dcx[jj]) * double(dcy[kk]), coefs);
 }
 
 template <typename T, int MODE, int WT>
 __global__ __launch_bounds__(256) void k_gather(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
                                                 double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                                 double n0_over_nt, double scale, int wt, int deg,
-                                                const T* __restrict__ hcoef, cx<T>* __restrict__ Fh) {
+                                                const T* __restrict__ hcoef, const T* __restrict__ dcx,
+                                                const T* __restrict__ dcy, cx<T>* __restrict__ Fh) {
   __shared__ T coefs[kMaxTapCoefs];
   stage_tap_coefs<T, WT>(coefs, hcoef, deg);
   __syncthreads();
   gather_body<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg, hcoef,
-                           Fh, blockIdx.x, coefs);
+                           dcx, dcy, Fh, blockIdx.x, coefs);
 }
 
 // Gather fused with the first pass of the inverse 3-D FFT (image and
@@ -215,9 +220,11 @@ template <typename T, int MODE, int WT>
 __device__ __forceinline__ void gather_fill(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny,
                                             int Nz, double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                             double n0_over_nt, double scale, int wt, int deg,
-                                            const T* __restrict__ hcoef, int l0, int nl, bool padded, int stride,
+                                            const T* __restrict__ hcoef, const T* __restrict__ dcx,
+                                            const T* __restrict__ dcy, int l0, int nl, bool padded, int stride,
                                             cx<T>* buf, int kk, const T* coefs) {
   const FastDiv div_nl(nl);
+  const double dk = dcy[kk];
   // (one loop form for every length: the batched reconstruction runs this
   // loop too, and the same code keeps the two paths' values bit for bit equal)
   for (int q = threadIdx.x; q < nl * Nx; q += blockDim.x) {
@@ -225,7 +232,7 @@ __device__ __forceinline__ void gather_fill(const cx<T>* __restrict__ Gh, int nb
     const int li = q - jj * nl;
     buf[li * stride + (padded ? lpos(jj) : jj)] =
         gather_point<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale,
-                                  wt, deg, hcoef, jj, kk, l0 + li, coefs);
+                                  wt, deg, hcoef, jj, kk, l0 + li, double(dcx[jj]) * dk, coefs);
   }
 }
 
@@ -270,6 +277,7 @@ __global__ __launch_bounds__(kFftThreads) void k_gather_x(const cx<T>* __restric
                                                         int Nx, int Ny, int Nz, double s_per_k, double kxu,
                                                         double kyu, double kzu, double two_c, double n0_over_nt,
                                                         double scale, int wt, int deg, const T* __restrict__ hcoef,
+                                                        const T* __restrict__ dcx, const T* __restrict__ dcy,
                                                         int lchunk, FftDesc<T> fd, Fft2Raw f2, int wm,
                                                         cx<T>* __restrict__ F, int pitch_f) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -285,7 +293,7 @@ __global__ __launch_bounds__(kFftThreads) void k_gather_x(const cx<T>* __restric
   const int l0 = (gl - kk * int(gridDim.x)) * lchunk;
   const int nl = min(lchunk, Nz / 2 - l0);
   gather_fill<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg,
-                           hcoef, l0, nl, CLS == 0, CLS == 0 ? lseq(Nx) : f2.P, buf, kk, coefs);
+                           hcoef, dcx, dcy, l0, nl, CLS == 0, CLS == 0 ? lseq(Nx) : f2.P, buf, kk, coefs);
   __syncthreads();
   gather_transform<T, CLS>(buf, f2, fd, lchunk, Nx, Ny, nl, wm, F, pitch_f, l0, kk);
 }
@@ -329,6 +337,8 @@ hipError_t launch_gather_x(const DevPlan& p, const void* Gh, void* F, int mode, 
   const cx<T>* in = static_cast<const cx<T>*>(Gh);
   cx<T>* out = static_cast<cx<T>*>(F);
   const T* hc = static_cast<const T*>(p.hcoef);
+  const T* dcx = static_cast<const T*>(p.dcx);
+  const T* dcy = static_cast<const T*>(p.dcy);
   const bool adj = mode == GATHER_ADJOINT;
   const double scale = adj ? p.adj_scale : p.inv_vol;
   return wt_pick(p.w_t, [&](auto w) {
@@ -339,7 +349,7 @@ hipError_t launch_gather_x(const DevPlan& p, const void* Gh, void* F, int mode, 
         hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(kern, grid, dim3(cfg.threads), lds, s, in, p.nb, p.pitch_g, p.b_lo, p.Nx, p.Ny, p.Nz,
-                           p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, scale, p.w_t, p.hdeg, hc, lc,
+                           p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, scale, p.w_t, p.hdeg, hc, dcx, dcy, lc,
                            as_desc<T>(p.f_Nx), f2, cfg.wave, out, p.pitch_f);
         return hipGetLastError();
       };
@@ -355,28 +365,15 @@ hipError_t launch_gather(const DevPlan& p, const void* Gh, void* Fh, int mode, h
   const cx<T>* in = static_cast<const cx<T>*>(Gh);
   cx<T>* out = static_cast<cx<T>*>(Fh);
   const T* hc = static_cast<const T*>(p.hcoef);
+  const T* dcx = static_cast<const T*>(p.dcx);
+  const T* dcy = static_cast<const T*>(p.dcy);
   if (p.w_t * (p.hdeg + 1) > kMaxTapCoefs) return hipErrorInvalidValue;
+  if (mode != GATHER_PHYSICAL) return hipErrorInvalidValue;  // the image modes run with the x pass
   return wt_pick(p.w_t, [&](auto c) {
     constexpr int WT = decltype(c)::value;
-    switch (mode) {
-      case GATHER_IMAGE:
-        hipLaunchKernelGGL((k_gather<T, MODE_IMAGE, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.pitch_g, p.b_lo, p.Nx,
-                           p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, p.inv_vol, p.w_t, p.hdeg,
-                           hc, out);
-        break;
-      case GATHER_PHYSICAL:
-        hipLaunchKernelGGL((k_gather<T, MODE_PHYSICAL, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.pitch_g, p.b_lo, p.Nx,
-                           p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, 1.0, p.w_t, p.hdeg, hc,
-                           out);
-        break;
-      case GATHER_ADJOINT:
-        hipLaunchKernelGGL((k_gather<T, MODE_ADJOINT, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.pitch_g, p.b_lo, p.Nx,
-                           p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, p.adj_scale, p.w_t,
-                           p.hdeg, hc, out);
-        break;
-      default:
-        return hipErrorInvalidValue;
-    }
+    hipLaunchKernelGGL((k_gather<T, MODE_PHYSICAL, WT>), dim3(blocks), dim3(256), 0, s, in, p.nb, p.pitch_g, p.b_lo,
+                       p.Nx, p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu, p.two_c, p.n0_over_nt, 1.0, p.w_t, p.hdeg, hc,
+                       dcx, dcy, out);
     return hipGetLastError();
   });
 }
@@ -565,7 +562,8 @@ __device__ __forceinline__ void gather_batch_fill(const GatherBA& a, T* coefs, b
   __syncthreads();
   gather_fill<T, MODE_IMAGE, WT>(static_cast<const cx<T>*>(a.Gh), a.nb, a.pitch_g, a.b_lo, a.Nx, a.Ny, a.Nz,
                                  a.s_per_k, a.kxu, a.kyu, a.kzu, a.two_c, a.n0_over_nt, a.scale, a.wt, a.deg,
-                                 static_cast<const T*>(a.hcoef), l0, nl, padded, stride, buf, kk, coefs);
+                                 static_cast<const T*>(a.hcoef), static_cast<const T*>(a.dcx),
+                                 static_cast<const T*>(a.dcy), l0, nl, padded, stride, buf, kk, coefs);
 }
 
 template <typename T, int CLS>

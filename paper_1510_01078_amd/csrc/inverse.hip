@@ -45,40 +45,57 @@ __global__ __launch_bounds__(kInvYThreads, (reg_waves<T, CLS>())) void k_cfft_y_
 }
 
 // Two-pass register transform of pairs of rows along z to real: two real rows
-// share one complex transform, Z = X0 + i X1 (each Hermitian-extended, loaded
-// as the first pass's inputs) transforms to x0 + i x1. The DC bin keeps its
-// real part only, as the real part of a single row's transform would; the
-// Nyquist bin is zero.
+// share one complex transform, Z = X0 + i X1 (each Hermitian-extended)
+// transforms to x0 + i x1. The DC bin keeps its real part only, as the real
+// part of a single row's transform would; the Nyquist bin is zero. The rows go
+// to LDS once and the first pass works there: loading its inputs from memory
+// takes every value twice, for z and -z.
 template <typename T, int CLS>
 __device__ __forceinline__ void c2r_reg_body(const cx<T>* __restrict__ F, long long nrows, int pitch, const Fft2<T>& f,
                                              T* __restrict__ out, int bx, int tid) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
-  const int Nz = f.r1 * f.r2;
+  const int Nz = f.r1 * f.r2, Lz = Nz / 2;
   const long long r0 = (long long)bx * (2 << f.ls);  // the group's first row
   const int nr = (int)min((long long)(2 << f.ls), nrows - r0);
+  const int np = (nr + 1) / 2;
   {
-    const int s = small_div(tid, f.r2), i = tid - s * f.r2;
-    if (2 * s < nr) {
-      const cx<T>* row = F + r0 * pitch;
-      const bool two = 2 * s + 1 < nr;
-      const unsigned at = unsigned(2 * s * pitch);
-      reg_first_any<T, CLS, true>(f, buf + s * f.P, i, [&](int e) {
-        const int l = min(e, Nz - e);
-        if (l == Nz / 2) return cx<T>{T(0), T(0)};
-        const cx<T> a = cx_at(row, at + unsigned(l));
-        const cx<T> c = two ? cx_at(row, at + unsigned(l + pitch)) : cx<T>{T(0), T(0)};
-        if (e == 0) return cx<T>{a.x, c.x};
-        return e == l ? cx<T>{a.x - c.y, a.y + c.x} : cx<T>{a.x + c.y, c.x - a.y};
-      });
-    }
+    const cx<T>* row = F + r0 * pitch;
+    const FastDiv div_lz(Lz);
+    struct Two {
+      cx<T> a, c;
+    };
+    // Lz values per pair over the r1 or r2 threads a pair has: at most half the smaller radix each
+    staged_copy<CLS == 16 ? 8 : 10>(
+        np * Lz, tid, blockDim.x,
+        [&](int q) {
+          const int s = div_lz(q);
+          const unsigned at = unsigned(2 * s * pitch + (q - s * Lz));
+          return Two{cx_at(row, at), cx_at(row, at + (2 * s + 1 < nr ? unsigned(pitch) : 0u))};
+        },
+        [&](int q, Two v) {
+          const int s = div_lz(q), l = q - s * Lz;
+          if (2 * s + 1 >= nr) v.c = cx<T>{T(0), T(0)};
+          cx<T>* seq = buf + s * f.P;
+          if (l == 0) {
+            seq[0] = cx<T>{v.a.x, v.c.x};
+            seq[Lz] = cx<T>{T(0), T(0)};
+          } else {
+            seq[l] = cx<T>{v.a.x - v.c.y, v.a.y + v.c.x};
+            seq[Nz - l] = cx<T>{v.a.x + v.c.y, v.c.x - v.a.y};
+          }
+        });
   }
   __syncthreads();
-  const int s = small_div(tid, f.r1), k = tid - s * f.r1;
-  if (2 * s < nr && s < (1 << f.ls)) {
-    T* o = out + (r0 + 2 * s) * Nz + k;
+  int s = small_div(tid, f.r2), i = tid - s * f.r2;
+  reg_first_in_lds_any<T, CLS, true>(f, buf + s * f.P, i, s < np);
+  __syncthreads();
+  s = small_div(tid, f.r1);
+  i = tid - s * f.r1;
+  if (s < np) {
+    T* o = out + (r0 + 2 * s) * Nz + i;
     const bool two = 2 * s + 1 < nr;
-    reg_second_any<T, CLS, true>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
+    reg_second_any<T, CLS, true>(f, buf + s * f.P, i, [&](int q, cx<T> v) {
       o[q * f.r1] = v.x;
       if (two) o[q * f.r1 + Nz] = v.y;
     });

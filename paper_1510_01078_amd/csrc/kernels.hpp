@@ -227,12 +227,12 @@ struct FftXBA {
   const void* U; FftView fd; Fft2Raw f2; int n_y, Nx, rows, gx, pitch_u, pitch_v; void* V; const int* brange;
 };
 struct FftYBA {
-  const void* V; const void* dcx; const void* dcy; FftView fd; Fft2Raw f2; int nb, Nx, Ny, bins, gx, pitch_v, pitch_g; void* Gh;
+  const void* V; FftView fd; Fft2Raw f2; int nb, Nx, Ny, bins, gx, pitch_v, pitch_g; void* Gh;
   const int* jrange;  // per x-mode band range (bin groups outside it are skipped)
   const int* ylist;   // the work items inside the ranges (jj << 16 | bin group), or nullptr: gx * Nx items
 };
 struct GatherBA {  // the gather fused with the inverse transform along x
-  const void* Gh; const void* hcoef; int nb, b_lo, Nx, Ny, Nz, wt, deg;
+  const void* Gh; const void* hcoef; const void* dcx; const void* dcy; int nb, b_lo, Nx, Ny, Nz, wt, deg;
   int wt_ct, pitch_g;  // compile-time tap count to run (kBatchTaps member equal to wt, else 0: runtime taps)
   double s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale; void* Fh;
   FftView fd; Fft2Raw f2; int lchunk, gx, pitch_f, pad;  // x transform (length Nx), z modes per group, groups along z

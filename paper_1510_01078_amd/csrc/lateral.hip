@@ -160,9 +160,10 @@ hipError_t launch_fft_x(const DevPlan& p, const void* U, void* V, int b_begin, i
 }
 
 // ---------------------------------------------------------------------------
-// Stage 3: FFT along y, keep the Ny centred modes, divide by the window
-// transform in x and y (eq. NED_NUFFT's 1/Psi_j), and transpose so the bins
-// of each lateral mode are contiguous: V[b][jj][py] -> Gh[jj][kk][b].
+// Stage 3: FFT along y, keep the Ny centred modes and transpose so the bins
+// of each lateral mode are contiguous: V[b][jj][py] -> Gh[jj][kk][b]. (The
+// gather divides by the window transform in x and y, eq. NED_NUFFT's 1/Psi_j:
+// one factor per interpolated point instead of one per mode and bin.)
 // ---------------------------------------------------------------------------
 // jrange (may be nullptr): groups of bins outside the x-mode's range are
 // skipped (the interpolation never reads them).
@@ -172,9 +173,7 @@ hipError_t launch_fft_x(const DevPlan& p, const void* U, void* V, int b_begin, i
 // once, and keeping it out of the caches leaves them to the spectra this
 // kernel writes, which the gather reads next.
 template <typename T, int CLS>
-__device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny,
-                                               const T* __restrict__ dcx, const T* __restrict__ dcy,
-                                               const Fft2<T>& f, cx<T>* __restrict__ Gh, int bx, int jj,
+__device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny, const Fft2<T>& f, cx<T>* __restrict__ Gh, int bx, int jj,
                                                const int* __restrict__ jrange, int tid) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
@@ -194,23 +193,18 @@ __device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int 
   __syncthreads();
   const int s = tid & (S - 1), k = tid >> f.ls;
   if (k < f.r1 && s < nbc) {
-    const T cxj = dcx[jj];
     cx<T>* dst = Gh + size_t(jj) * Ny * pg + b0 + s;
     reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
       // element e holds mode e below Ny/2 and e - n_y from -Ny/2 on
       const int e = k + q * f.r1;
       const int kk = e < Ny / 2 ? e : e - (n_y - Ny);
-      if (e < Ny / 2 || e >= n_y - Ny / 2) {
-        const T sc = cxj * dcy[kk];
-        cx_at(dst, unsigned(kk * pg)) = cx<T>{v.x * sc, v.y * sc};
-      }
+      if (e < Ny / 2 || e >= n_y - Ny / 2) cx_at(dst, unsigned(kk * pg)) = v;
     });
   }
 }
 
 template <typename T>
 __device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny, int bins,
-                                           const T* __restrict__ dcx, const T* __restrict__ dcy,
                                            FftDesc<T> fd, cx<T>* __restrict__ Gh, int wm, int bx, int by,
                                            const int* __restrict__ jrange = nullptr, int tid = threadIdx.x) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -224,7 +218,6 @@ __device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, 
   if (jrange && (b0 + nbc - 1 < jrange[2 * jj] || b0 > jrange[2 * jj + 1])) return;
   const cx<T>* src = V + (size_t(b0) * Nx + jj) * pv;  // bin b0 + bi at src + bi * Nx * pv
   const size_t bin_stride = size_t(Nx) * pv;
-  const T cxj = dcx[jj];
   cx<T>* dst = Gh + size_t(jj) * Ny * pg + b0;
   // output mode kk of the Ny kept, centred, at its slot of the n_y transform
   auto slot = [&](int kk) {
@@ -251,10 +244,7 @@ __device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, 
       nbc * Ny, tid, nthr,
       [&](int q) {
         const int kk = div_nbc(q);
-        const int bi = q - kk * nbc;
-        const T sc = cxj * dcy[kk];
-        const cx<T> v = buf[bi * bstride + slot(kk)];
-        return cx<T>{v.x * sc, v.y * sc};
+        return buf[(q - kk * nbc) * bstride + slot(kk)];
       },
       [&](int q, cx<T> v) {
         const int kk = div_nbc(q);
@@ -277,25 +267,23 @@ __device__ __forceinline__ void y_item(const int* __restrict__ ylist, int gl, in
 
 template <typename T>
 __global__ __launch_bounds__(kFftThreads) void k_fft_y(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny, int bins,
-                                                     const T* __restrict__ dcx, const T* __restrict__ dcy,
                                                      FftDesc<T> fd, cx<T>* __restrict__ Gh, int wm,
                                                      const int* __restrict__ jrange, const int* __restrict__ ylist) {
   // neighbouring groups write the two halves of each 128-byte output line:
   // keep them on one XCD so its L2 merges the halves
   int bx, by;
   y_item(ylist, xcd_linear(), bx, by);
-  fft_y_body<T>(V, nb, pv, pg, Nx, Ny, bins, dcx, dcy, fd, Gh, wm, bx, by, jrange);
+  fft_y_body<T>(V, nb, pv, pg, Nx, Ny, bins, fd, Gh, wm, bx, by, jrange);
 }
 
 template <typename T, int CLS>
 __global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_y_reg(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny,
-                                                           const T* __restrict__ dcx, const T* __restrict__ dcy,
                                                            Fft2Raw f, cx<T>* __restrict__ Gh,
                                                            const int* __restrict__ jrange,
                                                            const int* __restrict__ ylist) {
   int bx, by;
   y_item(ylist, xcd_linear(), bx, by);
-  fft_y_reg_body<T, CLS>(V, nb, pv, pg, Nx, Ny, dcx, dcy, as_fft2<T>(f), Gh, bx, by, jrange, threadIdx.x);
+  fft_y_reg_body<T, CLS>(V, nb, pv, pg, Nx, Ny, as_fft2<T>(f), Gh, bx, by, jrange, threadIdx.x);
 }
 
 template <typename T>
@@ -313,8 +301,7 @@ hipError_t launch_fft_y(const DevPlan& p, const void* V, void* Gh, hipStream_t s
       hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(kern, grid, dim3(fft2_threads(f)), lds, s, static_cast<const cx<T>*>(V), p.nb, p.pitch_v,
-                         p.pitch_g, p.Nx, p.Ny,
-                         static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), f, static_cast<cx<T>*>(Gh),
+                         p.pitch_g, p.Nx, p.Ny, f, static_cast<cx<T>*>(Gh),
                          p.jrange, ylist);
       return hipGetLastError();
     });
@@ -326,8 +313,7 @@ hipError_t launch_fft_y(const DevPlan& p, const void* V, void* Gh, hipStream_t s
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_fft_y<T>, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(V), p.nb, p.pitch_v,
                      p.pitch_g, p.Nx, p.Ny,
-                     bins, static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), as_desc<T>(p.f_ny),
-                     static_cast<cx<T>*>(Gh), cfg.wave, p.jrange, ylist);
+                     bins, as_desc<T>(p.f_ny), static_cast<cx<T>*>(Gh), cfg.wave, p.jrange, ylist);
   return hipGetLastError();
 }
 
@@ -546,12 +532,10 @@ __global__ __launch_bounds__(kFftThreads, (any_waves<T, CLS>())) void k_fft_y_ba
       bx = e & 0xffff;
     }
     if constexpr (CLS > 0)
-      fft_y_reg_body<T, CLS>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, static_cast<const T*>(a.dcx),
-                             static_cast<const T*>(a.dcy), as_fft2<T>(a.f2), static_cast<cx<T>*>(a.Gh), bx, by,
+      fft_y_reg_body<T, CLS>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, as_fft2<T>(a.f2), static_cast<cx<T>*>(a.Gh), bx, by,
                              a.jrange, loop_lane());
     else
-      fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, a.bins, static_cast<const T*>(a.dcx),
-                    static_cast<const T*>(a.dcy), view_desc<T>(a.fd), static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
+      fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, a.bins, view_desc<T>(a.fd), static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
                     loop_lane());
   }
 }
