@@ -620,6 +620,8 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   // halo recomputation, measured faster) where the work-group LDS holds them
   dp.fused_strip =
       dp.tiles_y >= 2 && patk::fused_interp_lds<T>(dp, 2) + patk::kStaticLdsMargin <= (size_t)lds_limit ? 2 : 1;
+  P->forward_reg = P->forward_fused && dp.f_ny.two.r1 &&
+                   patk::fused_reg_ok<T>(dp, (size_t)lds_limit - patk::kStaticLdsMargin);
   return PAT_OK;
 }
 
@@ -710,10 +712,14 @@ pat_status run_image_in(pat_plan* P, const void* f, void* g, void* ws, hipStream
   mark(5, 4);
   if ((e = patk::launch_scatter<T>(dp, B, A, deriv, s)) != hipSuccess) return to_status(e);
   mark(4, 3);
-  if ((e = patk::launch_fft_y_t<T>(dp, A, B, s)) != hipSuccess) return to_status(e);
+  const bool reg = P->forward_reg && op == OP_FORWARD;
+  if ((e = reg ? patk::launch_fft_y_t_reg<T>(dp, A, B, s) : patk::launch_fft_y_t<T>(dp, A, B, s)) != hipSuccess)
+    return to_status(e);
   mark(3, P->forward_fused ? 1 : 2);
   if (P->forward_fused) {
-    if ((e = patk::launch_fft_x_interp<T>(dp, B, C, s)) != hipSuccess) return to_status(e);
+    if ((e = reg ? patk::launch_fft_x_interp_reg<T>(dp, B, C, s) : patk::launch_fft_x_interp<T>(dp, B, C, s)) !=
+        hipSuccess)
+      return to_status(e);
     mark(1, 0);
   } else {
     for (int b0 = 0; b0 < dp.nb; b0 += dp.chunk_bins) {

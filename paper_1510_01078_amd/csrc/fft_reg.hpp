@@ -432,20 +432,6 @@ __device__ __forceinline__ void three_last_any(const Fft3<T>& f, const cx<T>* sr
 #undef PATK_CASE
 }
 
-// The last of two passes (r3 = 1) into natural order in LDS.
-template <typename T, int CLS, bool INV, typename Store>
-__device__ __forceinline__ void two_last_any(const Fft3<T>& f, const cx<T>* src, bool active, Store st) {
-#define PATK_CASE(R) case R: reg_in_lds<T, R, INV>(src, 1, active, st); break;
-  if constexpr (CLS == 16) {
-    switch (f.r2) { PATK_RADICES_16(PATK_CASE) default: break; }
-  } else if constexpr (CLS == 20) {
-    switch (f.r2) { PATK_SECOND_20(PATK_CASE) default: break; }
-  } else {
-    switch (f.r2) { PATK_SECOND_32(PATK_CASE) default: break; }
-  }
-#undef PATK_CASE
-}
-
 template <typename T, int CLS, bool INV, typename Load>
 __device__ __forceinline__ void reg_first_any(const Fft2<T>& f, cx<T>* seq, int i, Load ld) {
 #define PATK_CASE(R) case R: reg_first<T, R, INV>(seq, f.r2, f.Q, f.tw, i, ld); break;
@@ -475,6 +461,21 @@ __device__ __forceinline__ void reg_first_in_lds_any(const Fft2<T>& f, cx<T>* se
 template <typename T, int CLS, bool INV, typename Store>
 __device__ __forceinline__ void reg_second_any(const Fft2<T>& f, const cx<T>* seq, int k, Store st) {
 #define PATK_CASE(R) case R: reg_second<T, R, INV>(seq, f.Q, k, st); break;
+  if constexpr (CLS == 16) {
+    switch (f.r2) { PATK_RADICES_16(PATK_CASE) default: break; }
+  } else if constexpr (CLS == 20) {
+    switch (f.r2) { PATK_SECOND_20(PATK_CASE) default: break; }
+  } else {
+    switch (f.r2) { PATK_SECOND_32(PATK_CASE) default: break; }
+  }
+#undef PATK_CASE
+}
+
+// Second pass in place in LDS: `active` threads read the r2 values at src, and
+// output q goes to st(q, v) after the barrier.
+template <typename T, int CLS, bool INV, typename Store>
+__device__ __forceinline__ void reg_second_in_lds_any(const Fft2<T>& f, const cx<T>* src, bool active, Store st) {
+#define PATK_CASE(R) case R: reg_in_lds<T, R, INV>(src, 1, active, st); break;
   if constexpr (CLS == 16) {
     switch (f.r2) { PATK_RADICES_16(PATK_CASE) default: break; }
   } else if constexpr (CLS == 20) {

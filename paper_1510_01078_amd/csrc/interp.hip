@@ -6,7 +6,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "kernels_common.hpp"
+#include "interp_sensor.hpp"
 
 namespace patk {
 
@@ -132,64 +132,6 @@ hipError_t launch_interp(const DevPlan& p, const void* U, void* Gt, int b_begin,
 // and the row transforms take the same passes as k_fft_x_t, so the two forms
 // agree to rounding.
 // ---------------------------------------------------------------------------
-constexpr int kFusedThreads = 512;  // per home-tile row of the strip
-constexpr int kFusedBins = 8;       // most bins per work-group
-// sensors per thread whose bins are held in registers: as many as fit the
-// register budget without spills (FP32 footprints up to 8 or 12 points)
-template <typename T, int W>
-__host__ __device__ constexpr int fused_held() {
-  return sizeof(T) == 4 ? (W <= 8 ? 2 : (W <= 12 ? 1 : 0)) : 0;
-}
-
-template <int W, int FS>
-__host__ __device__ constexpr int fused_rows() { return FS * kSpreadTile + W - 1; }
-
-// One sensor of the strip: footprint origin row within the strip, the LDS
-// slots of its footprint columns, and its weights.
-template <typename T, int W>
-struct FusedSensor {
-  int m, oy;
-  int col[W];
-  T wx[W], wy[W];
-};
-
-template <typename T, int W>
-__device__ __forceinline__ void fused_sensor_load(FusedSensor<T, W>& f, int m, int py0, int n_x,
-                                                  const int* __restrict__ sbx, const int* __restrict__ sby,
-                                                  const T* __restrict__ swx, const T* __restrict__ swy) {
-  f.m = m;
-  const int ox = sbx[m];
-  f.oy = sby[m] - py0;
-#pragma unroll
-  for (int t = 0; t < W; ++t) {
-    f.wx[t] = swx[size_t(m) * W + t];
-    f.wy[t] = swy[size_t(m) * W + t];
-    int c = ox + t;
-    if (c >= n_x) c -= n_x;
-    f.col[t] = lpos(c);
-  }
-}
-
-// footprint sum in k_interp's order: rows of x-weighted sums, then y weights
-template <typename T, int W>
-__device__ __forceinline__ cx<T> fused_sensor_sum(const FusedSensor<T, W>& f, const cx<T>* buf, int bstride) {
-  const cx<T>* rows = buf + f.oy * bstride;
-  cx<T> acc{T(0), T(0)};
-#pragma unroll
-  for (int ty = 0; ty < W; ++ty) {
-    cx<T> row{T(0), T(0)};
-#pragma unroll
-    for (int tx = 0; tx < W; ++tx) {
-      const cx<T> v = rows[ty * bstride + f.col[tx]];
-      row.x += f.wx[tx] * v.x;
-      row.y += f.wx[tx] * v.y;
-    }
-    acc.x += f.wy[ty] * row.x;
-    acc.y += f.wy[ty] * row.y;
-  }
-  return acc;
-}
-
 template <typename T, int W, int MAXV, int NCT, int FS>
 __global__ __launch_bounds__(kFusedThreads * FS) void k_fft_x_interp(
     const cx<T>* __restrict__ V, int nb, int Nx, int n_y, int tiles_x, int nchunks, int bins,
@@ -316,40 +258,9 @@ static hipError_t launch_fused_wvs(const DevPlan& p, const void* V, void* Gt, hi
   const size_t lds = fused_interp_lds<T>(p, FS);
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_fft_x_interp<T, W, MAXV, NCT, FS>), lds);
   if (e != hipSuccess) return e;
-  // bins per work-group: enough groups to fill the device several times over
   const long long strips = (p.tiles_y + FS - 1) / FS;
-  int bins = int(std::min<long long>(kFusedBins, std::max<long long>(1, p.tiles_y * p.nb / 2048)));
-  // where even 4 bins per group fill every resident slot at least twice, the
-  // count in 4..kFusedBins whose last wave of work-groups is fullest (the
-  // groups take about equal time, and a part-filled last wave idles the
-  // rest of the device: 0.98 -> 0.965 ms per forward call with 576 bins
-  // on a 384^2 grid, 7 bins instead of 6)
-  static int slots_cache[64] = {};  // resident groups on the device, per device
-  int dev = 0;
-  if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
-    if (slots_cache[dev] == 0) {
-      int per_cu = 0, cus = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-              &per_cu, reinterpret_cast<const void*>(&k_fft_x_interp<T, W, MAXV, NCT, FS>), kFusedThreads * FS,
-              lds) == hipSuccess &&
-          hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
-        slots_cache[dev] = std::max(1, per_cu * cus);
-      else
-        slots_cache[dev] = -1;
-    }
-    const long long slots = slots_cache[dev];
-    if (slots > 0 && strips * ((p.nb + 3) / 4) >= 2 * slots) {
-      double best = -1.0;
-      for (int bb = 4; bb <= kFusedBins; ++bb) {
-        const double waves = double(strips * ((p.nb + bb - 1) / bb)) / double(slots);
-        const double fill = waves / std::ceil(waves);
-        if (fill >= best - 1e-9) {
-          best = fill;
-          bins = bb;
-        }
-      }
-    }
-  }
+  const int bins = fused_bins(reinterpret_cast<const void*>(&k_fft_x_interp<T, W, MAXV, NCT, FS>), kFusedThreads * FS,
+                              lds, strips, p.nb, p.tiles_y);
   const int nchunks = (p.nb + bins - 1) / bins;
   const long long blocks = strips * nchunks;
   hipLaunchKernelGGL((k_fft_x_interp<T, W, MAXV, NCT, FS>), dim3((unsigned)blocks), dim3(kFusedThreads * FS), lds, s,

@@ -180,6 +180,14 @@ hipError_t launch_interp(const DevPlan& p, const void* U, void* Gt, int b_begin,
 // work-group LDS limit.
 template <typename T>
 hipError_t launch_fft_x_interp(const DevPlan& p, const void* V, void* Gt, hipStream_t s);
+// The two as register transforms (rows of pitch_v between them): lengths with
+// two passes, and for the second fused_reg_ok.
+template <typename T>
+hipError_t launch_fft_y_t_reg(const DevPlan& p, const void* Gh, void* V, hipStream_t s);
+template <typename T>
+hipError_t launch_fft_x_interp_reg(const DevPlan& p, const void* V, void* Gt, hipStream_t s);
+template <typename T>
+bool fused_reg_ok(const DevPlan& p, size_t lds_limit);
 // Static LDS that the fused kernel and the transposed interpolation hold
 // beside their dynamic LDS (row and run tables); the plan's fit checks add it.
 constexpr size_t kStaticLdsMargin = 512;

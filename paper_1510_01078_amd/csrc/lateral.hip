@@ -323,6 +323,74 @@ hipError_t launch_fft_y(const DevPlan& p, const void* V, void* Gh, hipStream_t s
 // inverse FFT).
 // Gh'[j][k][b] -> V'[b][j][py] = dcx_j sum_k dcy_k Gh'[j][k][b] e^{+2 pi i k py/n_y}
 // ---------------------------------------------------------------------------
+// Two-pass register form (the forward model): a wave of the first pass walks
+// the S bins of one mode, the slots between the kept modes are zeros, and the
+// second pass writes along the rows (of pv elements).
+template <typename T, int CLS>
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_y_t_reg(
+    const cx<T>* __restrict__ Gh, int nb, int Nx, int Ny, const T* __restrict__ dcx, const T* __restrict__ dcy,
+    Fft2Raw fr, cx<T>* __restrict__ V, int pv, const int* __restrict__ jrange, const int* __restrict__ ylist) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
+  const Fft2<T> f = as_fft2<T>(fr);
+  const int tid = threadIdx.x;
+  const int S = 1 << f.ls;
+  const int n_y = f.r1 * f.r2;
+  // (an XCD-grouped order measured slower here)
+  const int jj = ylist ? ylist[blockIdx.x] >> 16 : int(blockIdx.y);
+  const int b0 = (ylist ? ylist[blockIdx.x] & 0xffff : int(blockIdx.x)) << f.ls;
+  const int nbc = min(S, nb - b0);
+  // bins outside the x-mode's range hold zeros that nothing reads: skipped
+  if (jrange && (b0 + nbc - 1 < jrange[2 * jj] || b0 > jrange[2 * jj + 1])) return;
+  {
+    const int s = tid & (S - 1), i = tid >> f.ls;
+    if (i < f.r2 && s < nbc) {
+      const T cxj = dcx[jj];
+      const cx<T>* src = Gh + size_t(jj) * Ny * nb + b0 + s;
+      reg_first_any<T, CLS, true>(f, buf + s * f.P, i, [&](int e) {
+        const bool in = e < Ny / 2 || e >= n_y - Ny / 2;
+        const int kk = e < Ny / 2 ? e : in ? e - (n_y - Ny) : 0;  // the loads carry no branch
+        const T sc = in ? cxj * dcy[kk] : T(0);
+        const cx<T> v = cx_at(src, unsigned(kk * nb));
+        return cx<T>{in ? v.x * sc : T(0), in ? v.y * sc : T(0)};
+      });
+    }
+  }
+  __syncthreads();
+  const int s = small_div(tid, f.r1), k = tid - s * f.r1;
+  if (s < nbc) {
+    cx<T>* v0 = V + (size_t(b0) * Nx + jj) * pv;  // bin b0 + s at v0 + s * Nx * pv
+    const unsigned at = unsigned(s) * unsigned(Nx * pv) + unsigned(k);
+    reg_second_any<T, CLS, true>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
+      // non-temporal: streams out once (measured faster for the fused reader)
+      nt_store(&cx_at(v0, at + unsigned(q * f.r1)), v);
+    });
+  }
+}
+
+template <typename T>
+hipError_t launch_fft_y_t_reg(const DevPlan& p, const void* Gh, void* V, hipStream_t s) {
+  if (!p.f_ny.two.r1) return hipErrorInvalidValue;
+  const FftCfg cfg = fft_cfg();
+  const int bins = fft_bins<T>(p.f_ny, cfg.threads, cfg.cap);
+  const bool listed = p.ylist && p.ylist_n > 0 && p.jrange;
+  const dim3 grid = listed ? dim3(p.ylist_n) : dim3((p.nb + bins - 1) / bins, p.Nx);
+  const Fft2Raw f = fft2_shape<T>(p.f_ny, bins);
+  const size_t lds = fft2_slots(f) * sizeof(cx<T>);
+  return class_pick(f, [&](auto c) {
+    constexpr auto kern = &k_fft_y_t_reg<T, decltype(c)::value>;
+    hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, grid, dim3(fft2_threads(f)), lds, s, static_cast<const cx<T>*>(Gh), p.nb, p.Nx, p.Ny,
+                       static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), f, static_cast<cx<T>*>(V),
+                       p.pitch_v, p.jrange, listed ? p.ylist : nullptr);
+    return hipGetLastError();
+  });
+}
+
+// Passes in LDS: other lengths, the two-kernel interpolation, and the position
+// derivatives at every length (they enter gradients that the autograd wrapper
+// returns in double; this form's sums keep their bits).
 template <typename T, int NCT>
 __global__ __launch_bounds__(kFftThreads) void k_fft_y_t(const cx<T>* __restrict__ Gh, int nb, int Nx, int Ny,
                                                        int bins, const T* __restrict__ dcx,
@@ -566,6 +634,7 @@ hipError_t launch_fft_y_batch(const BatchStage& st, const BatchIO& io, hipStream
   template hipError_t launch_fft_x<T>(const DevPlan&, const void*, void*, int, int, hipStream_t); \
   template hipError_t launch_fft_y<T>(const DevPlan&, const void*, void*, hipStream_t);          \
   template hipError_t launch_fft_y_t<T>(const DevPlan&, const void*, void*, hipStream_t);        \
+  template hipError_t launch_fft_y_t_reg<T>(const DevPlan&, const void*, void*, hipStream_t);    \
   template hipError_t launch_fft_x_t<T>(const DevPlan&, const void*, void*, int, int, hipStream_t); \
   template hipError_t launch_fft_x_batch<T>(const BatchStage&, const BatchIO&, hipStream_t); \
   template hipError_t launch_fft_y_batch<T>(const BatchStage&, const BatchIO&, hipStream_t);

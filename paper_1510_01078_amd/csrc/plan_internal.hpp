@@ -69,6 +69,7 @@ struct pat_plan {
   int64_t band_pairs = 0;   // (x-mode, bin) pairs inside the per-x-mode band ranges
   bool forward_ok = false;  // the forward model's per-column LDS fits the device
   bool forward_fused = false;  // the forward model's x-FFT and interpolation run as one kernel
+  bool forward_reg = false;    // ... and its lateral transforms as register passes
   double range_xy = 1.0;    // dynamic range of the lateral deconvolution (x times y)
   double range_t = 1.0;     // dynamic range of the temporal deapodisation
   // timing: per recorded call, marks_per_call events; mark i > 0 closes the

@@ -48,6 +48,7 @@ __device__ __forceinline__ void temporal_reg_body(const T* __restrict__ g, int M
     return s < pairs && i < count;
   };
   constexpr bool TWO = FORM == TEMPORAL_TWO;
+  const Fft2<T> two{f.r1, f.r2, f.P, f.QA, f.ls, f.twA};
   int s, i;
   auto first = [&]() {
     const int m0 = 2 * ((bx << f.ls) + s);
@@ -67,7 +68,7 @@ __device__ __forceinline__ void temporal_reg_body(const T* __restrict__ g, int M
       return cx<T>{in ? a : T(0), in && has1 ? b : T(0)};
     };
     if constexpr (TWO)
-      reg_first_any<T, CLS, false>(Fft2<T>{f.r1, f.r2, f.P, f.QA, f.ls, f.twA}, buf + s * f.P, i, sample);
+      reg_first_any<T, CLS, false>(two, buf + s * f.P, i, sample);
     else
       three_first_any<T, CLS, false>(f, buf + s * f.P, i, sample);
   };
@@ -86,7 +87,7 @@ __device__ __forceinline__ void temporal_reg_body(const T* __restrict__ g, int M
   if constexpr (TWO) {
     const bool on = split(tid, f.r1, s, i);
     seq = buf + s * f.P;
-    two_last_any<T, CLS, false>(f, seq + i * f.QA, on, [&](int q, cx<T> v) { keep(i + f.r1 * q, v); });
+    reg_second_in_lds_any<T, CLS, false>(two, seq + i * f.QA, on, [&](int q, cx<T> v) { keep(i + f.r1 * q, v); });
   } else {
     bool on = split(tid, f.r1 * f.r3, s, i);
     {

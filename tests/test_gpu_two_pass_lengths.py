@@ -98,6 +98,37 @@ def test_image_lengths_vs_oracle(dev, nx, ny, nz):
         assert err <= tol
 
 
+@pytest.mark.parametrize("nx,ny,nz,width", [(8, 6, 4, 8), (24, 40, 6, 8), (48, 18, 4, 2), (96, 20, 4, 8), (100, 30, 6, 12),
+                                            (20, 100, 4, 10), (144, 12, 4, 8), (160, 16, 4, 6), (192, 16, 4, 8),
+                                            (192, 4, 4, 8), (216, 10, 4, 12), (240, 10, 4, 8), (256, 36, 4, 8),
+                                            (320, 8, 4, 8), (16, 360, 4, 8)])
+def test_forward_lengths_vs_oracle(dev, nx, ny, nz, width):
+    """The forward model's transposed lateral transforms: every class of the
+    fused x transform and interpolation, strips of one and two home-tile rows,
+    short y axes that the strip wraps around, narrow and wide footprints, and
+    lengths whose second pass has more butterflies than threads (passes in LDS
+    then). The adjoint beside it: <A f, g> = <f, A* g> within the FP32 sums'
+    rounding (1e-5 of the norms' product)."""
+    from oracle import forward_model as fm
+    from paper_1510_01078_amd import Plan
+    p = _problem(2 * nx, 2 * ny, 2.0, nz)
+    rng = np.random.default_rng(nx + ny)
+    f = rng.standard_normal(p.shape)
+    ref = fm.forward(f, p.xy, p.nt, p.dt, p.c, p.extent)
+    kw = dict(_kw(2.0), width_xy=width)
+    tol = max(1e-5, 8 * np.exp(-np.pi * width * np.sqrt(0.5)))
+    pl = Plan(p.xy, p.nt, p.dt, p.c, p.shape, p.extent, sensor_h=p.h, precision="fp32", **kw)
+    fd = torch.from_numpy(f).to(dev, torch.float32)
+    gd = torch.from_numpy(p.g).to(dev, torch.float32)
+    a, b = pl.forward(fd), pl.adjoint(gd)
+    err = rel_l2(a.cpu().numpy().astype(np.float64), ref)
+    gap = abs(float((a.double() * gd.double()).sum()) - float((fd.double() * b.double()).sum()))
+    scale = float(a.double().norm() * gd.double().norm())
+    pl.close()
+    _say(f"[gpu] forward {nx} x {ny} x {nz} w {width}: {err:.2e}, adjointness {gap / scale:.1e}")
+    assert err <= tol and gap <= 1e-5 * scale
+
+
 def test_batch_of_all_classes_equals_single(dev):
     from paper_1510_01078_amd import Plan
     from paper_1510_01078_amd.batch import Batch, problem_dict
