@@ -708,9 +708,17 @@ pat_status run_image_in(pat_plan* P, const void* f, void* g, void* ws, hipStream
   hipError_t e;
   const int deriv = op == OP_FORWARD_DX ? 1 : (op == OP_FORWARD_DY ? 2 : 0);
   mark(-1, 5);
-  if ((e = patk::launch_forward3d<T>(dp, static_cast<const T*>(f), B, s)) != hipSuccess) return to_status(e);
+  // the register transforms; the position derivatives keep the passes in LDS
+  // at every length: they enter gradients that the autograd wrapper returns in
+  // double, and so keep their bits
+  const bool reg3 = op == OP_FORWARD && dp.f_Nx.two.r1 && dp.f_Ny.two.r1 && dp.f_Nz.two.r1;
+  const T* image = static_cast<const T*>(f);
+  if ((e = reg3 ? patk::launch_forward3d_reg<T>(dp, image, B, s) : patk::launch_forward3d<T>(dp, image, B, s)) !=
+      hipSuccess)
+    return to_status(e);
   mark(5, 4);
-  if ((e = patk::launch_scatter<T>(dp, B, A, deriv, s)) != hipSuccess) return to_status(e);
+  if ((e = patk::launch_scatter<T>(dp, B, reg3 ? dp.pitch_f : dp.Nz / 2 + 1, A, deriv, s)) != hipSuccess)
+    return to_status(e);
   mark(4, 3);
   const bool reg = P->forward_reg && op == OP_FORWARD;
   if ((e = reg ? patk::launch_fft_y_t_reg<T>(dp, A, B, s) : patk::launch_fft_y_t<T>(dp, A, B, s)) != hipSuccess)

@@ -395,7 +395,7 @@ hipError_t launch_gather(const DevPlan& p, const void* Gh, void* Fh, int mode, h
 // per-l phase keeps its threads busy.
 // ---------------------------------------------------------------------------
 template <typename T, int WT>
-__global__ __launch_bounds__(256) void k_scatter(const cx<T>* __restrict__ Dh, int nb, int b_lo, int Nx, int Ny, int Nz,
+__global__ __launch_bounds__(256) void k_scatter(const cx<T>* __restrict__ Dh, int pitch, int nb, int b_lo, int Nx, int Ny, int Nz,
                                                  double s_per_k, double kxu, double kyu, double kzu, double n0_over_nt,
                                                  double scale, int deriv, int wt, int deg, const T* __restrict__ hcoef,
                                                  int cols_per_group, int first_table, const int* __restrict__ jrange,
@@ -405,7 +405,6 @@ __global__ __launch_bounds__(256) void k_scatter(const cx<T>* __restrict__ Dh, i
   stage_tap_coefs<T, WT>(coefs, hcoef, deg);
   __syncthreads();
   const int Lz = Nz / 2;
-  const int Lh = Lz + 1;
   const int ncol_total = Nx * Ny;
   const int col0 = blockIdx.x * cols_per_group;
   const int ncol = min(cols_per_group, ncol_total - col0);
@@ -435,8 +434,8 @@ __global__ __launch_bounds__(256) void k_scatter(const cx<T>* __restrict__ Dh, i
     s_base[q] = tp.base;
     cx<T> z{T(0), T(0)};
     if (jj != Nx / 2 && kk != Ny / 2) {
-      const cx<T> a = Dh[(size_t)col * Lh + l];
-      const cx<T> b = Dh[((size_t)((Nx - jj) % Nx) * Ny + (Ny - kk) % Ny) * Lh + l];
+      const cx<T> a = Dh[(size_t)col * pitch + l];
+      const cx<T> b = Dh[((size_t)((Nx - jj) % Nx) * Ny + (Ny - kk) % Ny) * pitch + l];
       cx<T> u{a.x + b.x, a.y - b.y};
       if (deriv == 1) u = cx<T>{T(-Kx) * u.y, T(Kx) * u.x};
       if (deriv == 2) u = cx<T>{T(-Ky) * u.y, T(Ky) * u.x};
@@ -529,7 +528,7 @@ size_t scatter_lds_bytes(const DevPlan& p) {
 }
 
 template <typename T>
-hipError_t launch_scatter(const DevPlan& p, const void* Dh, void* Gh, int deriv, hipStream_t s) {
+hipError_t launch_scatter(const DevPlan& p, const void* Dh, int pitch, void* Gh, int deriv, hipStream_t s) {
   if (deriv < 0 || deriv > 2) return hipErrorInvalidValue;
   const size_t lds = scatter_lds_bytes<T>(p);
   if (p.w_t * (p.hdeg + 1) > kMaxTapCoefs) return hipErrorInvalidValue;
@@ -540,7 +539,7 @@ hipError_t launch_scatter(const DevPlan& p, const void* Dh, void* Gh, int deriv,
   const int cpg = scatter_cols<T>(p);
   const int ncol = p.Nx * p.Ny;
   hipLaunchKernelGGL((k_scatter<T, WT>), dim3((unsigned)((ncol + cpg - 1) / cpg)), dim3(256), lds, s,
-                     static_cast<const cx<T>*>(Dh), p.nb, p.b_lo, p.Nx, p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu,
+                     static_cast<const cx<T>*>(Dh), pitch, p.nb, p.b_lo, p.Nx, p.Ny, p.Nz, p.s_per_k, p.kxu, p.kyu, p.kzu,
                      p.n0_over_nt, p.adj_scale, deriv, p.w_t, p.hdeg, static_cast<const T*>(p.hcoef), cpg,
                      scatter_first_table<T>(p) ? 1 : 0, p.jrange, static_cast<cx<T>*>(Gh));
   return hipGetLastError();
@@ -619,7 +618,7 @@ hipError_t launch_gather_batch(const BatchStage& st, const BatchIO& io, hipStrea
   template hipError_t launch_gather_x<T>(const DevPlan&, const void*, void*, int, hipStream_t); \
   template void gather_shape<T>(const DevPlan&, int&, Fft2Raw&, size_t&);               \
   template size_t scatter_lds_bytes<T>(const DevPlan&);                                  \
-  template hipError_t launch_scatter<T>(const DevPlan&, const void*, void*, int, hipStream_t); \
+  template hipError_t launch_scatter<T>(const DevPlan&, const void*, int, void*, int, hipStream_t); \
   template hipError_t launch_gather_batch<T>(const BatchStage&, const BatchIO&, hipStream_t);
 PATK_INST(float)
 PATK_INST(double)

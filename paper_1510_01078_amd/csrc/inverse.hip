@@ -16,24 +16,31 @@ namespace patk {
 // model's transforms (below) keep the plane and the passes in LDS.
 // ---------------------------------------------------------------------------
 
-// Two-pass register transform along y, in place: each pass's threads walk the
-// S z modes of one y mode (one line of 128 bytes where S = 16). Bound by HBM.
+// Two-pass register transform along x or y, in place: each pass's threads walk
+// the nl <= S z modes at `base`, element e of mode s at base[e * stride + s]
+// (one line of 128 bytes where S = 16). Bound by HBM.
+template <typename T, int CLS, bool INV>
+__device__ __forceinline__ void cfft_reg_body(cx<T>* __restrict__ base, unsigned stride, int nl, const Fft2<T>& f,
+                                              int tid) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
+  const int s = tid & ((1 << f.ls) - 1), i = tid >> f.ls;
+  const bool in = s < nl;
+  cx<T>* b = base + s;
+  if (in && i < f.r2)
+    reg_first_any<T, CLS, INV>(f, buf + s * f.P, i, [&](int e) { return cx_at(b, unsigned(e) * stride); });
+  __syncthreads();
+  if (in && i < f.r1)
+    reg_second_any<T, CLS, INV>(f, buf + s * f.P, i,
+                                [&](int q, cx<T> v) { cx_at(b, unsigned(i + q * f.r1) * stride) = v; });
+}
+
 template <typename T, int CLS>
 __device__ __forceinline__ void cfft_y_reg_body(cx<T>* __restrict__ F, int Lz, int pitch, const Fft2<T>& f, int bx,
                                                 int jj, int tid) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
-  const int S = 1 << f.ls;
   const int l0 = bx << f.ls;
-  const int s = tid & (S - 1), i = tid >> f.ls;
-  const bool in = s < min(S, Lz - l0);
-  cx<T>* base = F + size_t(jj) * (f.r1 * f.r2) * pitch + l0 + s;  // y mode kk at base[kk * pitch]
-  if (in && i < f.r2)
-    reg_first_any<T, CLS, true>(f, buf + s * f.P, i, [&](int e) { return cx_at(base, unsigned(e * pitch)); });
-  __syncthreads();
-  if (in && i < f.r1)
-    reg_second_any<T, CLS, true>(f, buf + s * f.P, i,
-                                 [&](int q, cx<T> v) { cx_at(base, unsigned((i + q * f.r1) * pitch)) = v; });
+  cfft_reg_body<T, CLS, true>(F + size_t(jj) * (f.r1 * f.r2) * pitch + l0, unsigned(pitch),
+                              min(1 << f.ls, Lz - l0), f, tid);
 }
 
 template <typename T, int CLS>
@@ -42,6 +49,61 @@ __global__ __launch_bounds__(kInvYThreads, (reg_waves<T, CLS>())) void k_cfft_y_
   // neighbouring groups share the 128-byte lines of the z runs: keep them on one XCD
   const int gl = xcd_linear();
   cfft_y_reg_body<T, CLS>(F, Lz, pitch, as_fft2<T>(f), gl % gridDim.x, gl / gridDim.x, threadIdx.x);
+}
+
+// Forward model: element stride and stride of the other axis' index (the grid's y)
+template <typename T, int CLS>
+__global__ __launch_bounds__(kInvYThreads, (reg_waves<T, CLS>())) void k_cfft_fwd_reg(cx<T>* __restrict__ F, int Lz,
+                                                                                     unsigned stride, unsigned other,
+                                                                                     Fft2Raw f) {
+  const int gl = xcd_linear();
+  const int by = gl / int(gridDim.x), l0 = (gl - by * int(gridDim.x)) << f.ls;
+  cfft_reg_body<T, CLS, false>(F + size_t(by) * other + l0, stride, min(1 << f.ls, Lz - l0), as_fft2<T>(f),
+                               threadIdx.x);
+}
+
+// Forward model's real-to-complex z pass: two real rows share one complex
+// transform, Z = FFT(x0 + i x1), loaded as the first pass's inputs; from its
+// natural order in LDS X0[l] = (Z[l] + conj Z[-l])/2 and X1[l] = (Z[l] - conj
+// Z[-l])/(2i), l < Nz/2 (the transposed interpolation reads no l = Nz/2).
+template <typename T, int CLS>
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_r2c_reg(const T* __restrict__ in,
+                                                                               long long nrows, int pitch, Fft2Raw fr,
+                                                                               cx<T>* __restrict__ D) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
+  const Fft2<T> f = as_fft2<T>(fr);
+  const int tid = threadIdx.x;
+  const int Nz = f.r1 * f.r2, Lz = Nz / 2;
+  const long long r0 = (long long)blockIdx.x * (2 << f.ls);
+  const int nr = (int)min((long long)(2 << f.ls), nrows - r0);
+  const int np = (nr + 1) / 2;
+  int s = small_div(tid, f.r2), i = tid - s * f.r2;
+  if (s < np) {
+    const T* row = in + (r0 + 2 * s) * Nz;
+    const bool two = 2 * s + 1 < nr;
+    const int next = two ? Nz : 0;
+    reg_first_any<T, CLS, false>(f, buf + s * f.P, i, [&](int e) {
+      const T a = row[e], c = row[e + next];
+      return cx<T>{a, two ? c : T(0)};
+    });
+  }
+  __syncthreads();
+  s = small_div(tid, f.r1);
+  i = tid - s * f.r1;
+  {
+    cx<T>* seq = buf + s * f.P;
+    reg_second_in_lds_any<T, CLS, false>(f, seq + i * f.Q, s < np, [&](int q, cx<T> v) { seq[i + q * f.r1] = v; });
+  }
+  __syncthreads();
+  const FastDiv div_lz(Lz);
+  for (int q = tid; q < nr * Lz; q += blockDim.x) {
+    const int r = div_lz(q), l = q - r * Lz;
+    const cx<T>* seq = buf + (r >> 1) * f.P;
+    const cx<T> z = seq[l], zm = seq[l == 0 ? 0 : Nz - l];
+    D[(r0 + r) * pitch + l] = (r & 1) ? cx<T>{T(0.5) * (z.y + zm.y), T(-0.5) * (z.x - zm.x)}
+                                      : cx<T>{T(0.5) * (z.x + zm.x), T(0.5) * (z.y - zm.y)};
+  }
 }
 
 // Two-pass register transform of pairs of rows along z to real: two real rows
@@ -308,7 +370,7 @@ __global__ __launch_bounds__(kFftThreads) void k_c2r_z(const cx<T>* __restrict__
 // registers of one sequence per row).
 template <typename T, int NCT>
 __global__ __launch_bounds__(kFftThreads) void k_r2c_z(const T* __restrict__ f, long long nrows, int rows,
-                                                     FftDesc<T> fd, cx<T>* __restrict__ D) {
+                                                     FftDesc<T> fd, cx<T>* __restrict__ D, int pitch, int modes) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
@@ -360,7 +422,11 @@ __global__ __launch_bounds__(kFftThreads) void k_r2c_z(const T* __restrict__ f, 
         return (r & 1) ? cx<T>{T(0.5) * (z.y + zm.y), T(-0.5) * (z.x - zm.x)}
                        : cx<T>{T(0.5) * (z.x + zm.x), T(0.5) * (z.y - zm.y)};
       },
-      [&](int q, cx<T> v) { D[r0 * Lh + q] = v; });
+      [&](int q, cx<T> v) {
+        const int r = div_lh(q);
+        const int l = q - r * Lh;
+        if (l < modes) D[(r0 + r) * pitch + l] = v;
+      });
 }
 
 // Forward model: in-place transforms of the half spectrum along y, then x.
@@ -445,26 +511,79 @@ hipError_t launch_inverse(const DevPlan& p, void* Fh, T* f, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Real-to-complex z pass with its passes in LDS: `modes` z modes of each row to
+// rows of `pitch`.
 template <typename T>
-hipError_t launch_forward3d(const DevPlan& p, const T* f, void* Dh, hipStream_t s) {
-  cx<T>* D = static_cast<cx<T>*>(Dh);
+static hipError_t launch_r2c_z(const DevPlan& p, const T* f, cx<T>* D, int pitch, int modes, hipStream_t s) {
   const FftCfg cfg = inv_cfg();
   const int rows = fft_batch<T>(p.Nz, cfg.threads, cfg.cap);
   const size_t lds = size_t(c2r_lds_slots(rows, p.Nz)) * sizeof(cx<T>);  // (rows + 1) / 2 sequences
   const long long nrows = (long long)p.Nx * p.Ny;
   if ((rows + 1) / 2 * p.Nz > kFftMaxV * cfg.threads || rows * (p.Nz / 2 + 1) > kFftMaxV * cfg.threads)
     return hipErrorInvalidValue;
-  hipError_t e = ct_pick(CtInverse{}, p.Nz, [&](auto c) {
+  return ct_pick(CtInverse{}, p.Nz, [&](auto c) {
     hipError_t e2 = allow_lds(reinterpret_cast<const void*>(&k_r2c_z<T, decltype(c)::value>), lds);
     if (e2 != hipSuccess) return e2;
     hipLaunchKernelGGL((k_r2c_z<T, decltype(c)::value>), dim3((unsigned)((nrows + rows - 1) / rows)),
-                       dim3(cfg.threads), lds, s, f, nrows, rows, as_desc<T>(p.f_Nz), D);
+                       dim3(cfg.threads), lds, s, f, nrows, rows, as_desc<T>(p.f_Nz), D, pitch, modes);
     return hipGetLastError();
   });
+}
+
+template <typename T>
+hipError_t launch_forward3d(const DevPlan& p, const T* f, void* Dh, hipStream_t s) {
+  cx<T>* D = static_cast<cx<T>*>(Dh);
+  const int Lh = p.Nz / 2 + 1;
+  hipError_t e = launch_r2c_z<T>(p, f, D, Lh, Lh, s);
   if (e != hipSuccess) return e;
   return launch_forward_xy<T>(p, D, s);
 }
 
+
+// The forward transforms as register passes: Dh[jj][kk][l], l < Nz/2, rows of
+// pitch_f; every axis of a length with two passes.
+template <typename T>
+hipError_t launch_forward3d_reg(const DevPlan& p, const T* f, void* Dh, hipStream_t s) {
+  if (!p.f_Nx.two.r1 || !p.f_Ny.two.r1 || !p.f_Nz.two.r1) return hipErrorInvalidValue;
+  cx<T>* D = static_cast<cx<T>*>(Dh);
+  const int Lz = p.Nz / 2;
+  const long long nrows = (long long)p.Nx * p.Ny;
+  const Fft2Raw z = fft2_shape<T>(p.f_Nz, fft_seqs<T>(p.f_Nz, kFftThreads, kC2rSeqs));
+  const size_t lds_z = fft2_slots(z) * sizeof(cx<T>);
+  // the lengths with a compile-time form stay with it in the z pass (256^3:
+  // 28 us, 40 us as register passes; 80 points: 9.8 and 6.0 us)
+  bool fixed = false;
+  (void)ct_pick(CtInverse{}, p.Nz, [&](auto c) {
+    fixed = decltype(c)::value > 0;
+    return hipSuccess;
+  });
+  hipError_t e = fixed ? launch_r2c_z<T>(p, f, D, p.pitch_f, Lz, s) : class_pick(z, [&](auto c) {
+    constexpr auto kern = &k_r2c_reg<T, decltype(c)::value>;
+    hipError_t e2 = allow_lds(reinterpret_cast<const void*>(kern), lds_z);
+    if (e2 != hipSuccess) return e2;
+    const long long rows = 2LL << z.ls;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((nrows + rows - 1) / rows)), dim3(fft2_threads(z)), lds_z, s, f, nrows,
+                       p.pitch_f, z, D);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  auto pass = [&](const FftRaw& raw, unsigned stride, unsigned other, int count) {
+    const Fft2Raw t = fft2_shape<T>(raw, fft_seqs<T>(raw, kInvYThreads, kInvCap));
+    const size_t lds = fft2_slots(t) * sizeof(cx<T>);
+    return class_pick(t, [&](auto c) {
+      constexpr auto kern = &k_cfft_fwd_reg<T, decltype(c)::value>;
+      hipError_t e2 = allow_lds(reinterpret_cast<const void*>(kern), lds);
+      if (e2 != hipSuccess) return e2;
+      hipLaunchKernelGGL(kern, dim3((Lz + (1 << t.ls) - 1) >> t.ls, count), dim3(fft2_threads(t)), lds, s, D, Lz, stride,
+                         other, t);
+      return hipGetLastError();
+    });
+  };
+  const unsigned row = unsigned(p.pitch_f), slab = unsigned(p.Ny) * row;
+  e = pass(p.f_Ny, row, slab, p.Nx);
+  if (e != hipSuccess) return e;
+  return pass(p.f_Nx, slab, row, p.Ny);
+}
 
 // Batched forms of the inverse passes (one variant of problems per launch, as
 // the lateral passes).
@@ -531,6 +650,7 @@ hipError_t launch_c2r_z_batch(const BatchStage& st, const BatchIO& io, hipStream
 #define PATK_INST(T)                                                                \
   template hipError_t launch_inverse<T>(const DevPlan&, void*, T*, hipStream_t); \
   template hipError_t launch_forward3d<T>(const DevPlan&, const T*, void*, hipStream_t); \
+  template hipError_t launch_forward3d_reg<T>(const DevPlan&, const T*, void*, hipStream_t); \
   template hipError_t launch_cfft_y_inv_batch<T>(const BatchStage&, const BatchIO&, hipStream_t); \
   template hipError_t launch_c2r_z_batch<T>(const BatchStage&, const BatchIO&, hipStream_t);
 PATK_INST(float)

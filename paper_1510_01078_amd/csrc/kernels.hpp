@@ -161,9 +161,11 @@ void gather_shape(const DevPlan& p, int& lchunk, Fft2Raw& f2, size_t& slots);
 // Forward model. f -> Dh (real-to-complex along z, forward FFTs along y, x)
 template <typename T>
 hipError_t launch_forward3d(const DevPlan& p, const T* f, void* Dh, hipStream_t s);
-// Dh -> Gh' (deriv 0: A; 1: d/dx_m; 2: d/dy_m); LDS bytes it needs
 template <typename T>
-hipError_t launch_scatter(const DevPlan& p, const void* Dh, void* Gh, int deriv, hipStream_t s);
+hipError_t launch_forward3d_reg(const DevPlan& p, const T* f, void* Dh, hipStream_t s);
+// Dh (rows of `pitch` z modes) -> Gh' (deriv 0: A; 1: d/dx_m; 2: d/dy_m); LDS bytes it needs
+template <typename T>
+hipError_t launch_scatter(const DevPlan& p, const void* Dh, int pitch, void* Gh, int deriv, hipStream_t s);
 template <typename T>
 size_t scatter_lds_bytes(const DevPlan& p);
 // Gh'[j][k][b] -> V'[b][j][py]

@@ -129,6 +129,25 @@ def test_forward_lengths_vs_oracle(dev, nx, ny, nz, width):
     assert err <= tol and gap <= 1e-5 * scale
 
 
+@pytest.mark.parametrize("nx,ny,nz", [(54, 50, 54), (8, 18, 128), (20, 16, 400), (288, 6, 30), (16, 162, 10),
+                                      (320, 20, 20), (6, 8, 640), (4, 6, 648)])
+def test_forward_image_lengths_vs_oracle(dev, nx, ny, nz):
+    """The forward model's transforms of the image: each class per axis, rows
+    that are no multiple of a group's, a z length with a compile-time form, the
+    longest z rows and the first past the range."""
+    from oracle import forward_model as fm
+    from paper_1510_01078_amd import Plan
+    p = _problem(2 * nx, 2 * ny, 2.0, nz)
+    f = np.random.default_rng(nx + nz).standard_normal(p.shape)
+    ref = fm.forward(f, p.xy, p.nt, p.dt, p.c, p.extent)
+    for precision, tol in (("fp32", 1e-5), ("fp64", 1e-6)):
+        pl = Plan(p.xy, p.nt, p.dt, p.c, p.shape, p.extent, sensor_h=p.h, precision=precision, **_kw(2.0))
+        err = rel_l2(pl.forward(torch.from_numpy(f).to(dev, pl.dtype)).cpu().numpy().astype(np.float64), ref)
+        pl.close()
+        _say(f"[gpu] forward image {nx} x {ny} x {nz} {precision}: {err:.2e}")
+        assert err <= tol
+
+
 def test_batch_of_all_classes_equals_single(dev):
     from paper_1510_01078_amd import Plan
     from paper_1510_01078_amd.batch import Batch, problem_dict
