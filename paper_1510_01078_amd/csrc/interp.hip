@@ -259,8 +259,9 @@ static hipError_t launch_fused_wvs(const DevPlan& p, const void* V, void* Gt, hi
   hipError_t e = allow_lds(reinterpret_cast<const void*>(&k_fft_x_interp<T, W, MAXV, NCT, FS>), lds);
   if (e != hipSuccess) return e;
   const long long strips = (p.tiles_y + FS - 1) / FS;
+  static std::atomic<unsigned long long> memo{0};
   const int bins = fused_bins(reinterpret_cast<const void*>(&k_fft_x_interp<T, W, MAXV, NCT, FS>), kFusedThreads * FS,
-                              lds, strips, p.nb, p.tiles_y);
+                              lds, strips, p.nb, p.tiles_y, memo);
   const int nchunks = (p.nb + bins - 1) / bins;
   const long long blocks = strips * nchunks;
   hipLaunchKernelGGL((k_fft_x_interp<T, W, MAXV, NCT, FS>), dim3((unsigned)blocks), dim3(kFusedThreads * FS), lds, s,

@@ -137,7 +137,9 @@ static hipError_t launch_reg_wcs(const DevPlan& p, const void* V, void* Gt, hipS
   hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
   if (e != hipSuccess) return e;
   const long long strips = (p.tiles_y + FS - 1) / FS;
-  const int bins = fused_bins(reinterpret_cast<const void*>(kern), reg_threads<CLS, FS>(), lds, strips, p.nb, p.tiles_y);
+  static std::atomic<unsigned long long> memo{0};
+  const int bins =
+      fused_bins(reinterpret_cast<const void*>(kern), reg_threads<CLS, FS>(), lds, strips, p.nb, p.tiles_y, memo);
   const int nchunks = (p.nb + bins - 1) / bins;
   hipLaunchKernelGGL(kern, dim3((unsigned)(strips * nchunks)), dim3(reg_threads<CLS, FS>()), lds, s,
                      static_cast<const cx<T>*>(V), p.nb, p.pitch_v, p.Nx, p.n_y, p.tiles_x, nchunks, bins, p.home_off,

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 
 #include "kernels_common.hpp"
@@ -81,16 +82,26 @@ __device__ __forceinline__ cx<T> fused_sensor_sum(const FusedSensor<T, W>& f, co
 // fullest (the groups take about equal time, and a part-filled last wave idles
 // the rest of the device: 0.98 -> 0.965 ms per forward call with 576 bins on a
 // 384^2 grid, 7 bins instead of 6).
-static inline int fused_bins(const void* kern, int threads, size_t lds, long long strips, int nb, int tiles_y) {
+// `memo`, one per kernel, holds the last answer of the occupancy query: device,
+// LDS bytes and resident groups in one word.
+static inline int fused_bins(const void* kern, int threads, size_t lds, long long strips, int nb, int tiles_y,
+                             std::atomic<unsigned long long>& memo) {
   int bins = int(std::min<long long>(kFusedBins, std::max<long long>(1, (long long)tiles_y * nb / 2048)));
-  int dev = 0, per_cu = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
-    (void)hipGetLastError();
-    return bins;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return bins;
+  const unsigned long long key = (unsigned long long)(dev & 0xffff) << 48 | (unsigned long long)(lds & 0xffffff) << 24;
+  unsigned long long word = memo.load(std::memory_order_relaxed);
+  if ((word >> 24) != (key >> 24) || !(word & 0xffffff)) {
+    int per_cu = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+      (void)hipGetLastError();
+      return bins;
+    }
+    word = key | (unsigned long long)std::max(1, per_cu * cus);
+    memo.store(word, std::memory_order_relaxed);
   }
-  const long long slots = std::max(1, per_cu * cus);
+  const long long slots = (long long)(word & 0xffffff);
   if (strips * ((nb + 3) / 4) >= 2 * slots) {
     double best = -1.0;
     for (int bb = 4; bb <= kFusedBins; ++bb) {
