@@ -374,6 +374,28 @@ __device__ __forceinline__ void reg_in_lds(const cx<T>* src, int stride, bool ac
   }
 }
 
+// Middle pass of three: the same in place (output k to dst[k*QB]), times the
+// twiddles tw[k*step], which are loaded beside the values: after the barrier
+// every wave of the group waited for them at once (sixteen uneven problems'
+// temporal FFTs 404 us, 353 us so).
+template <typename T, int R, bool INV>
+__device__ __forceinline__ void reg_mid(const cx<T>* src, int stride, bool active, const cx<T>* __restrict__ tw,
+                                        int step, cx<T>* dst, int QB) {
+  cx<T> v[R], w[R];
+  if (active) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) w[r] = tw[r * step];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = src[r * stride];
+    RDft<T, R, INV>::run(v);
+  }
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) dst[r * QB] = twiddle<T, INV>(v[r], w[r]);
+  }
+}
+
 // Radix by a uniform switch over those of the class (the host's table of
 // factorisations, two_pass_plan, pairs no others).
 #define PATK_RADICES_16(X) X(2) X(3) X(4) X(5) X(6) X(8) X(9) X(10) X(12) X(15) X(16)
@@ -406,9 +428,10 @@ __device__ __forceinline__ void three_first_any(const Fft3<T>& f, cx<T>* seq, in
 #undef PATK_CASE
 }
 
-template <typename T, int CLS, bool INV, typename Store>
-__device__ __forceinline__ void three_mid_any(const Fft3<T>& f, const cx<T>* src, bool active, Store st) {
-#define PATK_CASE(R) case R: reg_in_lds<T, R, INV>(src, f.r3, active, st); break;
+template <typename T, int CLS, bool INV>
+__device__ __forceinline__ void three_mid_any(const Fft3<T>& f, cx<T>* row, int i2, bool active) {
+#define PATK_CASE(R) \
+  case R: reg_mid<T, R, INV>(row + i2, f.r3, active, f.twB + i2, f.r3, row + i2, f.QB); break;
   if constexpr (CLS == 16) {
     switch (f.r2) { PATK_THREE_B16(PATK_CASE) default: break; }
   } else if constexpr (CLS == 20) {

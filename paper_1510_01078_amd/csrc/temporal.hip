@@ -91,16 +91,13 @@ __device__ __forceinline__ void temporal_reg_body(const T* __restrict__ g, int M
   } else {
     bool on = split(tid, f.r1 * f.r3, s, i);
     {
-      const int k1 = i / f.r3, i2 = i - k1 * f.r3;
+      const int k1 = small_div(i, f.r3), i2 = i - k1 * f.r3;
       seq = buf + s * f.P;
-      cx<T>* row = seq + k1 * f.QA;
-      three_mid_any<T, CLS, false>(f, row + i2, on, [&](int k2, cx<T> v) {
-        row[k2 * f.QB + i2] = twiddle<T, false>(v, f.twB[k2 * f.r3 + i2]);
-      });
+      three_mid_any<T, CLS, false>(f, seq + k1 * f.QA, i2, on);
     }
     __syncthreads();
     on = split(tid, f.r1 * f.r2, s, i);
-    const int k2 = i / f.r1, k1 = i - k2 * f.r1;
+    const int k2 = small_div(i, f.r1), k1 = i - k2 * f.r1;
     seq = buf + s * f.P;
     three_last_any<T, CLS, false>(f, seq + k1 * f.QA + k2 * f.QB, on,
                                   [&](int q, cx<T> v) { keep(k1 + f.r1 * (k2 + f.r2 * q), v); });
@@ -250,7 +247,8 @@ hipError_t launch_temporal(const DevPlan& p, const T* g, void* Gt, bool weighted
 // writes distinct slots.
 // ---------------------------------------------------------------------------
 template <typename T, int NCT>
-__global__ __launch_bounds__(temporal_threads<NCT>()) void k_temporal_t(const cx<T>* __restrict__ Gt, int M, int Nt, int n0,
+__global__ __launch_bounds__(temporal_threads<NCT>()) void k_temporal_t(const cx<T>* __restrict__ Gt, int M, int Nt,
+                                                                        int n0,
                                                                const T* __restrict__ deap, FftDesc<T> fd, int b_lo,
                                                                int nb, T* __restrict__ g) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
