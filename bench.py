@@ -57,14 +57,15 @@ def spread_bytes(plan, p, eb):
     """Algorithmic bytes of one spread launch: read the per-sensor band values,
     write the oversampled grid once, read the packed slot tables once (per
     slot: 64 lane weights and 4 sensor ids; per round of 8 slots one 32-bit
-    place word per lane, 32 bytes per slot) and the patch offsets."""
+    place word per lane, 32 bytes per slot) and 16 bytes per patch (its number
+    and range of slots)."""
     info = plan.info
     nb, nxo, nyo = info["band_bins"], info["nx_over"], info["ny_over"]
     m = p.m
     read_bins = m * nb * 2 * eb
     write_grid = nb * nxo * nyo * 2 * eb
     patches = -(-nxo // 16) * -(-nyo // 4)
-    tables = info["spread_slots"] * (64 * eb + 32 + 4 * 4) + 4 * (patches + 1)
+    tables = info["spread_slots"] * (64 * eb + 32 + 4 * 4) + 16 * patches
     return read_bins + write_grid + tables
 
 
@@ -79,13 +80,13 @@ def stage_bytes(plan, p, eb):
     pairs = info["band_pairs"]
     Nx, Ny, Nz = p.shape
     c = 2 * eb
-    lh = Nz // 2 + 1
+    lh = Nz // 2  # the plane l = Nz/2 is zero and not stored
     return [
         p.m * p.nt * eb + p.m * nb * c,                       # temporal: traces in, band out
         spread_bytes(plan, p, eb),                            # spread
         nb * nyo * nxo * c + pairs * nyo * c,                 # FFT along x with crop (band pairs written)
-        pairs * nyo * c + pairs * Ny * c,                     # FFT along y, crop, deconvolve (ranges only)
-        pairs * Ny * c + Nx * Ny * lh * c,                    # gather + weight + inverse x pass (one write)
+        pairs * nyo * c + pairs * Ny * c,                     # FFT along y, crop (ranges only)
+        pairs * Ny * c + Nx * Ny * lh * c,                    # gather, deconvolve, weight, inverse x pass
         3 * Nx * Ny * lh * c + Nx * Ny * Nz * eb,             # inverse y pass (read + write), z pass (read, write f)
     ]
 
@@ -140,7 +141,7 @@ def bench_batch(args, dev):
     """32 uneven problems (Ns ~ U{24..96}, Nt ~ U{512..2048}, 64^3..192^3),
     each with the window setting the autotuner picks for it (oversampling in
     {1.25, 1.5, 2}, widths in {6, 8, 12}, FP32 within 1e-5 with half of it as
-    margin): one batched call (seven launches), the same call replayed from a
+    margin): one batched call (seven stages), the same call replayed from a
     HIP graph, and the 32 problems one plan after another with the same
     settings."""
     import torch

@@ -228,8 +228,8 @@ pat_status pat_forward_dxy(pat_plan* plan, const void* f, int32_t axis, void* g,
  * Batched reconstruction: count (1..64) independent problems, each with its
  * own descriptor (geometry, trace length, output grid, window settings; all
  * with the same element type), reconstructed with one kernel launch per
- * stage for the whole batch: every stage's work items are the blocks of all
- * problems, so small problems share the device instead of running one after
+ * stage and class of FFT lengths for the whole batch: a launch's work items
+ * are the blocks of all its problems, so small problems share the device instead of running one after
  * another. Results equal pat_reconstruct's for each problem bit for bit.
  *
  * Problems are run in groups of at most 32 (one group per 32 problems by
@@ -238,7 +238,8 @@ pat_status pat_forward_dxy(pat_plan* plan, const void* f, int32_t axis, void* g,
  * stay within group_bytes (meant for handing each stage's output to the next
  * through the last-level cache; on MI355X this measured slower than one
  * group, so 0, no budget, is the default). Groups run one after another
- * (a launch per stage; one per class of FFT length in the lateral FFTs) and share one workspace (the largest group's).
+ * (a launch per stage, or one per class of FFT lengths) and share one
+ * workspace (the largest group's).
  *
  * pat_batch_create builds one plan per descriptor (as nufft_plan), uploads
  * per-group argument tables and allocates the workspace through descs[0]'s
@@ -264,8 +265,8 @@ pat_status pat_batch_set_grid(pat_batch* batch, int32_t blocks);
 
 /* f[p] = R g[p] for every problem p: g and f are HOST arrays of `count`
  * DEVICE pointers with the layouts of pat_reconstruct. Enqueues a kernel per
- * stage and group on `stream` (two to four for the lateral FFTs where the
- * problems' lengths fall into several classes; no allocation, no synchronisation), so the call can
+ * stage and group on `stream` (up to four where the problems' FFT lengths fall
+ * into several classes); no allocation, no synchronisation, so the call can
  * be captured into a HIP graph. Inputs and outputs must not overlap. */
 pat_status pat_batch_reconstruct(pat_batch* batch, const void* const* g, void* const* f, void* stream);
 

@@ -2,7 +2,7 @@
 
 A Batch holds up to 64 independent problems (own sensors, trace length,
 grid and window settings; one precision) and reconstructs all of them with
-one launch per stage (pat_batch_reconstruct).
+one launch per stage and class of FFT lengths (pat_batch_reconstruct).
 """
 from __future__ import annotations
 

@@ -1,9 +1,9 @@
 // Batched reconstruction: up to kBatchMax independent problems (each its own
 // sensor geometry, trace length and output grid) reconstructed with one
-// launch per stage and group of problems. Every stage's work items are the
-// blocks of the group's problems (problem after problem); per-problem
-// arguments are uploaded once at creation, so a call only enqueues eight
-// kernels per group.
+// launch per stage, kernel variant and group of problems. A stage's work items
+// are the blocks of the variant's problems (problem after problem);
+// per-problem arguments are uploaded once at creation, so a call only enqueues
+// seven stages of one to four kernels per group.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -128,7 +128,8 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     if (d.n_t > patk::kFftMaxV * 512) return PAT_ERR_UNSUPPORTED;
     // stage 0: temporal FFT, a block per sensor pair or a few
     const patk::Fft3Raw f0 = patk::temporal_shape<T>(d);
-    a0[p] = patk::TemporalBA{d.hw, d.deap, patk::as_view(d.f_nt), f0, d.M, d.Nt, d.n0, d.b_lo, d.nb, d.pitch_t, C, p, 0};
+    a0[p] = patk::TemporalBA{d.hw, d.deap, patk::as_view(d.f_nt), f0, d.M, d.Nt, d.n0, d.b_lo, d.nb, d.pitch_t, C, p,
+                             0};
     pre[0][p] = ((d.M + 1) / 2 + (1 << f0.ls) - 1) >> f0.ls;
     lds[0][p] = (f0.r1 ? size_t(f0.P) << f0.ls : size_t(patk::temporal_lds_slots(d.n_t))) * c;
     variant[0][p] = f0.r1 ? patk::three_class(f0) + 64 * (f0.r3 == 1 ? 1 : patk::fft3_rounds(f0) ? 2 : 0) : 0;
@@ -145,7 +146,8 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     const patk::Fft2Raw fx = d.f_nx.two.r1 ? patk::fft2_shape<T>(d.f_nx, rows) : d.f_nx.two;
     if (!fx.r1 && (rows * d.n_x > kFft || rows * d.Nx > kFft)) return PAT_ERR_UNSUPPORTED;
     const int gx2 = (d.n_y + rows - 1) / rows;
-    a2[p] = patk::FftXBA{A, patk::as_view(d.f_nx), fx, d.n_y, d.Nx, rows, gx2, d.pitch_u, d.pitch_v, Bw, d.jrange ? d.brange : nullptr};
+    a2[p] = patk::FftXBA{A, patk::as_view(d.f_nx), fx, d.n_y, d.Nx, rows, gx2, d.pitch_u, d.pitch_v, Bw,
+                         d.jrange ? d.brange : nullptr};
     pre[2][p] = gx2 * d.nb;
     lds[2][p] = (fx.r1 ? patk::fft2_slots(fx) : size_t(rows) * patk::lseq(d.n_x) + d.n_x) * c;
     variant[2][p] = fx.r1 ? patk::reg_class(fx) : 0;

@@ -116,7 +116,8 @@ enum { MODE_IMAGE = 0, MODE_PHYSICAL = 1, MODE_ADJOINT = 2 };
 // phihat_y) of the column (even in j and k, so it holds for both terms of
 // MODE_ADJOINT).
 template <typename T, int MODE, int WT = 0>
-__device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
+__device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx,
+                                              int Ny, int Nz,
                                               double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                               double n0_over_nt, double scale, int wt, int deg,
                                               const T* __restrict__ hcoef, int jj, int kk, int l,
@@ -178,7 +179,8 @@ __device__ __forceinline__ cx<T> gather_point(const cx<T>* __restrict__ Gh, int 
 }
 
 template <typename T, int MODE, int WT = 0>
-__device__ __forceinline__ void gather_body(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
+__device__ __forceinline__ void gather_body(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny,
+                                            int Nz,
                                             double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                             double n0_over_nt, double scale, int wt, int deg,
                                             const T* __restrict__ hcoef, const T* __restrict__ dcx,
@@ -192,12 +194,14 @@ __device__ __forceinline__ void gather_body(const cx<T>* __restrict__ Gh, int nb
   const long long col = idx / Lh;
   const int kk = int(col % Ny);
   const int jj = int(col / Ny);
-  Fh[idx] = gather_point<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt,
+  Fh[idx] = gather_point<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt,
+                                      scale, wt,
                                       deg, hcoef, jj, kk, l, double(dcx[jj]) * double(dcy[kk]), coefs);
 }
 
 template <typename T, int MODE, int WT>
-__global__ __launch_bounds__(256) void k_gather(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx, int Ny, int Nz,
+__global__ __launch_bounds__(256) void k_gather(const cx<T>* __restrict__ Gh, int nb, int pitch, int b_lo, int Nx,
+                                                int Ny, int Nz,
                                                 double s_per_k, double kxu, double kyu, double kzu, double two_c,
                                                 double n0_over_nt, double scale, int wt, int deg,
                                                 const T* __restrict__ hcoef, const T* __restrict__ dcx,
@@ -205,7 +209,8 @@ __global__ __launch_bounds__(256) void k_gather(const cx<T>* __restrict__ Gh, in
   __shared__ T coefs[kMaxTapCoefs];
   stage_tap_coefs<T, WT>(coefs, hcoef, deg);
   __syncthreads();
-  gather_body<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg, hcoef,
+  gather_body<T, MODE, WT>(Gh, nb, pitch, b_lo, Nx, Ny, Nz, s_per_k, kxu, kyu, kzu, two_c, n0_over_nt, scale, wt, deg,
+                           hcoef,
                            dcx, dcy, Fh, blockIdx.x, coefs);
 }
 
@@ -395,7 +400,8 @@ hipError_t launch_gather(const DevPlan& p, const void* Gh, void* Fh, int mode, h
 // per-l phase keeps its threads busy.
 // ---------------------------------------------------------------------------
 template <typename T, int WT>
-__global__ __launch_bounds__(256) void k_scatter(const cx<T>* __restrict__ Dh, int pitch, int nb, int b_lo, int Nx, int Ny, int Nz,
+__global__ __launch_bounds__(256) void k_scatter(const cx<T>* __restrict__ Dh, int pitch, int nb, int b_lo, int Nx,
+                                                 int Ny, int Nz,
                                                  double s_per_k, double kxu, double kyu, double kzu, double n0_over_nt,
                                                  double scale, int deriv, int wt, int deg, const T* __restrict__ hcoef,
                                                  int cols_per_group, int first_table, const int* __restrict__ jrange,

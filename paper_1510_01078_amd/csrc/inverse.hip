@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_c2r_reg(
   c2r_reg_body<T, CLS>(F, nrows, pitch, as_fft2<T>(f), out, blockIdx.x, threadIdx.x);
 }
 
-template <typename T, bool INV, int NCT = 0>
+template <typename T, int NCT>
 __device__ __forceinline__ void cfft_x_body(cx<T>* __restrict__ F, int Ny, int Lh, int lchunk,
                                             FftDesc<T> fd, int wm, int bx, int by) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -195,7 +195,7 @@ __device__ __forceinline__ void cfft_x_body(cx<T>* __restrict__ F, int Ny, int L
         [&](int jj, int li, int, cx<T> v) { buf[li * BS + lpos(jj)] = v; });
     for (int t = tid; t < NCT; t += kFftThreads) twl[t] = fd.tw[t];
     __syncthreads();
-    fft_ct<T, NCT, kFftThreads, ROWS, INV>(buf, nl, twl, tid);
+    fft_ct<T, NCT, kFftThreads, ROWS, false>(buf, nl, twl, tid);
     __syncthreads();
     staged_cols<ROWS, kFftThreads, U>(
         NCT, nl, tid, [&](int jj, int li, int) { return buf[li * BS + lpos(jj)]; },
@@ -214,7 +214,7 @@ __device__ __forceinline__ void cfft_x_body(cx<T>* __restrict__ F, int Ny, int L
         });
     for (int t = tid; t < fd.n; t += nthr) twl[t] = fd.tw[t];
     __syncthreads();
-    fft_group<T, INV>(buf, lds_twiddles(fd, twl), nl, bstride, tid, nthr, wm);
+    fft_group<T, false>(buf, lds_twiddles(fd, twl), nl, bstride, tid, nthr, wm);
     __syncthreads();
     staged_copy<kFftMaxV>(
         nl * Nx, tid, nthr,
@@ -229,12 +229,12 @@ __device__ __forceinline__ void cfft_x_body(cx<T>* __restrict__ F, int Ny, int L
   }
 }
 
-template <typename T, bool INV, int NCT>
+template <typename T, int NCT>
 __global__ __launch_bounds__(kFftThreads) void k_cfft_x(cx<T>* __restrict__ F, int Ny, int Lh, int lchunk,
                                                       FftDesc<T> fd, int wm) {
   // neighbouring groups share the 128-byte lines of the z runs: keep them on one XCD
   const int gl = xcd_linear();
-  cfft_x_body<T, INV, NCT>(F, Ny, Lh, lchunk, fd, wm, gl % gridDim.x, gl / gridDim.x);
+  cfft_x_body<T, NCT>(F, Ny, Lh, lchunk, fd, wm, gl % gridDim.x, gl / gridDim.x);
 }
 
 template <typename T, bool INV, int NCT = 0>
@@ -452,9 +452,9 @@ static hipError_t launch_forward_xy(const DevPlan& p, cx<T>* F, hipStream_t s) {
   return ct_pick(CtInverse{}, p.Nx, [&](auto c) {
     constexpr int NCT = decltype(c)::value;
     if (NCT > 0 && (lx != ct_maxb(NCT, kInvCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
-    hipError_t e2 = allow_lds(reinterpret_cast<const void*>(&k_cfft_x<T, false, NCT>), lds_x);
+    hipError_t e2 = allow_lds(reinterpret_cast<const void*>(&k_cfft_x<T, NCT>), lds_x);
     if (e2 != hipSuccess) return e2;
-    hipLaunchKernelGGL((k_cfft_x<T, false, NCT>), dim3((Lh + lx - 1) / lx, p.Ny), dim3(cfg.threads), lds_x, s, F,
+    hipLaunchKernelGGL((k_cfft_x<T, NCT>), dim3((Lh + lx - 1) / lx, p.Ny), dim3(cfg.threads), lds_x, s, F,
                        p.Ny, Lh, lx, as_desc<T>(p.f_Nx), cfg.wave);
     return hipGetLastError();
   });
@@ -574,7 +574,8 @@ hipError_t launch_forward3d_reg(const DevPlan& p, const T* f, void* Dh, hipStrea
       constexpr auto kern = &k_cfft_fwd_reg<T, decltype(c)::value>;
       hipError_t e2 = allow_lds(reinterpret_cast<const void*>(kern), lds);
       if (e2 != hipSuccess) return e2;
-      hipLaunchKernelGGL(kern, dim3((Lz + (1 << t.ls) - 1) >> t.ls, count), dim3(fft2_threads(t)), lds, s, D, Lz, stride,
+      hipLaunchKernelGGL(kern, dim3((Lz + (1 << t.ls) - 1) >> t.ls, count), dim3(fft2_threads(t)), lds, s, D, Lz,
+                         stride,
                          other, t);
       return hipGetLastError();
     });

@@ -204,9 +204,9 @@ template <typename T>
 hipError_t launch_temporal_t(const DevPlan& p, const void* Gt, T* g, hipStream_t s);
 
 // ---------------------------------------------------------------------------
-// Batched launches: one launch per stage serves up to kBatchMax problems of
-// different sizes. The work items of a stage are the blocks of every
-// problem, numbered problem after problem; prefix[p] is the first item of
+// Batched launches: one launch per stage and kernel variant (class of FFT
+// lengths) serves up to kGroupMax problems of different sizes. The work items
+// of a launch are the blocks of its problems, numbered problem after problem; prefix[p] is the first item of
 // problem p (prefix[nprob] = total). Each problem's arguments sit in a device
 // table; only the per-call input and output pointers travel in BatchIO (a
 // kernel argument), so a batched call allocates and synchronises nothing.

@@ -105,13 +105,16 @@ static inline FftCfg fft_cfg() { return FftCfg{}; }
 // runs of `cap` consecutive z modes: 16 per group measured faster there.
 constexpr int kInvCap = 16;
 // z modes per work-group of the gather fused with the inverse x pass: 8
-// (19.5 KiB of LDS at 256 points) fits 6 work-groups per CU where 16 fit 4,
-// and the gather is bound by instruction issue (0.083 -> 0.077 ms for a
-// 256^3 image from 576 band bins; 4 measured 0.088 ms)
+// (18 KiB of LDS at 256 points) leaves room for all the work-groups that the
+// registers allow; the gather is bound by instruction issue (runs of 16 and 4
+// took 0.083 and 0.088 ms where 8 took 0.077, on the passes in LDS)
 constexpr int kGatherCap = 8;
 static inline FftCfg inv_cfg() { return FftCfg{256, kInvCap, 0}; }
 
-// Lengths with compile-time FFT instantiations (fft_ct); a launcher calls
+// Lengths with compile-time FFT instantiations (fft_ct), for the kernels that
+// keep their passes in LDS: the position derivatives' (whose bits stay as they
+// are) and the forward model's temporal transform and real-to-complex z pass,
+// where they are the faster form. A launcher calls
 // f(std::integral_constant<int, N>) for a listed length and
 // f(std::integral_constant<int, 0>) (the runtime plan) otherwise.
 template <int... Ns>

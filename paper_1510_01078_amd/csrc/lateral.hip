@@ -18,7 +18,8 @@ namespace patk {
 // (the grid is read once) and by the vector ALU's DFT arithmetic; LDS is
 // crossed once.
 template <typename T, int CLS>
-__device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx, int b_begin,
+__device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx,
+                                               int b_begin,
                                                const Fft2<T>& f, cx<T>* __restrict__ V, int bx, int by,
                                                const int* __restrict__ brange, int tid) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -112,7 +113,8 @@ __device__ __forceinline__ void fft_x_body(const cx<T>* __restrict__ U, int n_y,
 }
 
 template <typename T>
-__global__ __launch_bounds__(kFftThreads) void k_fft_x(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx, int rows,
+__global__ __launch_bounds__(kFftThreads) void k_fft_x(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx,
+                                                       int rows,
                                                      int b_begin, FftDesc<T> fd, cx<T>* __restrict__ V, int wm,
                                                      const int* __restrict__ brange) {
   // neighbouring groups write the two halves of each 128-byte output line:
@@ -122,11 +124,13 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_x(const cx<T>* __restrict__
 }
 
 template <typename T, int CLS>
-__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_x_reg(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx, int b_begin,
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_x_reg(const cx<T>* __restrict__ U, int n_y,
+                                                                                  int pu, int pv, int Nx, int b_begin,
                                                            Fft2Raw f, cx<T>* __restrict__ V,
                                                            const int* __restrict__ brange) {
   const int gl = xcd_linear();
-  fft_x_reg_body<T, CLS>(U, n_y, pu, pv, Nx, b_begin, as_fft2<T>(f), V, gl % gridDim.x, gl / gridDim.x, brange, threadIdx.x);
+  fft_x_reg_body<T, CLS>(U, n_y, pu, pv, Nx, b_begin, as_fft2<T>(f), V, gl % gridDim.x, gl / gridDim.x, brange,
+                         threadIdx.x);
 }
 
 template <typename T>
@@ -173,7 +177,8 @@ hipError_t launch_fft_x(const DevPlan& p, const void* U, void* V, int b_begin, i
 // once, and keeping it out of the caches leaves them to the spectra this
 // kernel writes, which the gather reads next.
 template <typename T, int CLS>
-__device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny, const Fft2<T>& f, cx<T>* __restrict__ Gh, int bx, int jj,
+__device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny,
+                                               const Fft2<T>& f, cx<T>* __restrict__ Gh, int bx, int jj,
                                                const int* __restrict__ jrange, int tid) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
@@ -204,7 +209,8 @@ __device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int 
 }
 
 template <typename T>
-__device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny, int bins,
+__device__ __forceinline__ void fft_y_body(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny,
+                                           int bins,
                                            FftDesc<T> fd, cx<T>* __restrict__ Gh, int wm, int bx, int by,
                                            const int* __restrict__ jrange = nullptr, int tid = threadIdx.x) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -266,7 +272,8 @@ __device__ __forceinline__ void y_item(const int* __restrict__ ylist, int gl, in
 }
 
 template <typename T>
-__global__ __launch_bounds__(kFftThreads) void k_fft_y(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny, int bins,
+__global__ __launch_bounds__(kFftThreads) void k_fft_y(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx,
+                                                       int Ny, int bins,
                                                      FftDesc<T> fd, cx<T>* __restrict__ Gh, int wm,
                                                      const int* __restrict__ jrange, const int* __restrict__ ylist) {
   // neighbouring groups write the two halves of each 128-byte output line:
@@ -277,7 +284,8 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_y(const cx<T>* __restrict__
 }
 
 template <typename T, int CLS>
-__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_y_reg(const cx<T>* __restrict__ V, int nb, int pv, int pg, int Nx, int Ny,
+__global__ __launch_bounds__(kFftThreads, (reg_waves<T, CLS>())) void k_fft_y_reg(const cx<T>* __restrict__ V, int nb,
+                                                                                  int pv, int pg, int Nx, int Ny,
                                                            Fft2Raw f, cx<T>* __restrict__ Gh,
                                                            const int* __restrict__ jrange,
                                                            const int* __restrict__ ylist) {
@@ -600,10 +608,12 @@ __global__ __launch_bounds__(kFftThreads, (any_waves<T, CLS>())) void k_fft_y_ba
       bx = e & 0xffff;
     }
     if constexpr (CLS > 0)
-      fft_y_reg_body<T, CLS>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, as_fft2<T>(a.f2), static_cast<cx<T>*>(a.Gh), bx, by,
+      fft_y_reg_body<T, CLS>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, as_fft2<T>(a.f2),
+                             static_cast<cx<T>*>(a.Gh), bx, by,
                              a.jrange, loop_lane());
     else
-      fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, a.bins, view_desc<T>(a.fd), static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
+      fft_y_body<T>(static_cast<const cx<T>*>(a.V), a.nb, a.pitch_v, a.pitch_g, a.Nx, a.Ny, a.bins, view_desc<T>(a.fd),
+                    static_cast<cx<T>*>(a.Gh), 0, bx, by, a.jrange,
                     loop_lane());
   }
 }

@@ -166,7 +166,8 @@ __global__ __launch_bounds__(64) void k_spread_slots(const cx<T>* __restrict__ G
                                                      const unsigned* __restrict__ slot_k, int n_x, int n_y,
                                                      int tiles_x, int nchunks, int heavy, int groups, int b_begin,
                                                      int b_end, cx<T>* __restrict__ U) {
-  spread_slot_body<T, KAHAN>(Gt, nb, pitch_t, pitch_u, slot_rng, slot_sens, slot_w, slot_k, n_x, n_y, tiles_x, nchunks, heavy, groups,
+  spread_slot_body<T, KAHAN>(Gt, nb, pitch_t, pitch_u, slot_rng, slot_sens, slot_w, slot_k, n_x, n_y, tiles_x, nchunks,
+                             heavy, groups,
                              b_begin, b_end, U, blockIdx.x);
 }
 
