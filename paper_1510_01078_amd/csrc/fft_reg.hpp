@@ -165,6 +165,34 @@ struct RDft {
   }
 };
 
+// The same sums, output e given to st(e, v) as each of the last butterflies
+// ends: fewer values live where the outputs go to memory under conditions
+// (with all of them held until the first store, radix 32 on 128 registers
+// spilled 12 to 29 of them to scratch).
+template <typename T, int N, bool INV, typename Store>
+__device__ __forceinline__ void rdft_to(const cx<T> (&a)[N], Store st) {
+  constexpr int A = RadixSplit<N>::A, B = RadixSplit<N>::B;
+  constexpr int ia = ctrig::inverse_mod(A % B, B), ib = ctrig::inverse_mod(B % A, A);
+  constexpr bool coprime = (A * ia) % B == 1 && (B * ib) % A == 1;
+  cx<T> t[B][A];
+#pragma unroll
+  for (int i = 0; i < B; ++i) {
+#pragma unroll
+    for (int r = 0; r < A; ++r) t[i][r] = coprime ? a[(B * r + A * i) % N] : a[i + B * r];
+    RDft<T, A, INV>::run(t[i]);
+  }
+  if constexpr (!coprime) split_twiddles<T, N, INV, A, B, 1, 1>(t);
+#pragma unroll
+  for (int k = 0; k < A; ++k) {
+    cx<T> u[B];
+#pragma unroll
+    for (int i = 0; i < B; ++i) u[i] = t[i][k];
+    RDft<T, B, INV>::run(u);
+#pragma unroll
+    for (int q = 0; q < B; ++q) st(coprime ? (B * ib * k + A * ia * q) % N : k + A * q, u[q]);
+  }
+}
+
 template <typename T, bool INV>
 struct RDft<T, 2, INV> {
   __host__ __device__ __forceinline__ static void run(cx<T> (&a)[2]) {
@@ -253,8 +281,8 @@ __device__ __forceinline__ cx<T>& cx_at(cx<T>* base, unsigned at) {
 }
 
 // Kernels of two-pass transforms come in three classes by the larger radix,
-// since the largest radix a kernel holds sets its registers: up to 16 (72
-// registers in FP32: 6 waves per SIMD), 18 and 20 (5 waves), 24 to 32 (4
+// since the largest radix a kernel holds sets its registers: up to 16 (76 to
+// 80 registers in FP32: 6 waves per SIMD), 18 and 20 (5 waves), 24 to 32 (4
 // waves). One kernel for all took 128 registers, and the batched x pass over
 // lengths of 96 to 288 points 1.19 instead of 0.93 ms.
 constexpr int reg_larger(const Fft2Raw& f) { return f.r1 > f.r2 ? f.r1 : f.r2; }
@@ -325,16 +353,21 @@ __device__ __forceinline__ void reg_first_in_lds(cx<T>* seq, int r2, int Q, cons
   }
 }
 
-// Second pass for the index k: st(q, v) takes output k + r1*q.
+// Second pass for the index k: st(q, v) takes output k + r1*q (the larger
+// radices as their butterflies end, rdft_to).
 template <typename T, int R, bool INV, typename Store>
 __device__ __forceinline__ void reg_second(const cx<T>* seq, int Q, int k, Store st) {
   cx<T> v[R];
   const cx<T>* row = seq + k * Q;
 #pragma unroll
   for (int r = 0; r < R; ++r) v[r] = row[r];
-  RDft<T, R, INV>::run(v);
+  if constexpr (R >= 24) {
+    rdft_to<T, R, INV>(v, st);
+  } else {
+    RDft<T, R, INV>::run(v);
 #pragma unroll
-  for (int q = 0; q < R; ++q) st(q, v[q]);
+    for (int q = 0; q < R; ++q) st(q, v[q]);
+  }
 }
 
 // Three-pass transform of one length n = r1*r2*r3 (r3 = 1: two passes) for

@@ -45,13 +45,15 @@ __device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int 
     const int J0 = brange ? brange[2 * b] : 0, J1 = brange ? brange[2 * b + 1] : Nx;
     const int p0 = J0, p1 = min(J1, Nx / 2 - 1);                    // elements of the non-negative modes
     const int m0 = n_x - min(J1, Nx / 2), m1 = n_x - max(J0, 1);    // and of the negative ones
-    cx<T>* dst = V + size_t(b) * Nx * pv + py0 + s;
+    // one store per output from a uniform base, at offsets that differ by
+    // uniform steps (an address pair and two branches per output cost
+    // registers that radix 32 does not have)
+    cx<T>* dst = V + size_t(b) * Nx * pv + py0;
+    const unsigned at = unsigned(k * pv + s), step = unsigned(f.r1 * pv), back = unsigned((n_x - Nx) * pv);
     reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
       const int e = k + q * f.r1;
-      if (e >= p0 && e <= p1)
-        cx_at(dst, unsigned(e * pv)) = v;
-      else if (e >= m0 && e <= m1)
-        cx_at(dst, unsigned((e - (n_x - Nx)) * pv)) = v;
+      const bool neg = e >= m0 && e <= m1;
+      if (neg || (e >= p0 && e <= p1)) cx_at(dst, at + unsigned(q) * step - (neg ? back : 0u)) = v;
     });
   }
 }
@@ -198,12 +200,13 @@ __device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int 
   __syncthreads();
   const int s = tid & (S - 1), k = tid >> f.ls;
   if (k < f.r1 && s < nbc) {
-    cx<T>* dst = Gh + size_t(jj) * Ny * pg + b0 + s;
+    cx<T>* dst = Gh + size_t(jj) * Ny * pg + b0;
+    const unsigned at = unsigned(k * pg + s), step = unsigned(f.r1 * pg), back = unsigned((n_y - Ny) * pg);
     reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
       // element e holds mode e below Ny/2 and e - n_y from -Ny/2 on
       const int e = k + q * f.r1;
-      const int kk = e < Ny / 2 ? e : e - (n_y - Ny);
-      if (e < Ny / 2 || e >= n_y - Ny / 2) cx_at(dst, unsigned(kk * pg)) = v;
+      const bool neg = e >= n_y - Ny / 2;
+      if (neg || e < Ny / 2) cx_at(dst, at + unsigned(q) * step - (neg ? back : 0u)) = v;
     });
   }
 }
