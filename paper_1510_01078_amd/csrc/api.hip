@@ -381,22 +381,26 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
         sk16[size_t(q) * 64 + lane] = v;
       }
   P->spread_slots = (int64_t)(ssens.size() / SK);
-  // the patches' slot ranges, those of several rounds of slots first and the
-  // longest ahead: their items take the longest, so a launch starts with them
+  // the patches' slot ranges, the longest first: their items take the longest,
+  // so a launch starts with them
   std::vector<int> order(npatch);
   for (int i = 0; i < npatch; ++i) order[i] = i;
   auto rounds_of = [&](int pt) { return (soff[pt + 1] - soff[pt] + patk::kSlotBatch - 1) / patk::kSlotBatch; };
   std::stable_sort(order.begin(), order.end(),
                    [&](int a, int b) { return std::max(1, rounds_of(a)) > std::max(1, rounds_of(b)); });
   std::vector<int> srng(4 * size_t(npatch));
-  dp.spread_heavy = 0;
+  int several = 0;
+  long long rounds = 0;
   for (int i = 0; i < npatch; ++i) {
     const int pt = order[i];
     srng[4 * i] = soff[pt];
     srng[4 * i + 1] = soff[pt + 1];
     srng[4 * i + 2] = pt;
-    dp.spread_heavy += rounds_of(pt) > 1;
+    several += rounds_of(pt) > 1;
+    rounds += std::max(1, rounds_of(pt));
   }
+  const int nchunks = (dp.nb + 15) / 16;
+  dp.spread_heavy = patsz::spread_split(npatch, rounds, std::max(1, rounds_of(order[0])), nchunks) ? several : 0;
   const size_t o_srng = blob.add(srng.data(), srng.size() * sizeof(int));
   const size_t o_ssens = blob.add(ssens.data(), std::max<size_t>(1, ssens.size()) * sizeof(int));
   const size_t o_sw = add_real<T>(blob, sw.empty() ? std::vector<double>(1, 0.0) : sw);

@@ -15,6 +15,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "plan_sizes.hpp"
+
 namespace patk {
 
 struct FftPassRaw {
@@ -78,7 +80,8 @@ struct DevPlan {
   const void* swy = nullptr;      // [M][w]
   const int4* slot_rng = nullptr; // [tiles_x*patches_y] first and past-the-end packed slot of each 16 x kPatchRows
                                   // patch and the patch's index, patches of several rounds of slots first
-  int spread_heavy = 0;           // patches of more than one round (kSlotBatch slots)
+  int spread_heavy = 0;           // patches (the first of slot_rng) that take one bin group per work item: those of
+                                  // more than one round (kSlotBatch slots) where patsz::spread_split, else none
   const int* slot_sens = nullptr; // [slots][kSlotK] sensor ids of each slot, -1 for an empty place
   const void* slot_w = nullptr;   // [slots][64] each lane's weight wx*wy (0 where no sensor covers it)
   const unsigned* slot_k = nullptr;       // [slots][64] places in their slots of the lane's sensors for the
@@ -105,18 +108,18 @@ constexpr int kSlotK = 4;        // sensors per packed spread slot
 constexpr int kSpreadGroups = 2; // most spread bin groups (16 bins each) per work-group
 constexpr int kSlotBatch = 8;    // spread slots staged per round (their places fit one 32-bit word)
 
-// Work items of the spread over `nchunks` bin groups: a patch of several
-// rounds of slots takes one bin group per item (it reads its lane tables again
-// for every bin group anyway), the others `groups`.
+// Work items of the spread over `nchunks` bin groups: the first spread_heavy
+// patches take one bin group per item (they read their lane tables again for
+// every bin group anyway), the others `groups`.
 inline long long spread_items(const DevPlan& p, int nchunks, int groups) {
   return (long long)p.spread_heavy * nchunks +
          ((long long)p.tiles_x * p.patches_y - p.spread_heavy) * ((nchunks + groups - 1) / groups);
 }
 // Two bin groups per item (one read of the lane tables for both) once that
-// leaves enough one-wave items to fill the device's wave slots (256 CUs with
-// 20 each); smaller problems spread the bin groups over more waves.
+// leaves enough one-wave items to fill the device; smaller problems spread the
+// bin groups over more waves.
 inline int spread_groups(const DevPlan& p, int nchunks) {
-  return spread_items(p, nchunks, kSpreadGroups) >= 5120 ? kSpreadGroups : 1;
+  return spread_items(p, nchunks, kSpreadGroups) >= patsz::kSpreadWaves ? kSpreadGroups : 1;
 }
 
 // Stage launchers; T = float or double. Buffers are device pointers.

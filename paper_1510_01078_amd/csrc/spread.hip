@@ -54,7 +54,9 @@ __device__ __forceinline__ void accum(cx<T>& a, cx<T>& c, T wt, cx<T> g) {
 // grid point sums its sensors in slot order
 // (deterministic). A work-group takes kSpreadGroups consecutive bin groups of
 // its patch, so a patch with one round of slots (the usual case) reads its
-// lane tables once. Measured on MI355X at the headline size: 8 slots per
+// lane tables once; one bin group where the launch would not fill the device
+// (spread_groups) and, for patches of several rounds, where it would end in a
+// tail (patsz::spread_split). Measured on MI355X at the headline size: 8 slots per
 // round beat 16; two bin groups per work-group beat one, four and nine;
 // splitting a group's bins over two or four passes (fewer live accumulators)
 // and XCD-contiguous or patch-major block orders were slower.
@@ -75,7 +77,7 @@ __device__ __forceinline__ void spread_slot_body(const cx<T>* __restrict__ Gt, i
   constexpr int LSTRIDE = 64 * EL;               // elements between two loads' blocks
   static_assert(ROWS * LPR == 64 && BC % LPR == 0 && EPL % EL == 0 && SB * 2 <= 32 && K <= 4, "staging layout");
   __shared__ __align__(16) cx<T> s_g[NLD * LSTRIDE];
-  // item bx: one bin group of a patch of several rounds, or `groups` of
+  // item bx: one bin group of one of the first `heavy` patches, or `groups` of
   // another (bin groups vary fastest: neighbours share the patch's slots)
   const int nheavy = heavy * nchunks;
   int at, c_first, c_end;
