@@ -16,7 +16,15 @@ namespace patk {
 // rows (a wave walks along a row), the second stores straight to the columns
 // (a wave walks S rows of one mode, so S*8 bytes of one line). Bound by HBM
 // (the grid is read once) and by the vector ALU's DFT arithmetic; LDS is
-// crossed once.
+// crossed once. In double the grid's rows come by non-temporal loads, which
+// leave the caches to the columns that the y pass reads next and to the next
+// call's band values: 128^3 at the default windows 326 -> 312 us (x pass 117
+// -> 111, temporal 32 -> 28, y pass 45 -> 41; with cached loads it was slower
+// than the LDS passes' 319), 144^3 423 -> 406, 256^3 1208 -> 1204, 192^3 at
+// oversampling 1.5 550 -> 555, batches of small problems 0.90 to 1.02 times.
+// In single precision, half the bytes, the
+// columns fit the cache beside the grid and the y pass loses more than the x
+// pass gains (256^3 at the benchmark's windows 652 -> 662 us).
 template <typename T, int CLS>
 __device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int n_y, int pu, int pv, int Nx,
                                                int b_begin,
@@ -33,7 +41,10 @@ __device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int 
   {
     const int s = small_div(tid, f.r2), i = tid - s * f.r2;
     if (s < nr)
-      reg_first_any<T, CLS, false>(f, buf + s * f.P, i, [&](int e) { return cx_at(src, unsigned(s * pu + e)); });
+      reg_first_any<T, CLS, false>(f, buf + s * f.P, i, [&](int e) {
+        const cx<T>& u = cx_at(src, unsigned(s * pu + e));
+        return sizeof(T) == 8 ? nt_load(&u) : u;
+      });
   }
   __syncthreads();
   const int s = tid & (S - 1), k = tid >> f.ls;
