@@ -502,6 +502,15 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
       for (int b = jr[2 * jj]; b <= jr[2 * jj + 1]; b += ybins) yl.push_back(jj << 16 | (b / ybins));
   }
   const size_t o_yl = blob.add(yl.data(), std::max<size_t>(1, yl.size()) * sizeof(int));
+  // the same for the transposed pass in LDS, whose work-groups hold fft_batch
+  // bins: 6 and 7 from 540 to 640 points, where the register passes take 4
+  std::vector<int> ytl;
+  {
+    const int tbins = patk::fft_batch<T>(dp.n_y, patk::kFftThreads, patk::kFftCap);
+    for (int jj = 0; jj < d.nx; ++jj)
+      for (int b = jr[2 * jj]; b <= jr[2 * jj + 1]; b += tbins) ytl.push_back(jj << 16 | b);
+  }
+  const size_t o_ytl = blob.add(ytl.data(), std::max<size_t>(1, ytl.size()) * sizeof(int));
   // the same ranges per bin: both ends are non-decreasing in |j|, so the
   // x-modes that hold bin b are J0(b) <= |j| <= J1(b) (J0 > J1: none)
   std::vector<int> br(2 * size_t(dp.nb));
@@ -564,6 +573,8 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   dp.jrange = static_cast<const int*>(at(o_jr));
   dp.ylist = static_cast<const int*>(at(o_yl));
   dp.ylist_n = int(yl.size());
+  dp.ytlist = static_cast<const int*>(at(o_ytl));
+  dp.ytlist_n = int(ytl.size());
   dp.brange = static_cast<const int*>(at(o_br));
   dp.f_nt.tw = at(o_tw_nt);
   dp.f_nt3.twA = at(o_twA);
@@ -704,6 +715,8 @@ pat_status run_image_in(pat_plan* P, const void* f, void* g, void* ws, hipStream
     dp.brange = nullptr;
     dp.ylist = nullptr;
     dp.ylist_n = 0;
+    dp.ytlist = nullptr;
+    dp.ytlist_n = 0;
   }
   unsigned char* A = static_cast<unsigned char*>(ws);
   unsigned char* B = A + P->off_B;

@@ -95,6 +95,8 @@ struct DevPlan {
   const int* brange = nullptr;    // [nb][2] per band bin the smallest and largest |j| whose range holds it
   const int* ylist = nullptr;     // the y-FFT's work items inside the ranges: jj << 16 | bin group
   int ylist_n = 0;
+  const int* ytlist = nullptr;    // the same ranges for the transposed y pass with its passes in LDS, which takes
+  int ytlist_n = 0;               // fft_batch bins per item: jj << 16 | first bin
   const void* dcx = nullptr;      // [Nx] 1/phihat(j/n_x), 0 at j = -Nx/2
   const void* dcy = nullptr;      // [Ny]
   const void* hcoef = nullptr;    // [w_t][hdeg+1] temporal tap polynomials

@@ -418,19 +418,18 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_y_t(const cx<T>* __restrict
                                                        int bins, const T* __restrict__ dcx,
                                                        const T* __restrict__ dcy, FftDesc<T> fd,
                                                        cx<T>* __restrict__ V, const int* __restrict__ jrange,
-                                                       const int* __restrict__ ylist) {
+                                                       const int* __restrict__ ytlist) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int n_y = NCT > 0 ? NCT : fd.n;
   const int bstride = lseq(n_y);
-  // (an XCD-grouped order measured slower here); with ylist a one-dimensional
-  // grid over the work items inside the ranges
-  const int jj = ylist ? ylist[blockIdx.x] >> 16 : int(blockIdx.y);
-  const int b0 = (ylist ? ylist[blockIdx.x] & 0xffff : int(blockIdx.x)) * bins;
-  const int nbc = min(bins, nb - b0);
-  // bins outside the x-mode's range hold zeros that nothing reads: skipped
-  if (jrange && (b0 + nbc - 1 < jrange[2 * jj] || b0 > jrange[2 * jj + 1])) return;
+  // (an XCD-grouped order measured slower here); with ytlist a one-dimensional
+  // grid over the ranges' bins (those outside hold zeros that nothing reads)
+  const int item = ytlist ? ytlist[blockIdx.x] : 0;
+  const int jj = ytlist ? item >> 16 : int(blockIdx.y);
+  const int b0 = ytlist ? item & 0xffff : int(blockIdx.x) * bins;
+  const int nbc = min(bins, (ytlist ? jrange[2 * jj + 1] + 1 : nb) - b0);
   const int gap = n_y - Ny;  // zero slots k = Ny/2 .. n_y - Ny/2 - 1
   const T cxj = dcx[jj];
   const cx<T>* src = Gh + size_t(jj) * Ny * nb + b0;
@@ -504,7 +503,7 @@ __global__ __launch_bounds__(kFftThreads) void k_fft_y_t(const cx<T>* __restrict
 template <typename T>
 hipError_t launch_fft_y_t(const DevPlan& p, const void* Gh, void* V, hipStream_t s) {
   const FftCfg cfg = fft_cfg();
-  const int bins = fft_bins<T>(p.f_ny, cfg.threads, cfg.cap);
+  const int bins = fft_batch<T>(p.n_y, cfg.threads, cfg.cap);  // the plan's ytlist is in these
   const size_t lds = (size_t(bins) * lseq(p.n_y) + p.n_y) * sizeof(cx<T>);
   if (size_t(bins) * p.n_y > size_t(kFftMaxV) * cfg.threads || size_t(bins) * p.Ny > size_t(kFftMaxV) * cfg.threads)
     return hipErrorInvalidValue;
@@ -513,11 +512,11 @@ hipError_t launch_fft_y_t(const DevPlan& p, const void* Gh, void* V, hipStream_t
     if (nct > 0 && (bins != ct_maxb(nct, kFftCap) || cfg.threads != kFftThreads)) return hipErrorInvalidValue;
     hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
-    const bool listed = p.ylist && p.ylist_n > 0 && p.jrange;
-    const dim3 grid = listed ? dim3(p.ylist_n) : dim3((p.nb + bins - 1) / bins, p.Nx);
+    const bool listed = p.ytlist && p.ytlist_n > 0 && p.jrange;
+    const dim3 grid = listed ? dim3(p.ytlist_n) : dim3((p.nb + bins - 1) / bins, p.Nx);
     hipLaunchKernelGGL(kern, grid, dim3(cfg.threads), lds, s, static_cast<const cx<T>*>(Gh), p.nb, p.Nx, p.Ny,
                        bins, static_cast<const T*>(p.dcx), static_cast<const T*>(p.dcy), as_desc<T>(p.f_ny),
-                       static_cast<cx<T>*>(V), p.jrange, listed ? p.ylist : nullptr);
+                       static_cast<cx<T>*>(V), p.jrange, listed ? p.ytlist : nullptr);
     return hipGetLastError();
   };
   return ct_pick(CtLateral{}, p.n_y, [&](auto c) { return go(&k_fft_y_t<T, decltype(c)::value>, decltype(c)::value); });
