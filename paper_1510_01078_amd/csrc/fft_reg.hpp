@@ -353,15 +353,18 @@ __device__ __forceinline__ void reg_first_in_lds(cx<T>* seq, int r2, int Q, cons
   }
 }
 
-// Second pass for the index k: st(q, v) takes output k + r1*q (the larger
-// radices as their butterflies end, rdft_to).
-template <typename T, int R, bool INV, typename Store>
+// Second pass for the index k: st(q, v) takes output k + r1*q. PART: only part
+// of the outputs is stored, and the larger radices hand them on as their
+// butterflies end (rdft_to; passes that store them all need no more registers
+// in one burst, and the transposed y pass over 432 points takes 16.8 us so,
+// 21.0 with PART).
+template <typename T, int R, bool INV, bool PART, typename Store>
 __device__ __forceinline__ void reg_second(const cx<T>* seq, int Q, int k, Store st) {
   cx<T> v[R];
   const cx<T>* row = seq + k * Q;
 #pragma unroll
   for (int r = 0; r < R; ++r) v[r] = row[r];
-  if constexpr (R >= 24) {
+  if constexpr (PART && R >= 24) {
     rdft_to<T, R, INV>(v, st);
   } else {
     RDft<T, R, INV>::run(v);
@@ -514,9 +517,9 @@ __device__ __forceinline__ void reg_first_in_lds_any(const Fft2<T>& f, cx<T>* se
 #undef PATK_CASE
 }
 
-template <typename T, int CLS, bool INV, typename Store>
+template <typename T, int CLS, bool INV, bool PART = false, typename Store>
 __device__ __forceinline__ void reg_second_any(const Fft2<T>& f, const cx<T>* seq, int k, Store st) {
-#define PATK_CASE(R) case R: reg_second<T, R, INV>(seq, f.Q, k, st); break;
+#define PATK_CASE(R) case R: reg_second<T, R, INV, PART>(seq, f.Q, k, st); break;
   if constexpr (CLS == 16) {
     switch (f.r2) { PATK_RADICES_16(PATK_CASE) default: break; }
   } else if constexpr (CLS == 20) {

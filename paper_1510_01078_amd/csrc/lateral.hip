@@ -61,7 +61,7 @@ __device__ __forceinline__ void fft_x_reg_body(const cx<T>* __restrict__ U, int 
     // registers that radix 32 does not have)
     cx<T>* dst = V + size_t(b) * Nx * pv + py0;
     const unsigned at = unsigned(k * pv + s), step = unsigned(f.r1 * pv), back = unsigned((n_x - Nx) * pv);
-    reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
+    reg_second_any<T, CLS, false, true>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
       const int e = k + q * f.r1;
       const bool neg = e >= m0 && e <= m1;
       if (neg || (e >= p0 && e <= p1)) cx_at(dst, at + unsigned(q) * step - (neg ? back : 0u)) = v;
@@ -213,7 +213,7 @@ __device__ __forceinline__ void fft_y_reg_body(const cx<T>* __restrict__ V, int 
   if (k < f.r1 && s < nbc) {
     cx<T>* dst = Gh + size_t(jj) * Ny * pg + b0;
     const unsigned at = unsigned(k * pg + s), step = unsigned(f.r1 * pg), back = unsigned((n_y - Ny) * pg);
-    reg_second_any<T, CLS, false>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
+    reg_second_any<T, CLS, false, true>(f, buf + s * f.P, k, [&](int q, cx<T> v) {
       // element e holds mode e below Ny/2 and e - n_y from -Ny/2 on
       const int e = k + q * f.r1;
       const bool neg = e >= n_y - Ny / 2;
