@@ -367,10 +367,12 @@ __global__ __launch_bounds__(kFftThreads) void k_c2r_z(const cx<T>* __restrict__
 // share one complex transform, Z = FFT(x0 + i x1): X0[l] = (Z[l] + conj
 // Z[-l])/2 and X1[l] = (Z[l] - conj Z[-l])/(2i), so a work-group of `rows`
 // rows transforms (rows + 1) / 2 sequences (half the transforms, LDS and
-// registers of one sequence per row).
-template <typename T, int NCT>
+// registers of one sequence per row). PLANE: packed rows with the plane
+// l = Nz/2, stored in one run (the row and mode of every value cost the
+// position derivatives up to 3 % of this pass); else rows of `pitch` without it.
+template <typename T, int NCT, bool PLANE>
 __global__ __launch_bounds__(kFftThreads) void k_r2c_z(const T* __restrict__ f, long long nrows, int rows,
-                                                     FftDesc<T> fd, cx<T>* __restrict__ D, int pitch, int modes) {
+                                                     FftDesc<T> fd, cx<T>* __restrict__ D, int pitch) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cx<T>* buf = reinterpret_cast<cx<T>*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
@@ -423,9 +425,13 @@ __global__ __launch_bounds__(kFftThreads) void k_r2c_z(const T* __restrict__ f, 
                        : cx<T>{T(0.5) * (z.x + zm.x), T(0.5) * (z.y - zm.y)};
       },
       [&](int q, cx<T> v) {
-        const int r = div_lh(q);
-        const int l = q - r * Lh;
-        if (l < modes) D[(r0 + r) * pitch + l] = v;
+        if constexpr (PLANE) {
+          D[r0 * Lh + q] = v;
+        } else {
+          const int r = div_lh(q);
+          const int l = q - r * Lh;
+          if (l < Nz / 2) D[(r0 + r) * pitch + l] = v;
+        }
       });
 }
 
@@ -511,10 +517,11 @@ hipError_t launch_inverse(const DevPlan& p, void* Fh, T* f, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Real-to-complex z pass with its passes in LDS: `modes` z modes of each row to
-// rows of `pitch`.
-template <typename T>
-static hipError_t launch_r2c_z(const DevPlan& p, const T* f, cx<T>* D, int pitch, int modes, hipStream_t s) {
+// Real-to-complex z pass with its passes in LDS: packed rows with the plane
+// l = Nz/2 at every length, or rows of pitch_f without it at the lengths of
+// CtInverse (others return hipErrorInvalidValue).
+template <typename T, bool PLANE>
+static hipError_t launch_r2c_z(const DevPlan& p, const T* f, cx<T>* D, hipStream_t s) {
   const FftCfg cfg = inv_cfg();
   const int rows = fft_batch<T>(p.Nz, cfg.threads, cfg.cap);
   const size_t lds = size_t(c2r_lds_slots(rows, p.Nz)) * sizeof(cx<T>);  // (rows + 1) / 2 sequences
@@ -522,19 +529,24 @@ static hipError_t launch_r2c_z(const DevPlan& p, const T* f, cx<T>* D, int pitch
   if ((rows + 1) / 2 * p.Nz > kFftMaxV * cfg.threads || rows * (p.Nz / 2 + 1) > kFftMaxV * cfg.threads)
     return hipErrorInvalidValue;
   return ct_pick(CtInverse{}, p.Nz, [&](auto c) {
-    hipError_t e2 = allow_lds(reinterpret_cast<const void*>(&k_r2c_z<T, decltype(c)::value>), lds);
-    if (e2 != hipSuccess) return e2;
-    hipLaunchKernelGGL((k_r2c_z<T, decltype(c)::value>), dim3((unsigned)((nrows + rows - 1) / rows)),
-                       dim3(cfg.threads), lds, s, f, nrows, rows, as_desc<T>(p.f_Nz), D, pitch, modes);
-    return hipGetLastError();
+    constexpr int NCT = decltype(c)::value;
+    if constexpr (PLANE || NCT > 0) {
+      constexpr auto kern = &k_r2c_z<T, NCT, PLANE>;
+      hipError_t e2 = allow_lds(reinterpret_cast<const void*>(kern), lds);
+      if (e2 != hipSuccess) return e2;
+      hipLaunchKernelGGL(kern, dim3((unsigned)((nrows + rows - 1) / rows)), dim3(cfg.threads), lds, s, f, nrows, rows,
+                         as_desc<T>(p.f_Nz), D, PLANE ? p.Nz / 2 + 1 : p.pitch_f);
+      return hipGetLastError();
+    } else {
+      return hipErrorInvalidValue;
+    }
   });
 }
 
 template <typename T>
 hipError_t launch_forward3d(const DevPlan& p, const T* f, void* Dh, hipStream_t s) {
   cx<T>* D = static_cast<cx<T>*>(Dh);
-  const int Lh = p.Nz / 2 + 1;
-  hipError_t e = launch_r2c_z<T>(p, f, D, Lh, Lh, s);
+  hipError_t e = launch_r2c_z<T, true>(p, f, D, s);
   if (e != hipSuccess) return e;
   return launch_forward_xy<T>(p, D, s);
 }
@@ -557,7 +569,7 @@ hipError_t launch_forward3d_reg(const DevPlan& p, const T* f, void* Dh, hipStrea
     fixed = decltype(c)::value > 0;
     return hipSuccess;
   });
-  hipError_t e = fixed ? launch_r2c_z<T>(p, f, D, p.pitch_f, Lz, s) : class_pick(z, [&](auto c) {
+  hipError_t e = fixed ? launch_r2c_z<T, false>(p, f, D, s) : class_pick(z, [&](auto c) {
     constexpr auto kern = &k_r2c_reg<T, decltype(c)::value>;
     hipError_t e2 = allow_lds(reinterpret_cast<const void*>(kern), lds_z);
     if (e2 != hipSuccess) return e2;
