@@ -228,7 +228,6 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
         st.lds = std::max(st.lds, lds[i][p]);
         st.threads = std::max(part.size() == 1 ? 0 : st.threads, threads[i][p]);
       }
-      st.nprob = int(part.size());
       st.total = prefix.back();
       st.grid = kDefaultGrid;
       st.kahan = kahan;

@@ -267,7 +267,6 @@ struct C2rBA {
 struct BatchStage {
   const void* args = nullptr;
   const int* prefix = nullptr;
-  int nprob = 0;
   int total = 0;
   size_t lds = 0;
   int grid = 0;
