@@ -67,15 +67,17 @@ constexpr long long kSpreadWaves = 5120;
 // Whether the patches of several rounds of slots take one bin group per work
 // item instead of two. Their items then read the slots twice as often (253
 // instead of 188 MB for 16384 sensors on a 384^2 grid), which pays where the
-// launch ends in a tail: items that fill the device less than twice over (a
-// 192^2 grid in FP64: 52 us so, 59 us with two groups), or a longest item well
-// above the waves' average share (9 rounds in the densest patch of the same
-// grid: 54 and 94 us). Elsewhere it only cost: 384^2 grid, 193 against 180 us;
-// 288^2 in FP64, 165 against 153 us. rounds: over all patches, at least one
-// each; most: of the largest patch.
+// launch ends in a tail: items that fill the device less than two and a half
+// times (a 192^2 grid in FP64, 5184 items: 52 us so, 59 us with two groups;
+// 11264 items at 12-point footprints on 256^2, 149 and 152 us per call), or a
+// longest item well above the waves' average share (9 rounds in the densest
+// patch of the 192^2 grid: 54 and 94 us). Elsewhere it only cost: 14336 items
+// on 256^2, 54 against 52 us; 384^2 grid, 193 against 180 us; 288^2 in FP64,
+// 165 against 153 us. rounds: over all patches, at least one each; most: of
+// the largest patch.
 inline bool spread_split(long long patches, long long rounds, long long most, int nchunks) {
   const long long items = patches * ((nchunks + 1) / 2);
-  return items < 2 * kSpreadWaves || 4 * (2 * most) * kSpreadWaves > 5 * rounds * nchunks;
+  return 2 * items < 5 * kSpreadWaves || 4 * (2 * most) * kSpreadWaves > 5 * rounds * nchunks;
 }
 
 }  // namespace patsz

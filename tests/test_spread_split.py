@@ -21,6 +21,7 @@ CASES = [
     ((2304, 4171, 40, 34), True),    # one far denser patch
     ((1296, 2600, 3, 26), False),    # 288^2 grid: 16848 items
     ((1024, 1309, 2, 27), False),    # 256^2 grid: 14336 items
+    ((1024, 2048, 3, 21), True),     # the same with a narrower band: 11264 items
     ((1, 1, 1, 1), True),
     ((1 << 24, 1 << 26, 1 << 20, 512), False),  # no overflow at the largest grids
 ]
