@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <type_traits>
 
 #include "kernels_common.hpp"
 
@@ -519,7 +520,7 @@ hipError_t launch_inverse(const DevPlan& p, void* Fh, T* f, hipStream_t s) {
 
 // Real-to-complex z pass with its passes in LDS: packed rows with the plane
 // l = Nz/2 at every length, or rows of pitch_f without it at the lengths of
-// CtInverse (others return hipErrorInvalidValue).
+// CtForwardZ (others return hipErrorInvalidValue).
 template <typename T, bool PLANE>
 static hipError_t launch_r2c_z(const DevPlan& p, const T* f, cx<T>* D, hipStream_t s) {
   const FftCfg cfg = inv_cfg();
@@ -528,7 +529,7 @@ static hipError_t launch_r2c_z(const DevPlan& p, const T* f, cx<T>* D, hipStream
   const long long nrows = (long long)p.Nx * p.Ny;
   if ((rows + 1) / 2 * p.Nz > kFftMaxV * cfg.threads || rows * (p.Nz / 2 + 1) > kFftMaxV * cfg.threads)
     return hipErrorInvalidValue;
-  return ct_pick(CtInverse{}, p.Nz, [&](auto c) {
+  return ct_pick(std::conditional_t<PLANE, CtInverse, CtForwardZ>{}, p.Nz, [&](auto c) {
     constexpr int NCT = decltype(c)::value;
     if constexpr (PLANE || NCT > 0) {
       constexpr auto kern = &k_r2c_z<T, NCT, PLANE>;
@@ -562,10 +563,9 @@ hipError_t launch_forward3d_reg(const DevPlan& p, const T* f, void* Dh, hipStrea
   const long long nrows = (long long)p.Nx * p.Ny;
   const Fft2Raw z = fft2_shape<T>(p.f_Nz, fft_seqs<T>(p.f_Nz, kFftThreads, kC2rSeqs));
   const size_t lds_z = fft2_slots(z) * sizeof(cx<T>);
-  // the lengths with a compile-time form stay with it in the z pass (256^3:
-  // 28 us, 40 us as register passes; 80 points: 9.8 and 6.0 us)
+  // the lengths of CtForwardZ stay with the compile-time form in the z pass
   bool fixed = false;
-  (void)ct_pick(CtInverse{}, p.Nz, [&](auto c) {
+  (void)ct_pick(CtForwardZ{}, p.Nz, [&](auto c) {
     fixed = decltype(c)::value > 0;
     return hipSuccess;
   });

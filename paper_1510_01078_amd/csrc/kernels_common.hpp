@@ -129,6 +129,11 @@ __host__ __device__ constexpr int ct_maxb(int n, int cap) {
 using CtLateral = CtList<256, 288, 384, 512>;
 using CtInverse = CtList<128, 192, 256, 512>;
 using CtTemporal = CtList<1920, 2048, 2560, 4096>;
+// the forward model's real-to-complex z pass: of CtInverse the lengths whose
+// compile-time form beats the register passes (image transforms 78 and 82 us
+// at 256^3, a call 76.4 and 77.4 us at 128^3; at 192^3 41 and 38, at 128 x 128
+// x 512 45 and 42 us)
+using CtForwardZ = CtList<128, 256>;
 // the forward model's fused x-FFT + interpolation (instantiated per footprint
 // width and strip height as well) keeps the shorter list
 using CtFused = CtList<256, 384, 512>;
