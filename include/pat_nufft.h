@@ -265,8 +265,9 @@ pat_status pat_batch_set_grid(pat_batch* batch, int32_t blocks);
 
 /* f[p] = R g[p] for every problem p: g and f are HOST arrays of `count`
  * DEVICE pointers with the layouts of pat_reconstruct. Enqueues a kernel per
- * stage and group on `stream` (up to four where the problems' FFT lengths fall
- * into several classes); no allocation, no synchronisation, so the call can
+ * stage and group on `stream`, or one per class of FFT lengths among the
+ * problems (at most four in a lateral or image transform, nine in the temporal
+ * one, one in the spread); no allocation, no synchronisation, so the call can
  * be captured into a HIP graph. Inputs and outputs must not overlap. */
 pat_status pat_batch_reconstruct(pat_batch* batch, const void* const* g, void* const* f, void* stream);
 
@@ -298,9 +299,9 @@ pat_status pat_reconstruct_noalloc(pat_plan* plan, const void* g, void* f, void*
  * synchronises on the last event, writes the summed milliseconds of each
  * stage to ms[0..nstage-1] (nstage <= PAT_TIMING_STAGES), the number of
  * recorded calls to *calls, and destroys the events. Stages: 0 temporal FFT,
- * 1 lateral spread, 2 lateral FFT along x, 3 lateral FFT along y with
- * deconvolution, 4 temporal interpolation and weight fused with the inverse
- * FFT along x (pat_spectrum: the interpolation alone), 5 the inverse FFT's
+ * 1 lateral spread, 2 lateral FFT along x, 3 lateral FFT along y, 4 temporal
+ * interpolation, deconvolution and weight fused with the inverse FFT along x
+ * (pat_spectrum: without that FFT), 5 the inverse FFT's
  * y and z passes (the spread and x-FFT run in rounds over bins; their rounds
  * are summed). Calls
  * of pat_forward and pat_forward_dxy add each kernel's time to the stage it

@@ -58,11 +58,11 @@ bool radix_plan(int n, patk::FftRaw& f) {
 // Radices of the two-pass register transform: the largest r1 <= r2 of the
 // radices the kernels hold (every even 2,3,5-smooth length up to 640 has a
 // pair; longer ones need radices whose registers cost occupancy, and keep the
-// passes in LDS). 288 and 320 points take r2 = 16 with r1 = 18 and 20: the
-// first pass then loads whole 128-byte lines and fills its waves (x and y
-// passes of a 192^3 image 84.8 and 49.3 us, 93.3 and 54.2 us as 16 * 18; the
-// same order lost 10 to 20 % at 384 = 24 * 16 and 480 = 30 * 16, whose first
-// pass holds more registers, and at 192 = 16 * 12).
+// passes in LDS). 288 and 320 points take the larger radix first, 18 * 16 and
+// 20 * 16, because it measured faster there (x and y passes of a 192^3 image
+// 84.8 and 49.3 us, 93.3 and 54.2 us as 16 * 18); it lost 10 to 20 % at 384 =
+// 24 * 16 and 480 = 30 * 16, whose first pass holds more registers, and lost at
+// 192 = 16 * 12, so this is a table of two lengths and no rule.
 void two_pass_plan(int n, patk::Fft2Raw& f) {
   f = patk::Fft2Raw{0, 0, 0, 0, 0, 0, nullptr};
   if (n > 640) return;
@@ -468,7 +468,7 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   // base(s) .. base(s) + w_t - 1 with s = |K| s_per_k non-decreasing in |k| and
   // l, so x-mode j needs base(s(j,0,0)) .. base(s(j,Ny/2,Nz/2)) + w_t - 1; one
   // bin of margin on each side (host and device may round |K| apart), widened
-  // to whole groups of the y-FFT's bins. The compile-time x-FFT writes and
+  // to whole groups of the y-FFT's bins. The x-FFT writes and
   // the y-FFT transforms only these (x mode, bin) pairs.
   std::vector<int> jr(2 * size_t(d.nx));
   {
@@ -624,7 +624,8 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   // y passes' runs of 8 rows and bins and the spread's 16-bin reads do not
   // straddle lines: the non-temporal partial lines of 270-point rows cost the
   // spread half of its rate. A plan that fits the allocation-free call's
-  // scratch only without the padding keeps its rows packed.
+  // scratch only without the padding keeps its rows packed, in every call (its
+  // tables and workspace size are one for all of them).
   layout(1);
   const size_t packed = P->ws_bytes;
   layout(int(128 / cxb));
@@ -632,7 +633,10 @@ pat_status build_tables(pat_plan* P, hipStream_t stream) {
   P->forward_ok = patk::scatter_lds_bytes<T>(dp) + patk::kStaticLdsMargin <= (size_t)lds_limit;
   P->forward_fused = patk::fused_interp_ok<T>(dp, (size_t)lds_limit - patk::kStaticLdsMargin);
   // two home-tile rows per fused strip (32 + w - 1 grid rows for 32: less
-  // halo recomputation, measured faster) where the work-group LDS holds them
+  // halo recomputation, measured faster) where the work-group LDS holds them.
+  // The register form is then asked for that height alone: where its second
+  // pass needs more threads (480 points at w = 8, 432 at w = 12, some from 432
+  // on at w = 16) the forward model keeps the passes in LDS.
   dp.fused_strip =
       dp.tiles_y >= 2 && patk::fused_interp_lds<T>(dp, 2) + patk::kStaticLdsMargin <= (size_t)lds_limit ? 2 : 1;
   P->forward_reg = P->forward_fused && dp.f_ny.two.r1 &&
@@ -726,8 +730,9 @@ pat_status run_image_in(pat_plan* P, const void* f, void* g, void* ws, hipStream
   const int deriv = op == OP_FORWARD_DX ? 1 : (op == OP_FORWARD_DY ? 2 : 0);
   mark(-1, 5);
   // the register transforms; the position derivatives keep the passes in LDS
-  // at every length: they enter gradients that the autograd wrapper returns in
-  // double, and so keep their bits
+  // at every length: another order of their sums would change a gradient that
+  // the autograd wrapper computes in single precision and returns in double by
+  // 2e-6, within its rounding but not the same digits
   const bool reg3 = op == OP_FORWARD && dp.f_Nx.two.r1 && dp.f_Ny.two.r1 && dp.f_Nz.two.r1;
   const T* image = static_cast<const T*>(f);
   if ((e = reg3 ? patk::launch_forward3d_reg<T>(dp, image, B, s) : patk::launch_forward3d<T>(dp, image, B, s)) !=

@@ -3,7 +3,8 @@
 // launch per stage, kernel variant and group of problems. A stage's work items
 // are the blocks of the variant's problems (problem after problem);
 // per-problem arguments are uploaded once at creation, so a call only enqueues
-// seven stages of one to four kernels per group.
+// seven stages per group: one kernel for the spread, one per variant for the
+// others (at most nine in the temporal stage, four in each later one).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -152,7 +153,7 @@ pat_status build_group(pat_batch* B, BatchGroup& G, unsigned char* ws, hipStream
     lds[2][p] = (fx.r1 ? patk::fft2_slots(fx) : size_t(rows) * patk::lseq(d.n_x) + d.n_x) * c;
     variant[2][p] = fx.r1 ? patk::reg_class(fx) : 0;
     threads[2][p] = fx.r1 ? patk::fft2_threads(fx) : cfg.threads;
-    // stage 3: FFT along y with deconvolution
+    // stage 3: FFT along y
     const int bins = patk::fft_bins<T>(d.f_ny, cfg.threads, cfg.cap);
     const patk::Fft2Raw fy = d.f_ny.two.r1 ? patk::fft2_shape<T>(d.f_ny, bins) : d.f_ny.two;
     if (!fy.r1 && (bins * d.n_y > kFft || bins * d.Ny > kFft)) return PAT_ERR_UNSUPPORTED;

@@ -13,8 +13,9 @@ namespace patk {
 // Stage 5: equispaced inverse 3-D FFT (step 3 of the NEDNER list). The x pass
 // runs with the gather; here the in-place inverse transform along y of
 // F[jj][kk][l], l = 0..Nz/2-1 (rows of `pitch` elements; the plane l = Nz/2 is
-// zero and not stored), then a complex-to-real transform along z. The forward
-// model's transforms (below) keep the plane and the passes in LDS.
+// zero and not stored), then a complex-to-real transform along z. Of the
+// transposes, the forward model's take the same rows and register passes, the
+// position derivatives' packed rows with the plane and the passes in LDS.
 // ---------------------------------------------------------------------------
 
 // Two-pass register transform along x or y, in place: each pass's threads walk

@@ -131,11 +131,11 @@ inline int spread_groups(const DevPlan& p, int nchunks) {
 // reverse order): forward3d -> scatter -> fft_y_t -> fft_x_t -> interp ->
 // temporal_t.
 
-// weighted = true: traces scaled by h_m dt (reconstruction); false: unit
-// weights (adjoint of the forward model).
-// Launch shape of the register form (r1 = 0: passes in LDS).
+// Launch shape of the temporal FFT's register form (r1 = 0: passes in LDS).
 template <typename T>
 Fft3Raw temporal_shape(const DevPlan& p);
+// weighted = true: traces scaled by h_m dt (reconstruction); false: unit
+// weights (adjoint of the forward model).
 template <typename T>
 hipError_t launch_temporal(const DevPlan& p, const T* g, void* Gt, bool weighted, hipStream_t s);
 // Bins [b_begin, b_end) of the band: U holds only those bins (U[b - b_begin]),
@@ -211,9 +211,9 @@ hipError_t launch_temporal_t(const DevPlan& p, const void* Gt, T* g, hipStream_t
 // ---------------------------------------------------------------------------
 // Batched launches: one launch per stage and kernel variant (class of FFT
 // lengths) serves up to kGroupMax problems of different sizes. The work items
-// of a launch are the blocks of its problems, numbered problem after problem; prefix[p] is the first item of
-// problem p (prefix[nprob] = total). Each problem's arguments sit in a device
-// table; only the per-call input and output pointers travel in BatchIO (a
+// of a launch are the blocks of its problems, numbered problem after problem;
+// prefix[p] is the first item of problem p (the total behind the last problem,
+// then INT_MAX). Each problem's arguments sit in a device table; only the per-call input and output pointers travel in BatchIO (a
 // kernel argument), so a batched call allocates and synchronises nothing.
 // ---------------------------------------------------------------------------
 constexpr int kBatchMax = 64;
@@ -224,7 +224,7 @@ struct BatchIO {
   void* out[kGroupMax];
 };
 
-struct FftView {  // plain data (it also lives in LDS)
+struct FftView {  // plain data, in the batch's argument tables
   int n, npass;
   const void* pass;
   const void* tw;
@@ -271,7 +271,8 @@ struct BatchStage {
   size_t lds = 0;
   int grid = 0;
   bool kahan = false;  // spread with compensated summation
-  int variant = 0;     // FFT stages: class of the problems' two-pass transforms (0: longer lengths)
+  int variant = 0;     // FFT stages: class of the problems' register transforms (0: passes in LDS), in the
+                       // temporal stage + 64 * its form
   int threads = 256;   // FFT stages: work-group size
 };
 

@@ -113,7 +113,7 @@ constexpr int kGatherCap = 8;
 static inline FftCfg inv_cfg() { return FftCfg{256, kInvCap, 0}; }
 
 // Lengths with compile-time FFT instantiations (fft_ct), for the kernels that
-// keep their passes in LDS: the position derivatives' (whose bits stay as they
+// keep their passes in LDS: the position derivatives' (whose digits stay as they
 // are) and the forward model's temporal transform and real-to-complex z pass,
 // where they are the faster form. A launcher calls
 // f(std::integral_constant<int, N>) for a listed length and

@@ -411,8 +411,7 @@ hipError_t launch_fft_y_t_reg(const DevPlan& p, const void* Gh, void* V, hipStre
 }
 
 // Passes in LDS: other lengths, the two-kernel interpolation, and the position
-// derivatives at every length (they enter gradients that the autograd wrapper
-// returns in double; this form's sums keep their bits).
+// derivatives at every length (whose digits stay as they are).
 template <typename T, int NCT>
 __global__ __launch_bounds__(kFftThreads) void k_fft_y_t(const cx<T>* __restrict__ Gh, int nb, int Nx, int Ny,
                                                        int bins, const T* __restrict__ dcx,
