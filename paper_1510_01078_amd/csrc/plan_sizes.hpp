@@ -65,9 +65,9 @@ inline Band temporal_band(double sigma_t, int Nt, int wt, double kmax, double c,
 constexpr long long kSpreadWaves = 5120;
 
 // Whether the patches of several rounds of slots take one bin group per work
-// item instead of two. Their items then read the slots twice as often (253
-// instead of 188 MB for 16384 sensors on a 384^2 grid), which pays where the
-// launch ends in a tail: items that fill the device less than two and a half
+// item instead of two. That makes half again as many items (63126 instead of
+// 41472 for 16384 sensors on a 384^2 grid), each with its chain of dependent
+// loads at the start, which pays where the launch ends in a tail: items that fill the device less than two and a half
 // times (a 192^2 grid in FP64, 5184 items: 52 us so, 59 us with two groups;
 // 11264 items at 12-point footprints on 256^2, 149 and 152 us per call), or a
 // longest item well above the waves' average share (9 rounds in the densest
